@@ -347,6 +347,9 @@ def main():
     for k, (tms, n) in kern.items():
         if n:
             kernels[k] = {"avg_ms": tms / n, "launches_per_step": n / args.steps, "ms_per_step": tms / args.steps}
+    if "gemm_vt" not in kernels and "gemm_vt" in flops:
+        # the projection went as one launch: its flops are the [Q|K] and the value product's
+        flops["gemm"] += flops.pop("gemm_vt")
     for k, f in flops.items():
         if k in kernels:
             # algorithmic flops of one launch: the family's share of a step over its launches

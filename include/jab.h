@@ -414,8 +414,9 @@ const char *jab_last_error(void);
  * bracketed by hipEvents on the launch stream.  jab_timing_read synchronises
  * those events and returns, per kernel family (JAB_KT_*), the summed duration
  * in milliseconds and the launch count since the last reset. */
-/* JAB_KT_GEMM: the projection of Q and K (or the single projection of jab_project);
- * JAB_KT_GEMM_VT: the projection that writes V transposed; JAB_KT_KL: the KL
+/* JAB_KT_GEMM: the projection of Q and K (or the single projection of jab_project, or the whole
+ * projection where the sizes let one launch write Q, K and V transposed);
+ * JAB_KT_GEMM_VT: the launch that writes V transposed, where it is separate; JAB_KT_KL: the KL
  * attention-map kernel of jab_loss_fwd_kl. */
 enum { JAB_KT_QUANT = 0, JAB_KT_GEMM = 1, JAB_KT_ATTN = 2, JAB_KT_REDUCE = 3,
        JAB_KT_ATTN_BWD = 4, JAB_KT_DW_GEMM = 5, JAB_KT_MISC = 6, JAB_KT_GEMM_VT = 7, JAB_KT_KL = 8,

@@ -144,13 +144,10 @@ size_t qk_main_bytes(const jab_problem &p) {
     const Dims D = dims_of(p);
     return (size_t)((D.M + QK_SLACK_ROWS) * (D.Hq + D.Hkv) * D.dh) * esize(p.dtype);
 }
-// 16-bit RoPE shapes whose [Q|K] GEMM cannot take the rotation in its epilogue project into an
+// 16-bit RoPE with a head_dim whose rotation the [Q|K] GEMM's epilogue does not take: projected into an
 // fp32 buffer first (the rotation acts on the projection before its rounding)
 bool rope_needs_f32(const jab_problem &p) {
-    const Dims D = dims_of(p);
-    const int nqk = (int)((D.Hq + D.Hkv) * D.dh);
-    return p.rope_theta > 0.f && p.dtype != JAB_F32 &&
-           !jab::gemm_rope_fuses(p.dtype, (int)D.M, nqk, (int)D.d, nqk, p.head_dim);
+    return p.rope_theta > 0.f && p.dtype != JAB_F32 && !jab::gemm_rope_fuses(p.dtype, p.head_dim);
 }
 size_t rope_f32_bytes(const jab_problem &p) {
     const Dims D = dims_of(p);
@@ -358,52 +355,53 @@ jab_status run_project(const jab_problem &p, const void *x, const void *w_operan
     return JAB_OK;
 }
 
-// [Q|K] = X W_QK^T and V^T = W_V X^T (same matrix-core kernel, operands swapped).
+// [Q|K] = X W_QK^T and V^T = W_V X^T.
 jab_status run_project_split(const jab_problem &p, const void *x, const void *w_operand, const Proj &pr,
                              hipStream_t st) {
     const Dims D = dims_of(p);
-    const int nqk = (int)((D.Hq + D.Hkv) * D.dh);
-    const void *w_v = static_cast<const char *>(w_operand) + (size_t)nqk * D.d * esize(p.dtype);
-    if (p.rope_theta > 0.f) {
-        // the rotary embedding turns the projection as accumulated (fp32) and rounds once: in the
-        // [Q|K] GEMM's epilogue where the persistent kernel takes the shape, else as a pass over an
-        // fp32 projection
-        char *tail = static_cast<char *>(pr.qk) + qk_main_bytes(p);
-        float2 *tab = reinterpret_cast<float2 *>(tail);
-        float4 *tab_t = reinterpret_cast<float4 *>(tail + rope_tab_bytes(p) / 2);
-        JAB_RUN(JAB_KT_MISC, st, "rotary table",
-                jab::launch_rope_table(p.seq_len, p.head_dim, p.rope_theta, tab, tab_t, st));
-        const int heads = p.n_heads + p.n_kv_heads;
-        if (jab::gemm_rope_fuses(p.dtype, (int)D.M, nqk, (int)D.d, nqk, p.head_dim)) {
-            JAB_RUN(JAB_KT_GEMM, st, "projection GEMM (Q, K) with the rotary embedding",
-                    jab::launch_gemm_nt_rope(p.dtype, x, w_operand, pr.qk, (int)D.M, nqk, (int)D.d, (int)D.d,
-                                             (int)D.d, nqk, p.head_dim, p.seq_len, tab_t, st));
-        } else if (p.dtype == JAB_F32) {
-            JAB_RUN(JAB_KT_GEMM, st, "projection GEMM (Q, K)",
-                    jab::launch_gemm_nt(p.dtype, x, w_operand, pr.qk, (int)D.M, nqk, (int)D.d, (int)D.d, (int)D.d,
-                                        nqk, st));
-            JAB_RUN(JAB_KT_MISC, st, "rotary embedding",
-                    jab::launch_rope_rows(p.dtype, static_cast<const float *>(pr.qk), nqk, pr.qk, nqk, D.M,
-                                          p.seq_len, heads, p.head_dim, tab, st));
-        } else {
-            float *y32 = reinterpret_cast<float *>(tail + rope_tab_bytes(p));
-            JAB_RUN(JAB_KT_GEMM, st, "projection GEMM (Q, K), fp32",
-                    jab::launch_gemm_nt_f32out(p.dtype, x, w_operand, y32, (int)D.M, nqk, (int)D.d, (int)D.d,
-                                               (int)D.d, nqk, 1.f, st, nullptr, nullptr));
-            JAB_RUN(JAB_KT_MISC, st, "rotary embedding",
-                    jab::launch_rope_rows(p.dtype, y32, nqk, pr.qk, nqk, D.M, p.seq_len, heads, p.head_dim, tab,
-                                          st));
-        }
-    } else {
-        JAB_RUN(JAB_KT_GEMM, st, "projection GEMM (Q, K)",
-                jab::launch_gemm_nt(p.dtype, x, w_operand, pr.qk, (int)D.M, nqk, (int)D.d, (int)D.d, (int)D.d,
-                                    nqk, st));
+    const int nqk = (int)((D.Hq + D.Hkv) * D.dh), nv = (int)(D.Hkv * D.dh), d = (int)D.d;
+    const int ldv = (int)vt_ld(p);
+    // both outputs in one launch, or [Q|K] and then the values
+    auto project = [&](const float4 *tab_t, const char *what) -> jab_status {
+        const bool one = jab::project_is_one_launch(p.dtype, p.batch, p.seq_len, nqk, nv, d, ldv);
+        JAB_RUN(JAB_KT_GEMM, st, what,
+                jab::launch_project(p.dtype, x, w_operand, pr.qk, one ? pr.vt : nullptr, p.batch, p.seq_len, nqk, nv,
+                                    d, ldv, p.head_dim, tab_t, st));
+        if (one) return JAB_OK;
+        JAB_RUN(JAB_KT_GEMM_VT, st, "projection GEMM (V transposed)",
+                jab::launch_project(p.dtype, x, w_operand, nullptr, pr.vt, p.batch, p.seq_len, nqk, nv, d, ldv,
+                                    p.head_dim, nullptr, st));
+        return JAB_OK;
+    };
+    if (!(p.rope_theta > 0.f)) return project(nullptr, "projection GEMM");
+    // the rotary embedding turns the projection as accumulated (fp32) and rounds once: in the [Q|K]
+    // GEMM's epilogue (16-bit, head_dim 64 or 128), else as a pass over an fp32 projection
+    char *tail = static_cast<char *>(pr.qk) + qk_main_bytes(p);
+    float2 *tab = reinterpret_cast<float2 *>(tail);
+    float4 *tab_t = reinterpret_cast<float4 *>(tail + rope_tab_bytes(p) / 2);
+    JAB_RUN(JAB_KT_MISC, st, "rotary table",
+            jab::launch_rope_table(p.seq_len, p.head_dim, p.rope_theta, tab, tab_t, st));
+    const int heads = p.n_heads + p.n_kv_heads;
+    if (jab::gemm_rope_fuses(p.dtype, p.head_dim)) {
+        return project(tab_t, "projection GEMM with the rotary embedding");
     }
+    jab_status s = JAB_OK;
+    if (p.dtype == JAB_F32) {
+        if ((s = project(nullptr, "projection GEMM"))) return s;
+        JAB_RUN(JAB_KT_MISC, st, "rotary embedding",
+                jab::launch_rope_rows(p.dtype, static_cast<const float *>(pr.qk), nqk, pr.qk, nqk, D.M, p.seq_len,
+                                      heads, p.head_dim, tab, st));
+        return JAB_OK;
+    }
+    float *y32 = reinterpret_cast<float *>(tail + rope_tab_bytes(p));
+    JAB_RUN(JAB_KT_GEMM, st, "projection GEMM (Q, K), fp32",
+            jab::launch_gemm_nt_f32out(p.dtype, x, w_operand, y32, (int)D.M, nqk, d, d, d, nqk, 1.f, st, nullptr,
+                                       nullptr));
+    JAB_RUN(JAB_KT_MISC, st, "rotary embedding",
+            jab::launch_rope_rows(p.dtype, y32, nqk, pr.qk, nqk, D.M, p.seq_len, heads, p.head_dim, tab, st));
     JAB_RUN(JAB_KT_GEMM_VT, st, "projection GEMM (V transposed)",
-            jab::launch_gemm_nt_vt(p.dtype, w_v, x, pr.vt, (int)(D.Hkv * D.dh), (int)D.M, (int)D.d,
-                                   (int)D.d, (int)D.d, (int)vt_ld(p), p.seq_len, st));
-    JAB_RUN(JAB_KT_MISC, st, "value padding",
-            jab::launch_zero_vt_pad(p.dtype, pr.vt, (int)(D.Hkv * D.dh), vt_ld(p), p.batch, p.seq_len, st));
+            jab::launch_project(p.dtype, x, w_operand, nullptr, pr.vt, p.batch, p.seq_len, nqk, nv, d, ldv,
+                                p.head_dim, nullptr, st));
     return JAB_OK;
 }
 

@@ -86,21 +86,6 @@ hipError_t dispatch_nv<F32>(const AttnArgs &a, hipStream_t st) {
     return dispatch_dh<F32, 1>(a, st);
 }
 
-// zero the padding columns [T, Tp) of every sequence of a transposed value tensor
-template <typename E>
-__global__ __launch_bounds__(256) void zero_vt_pad_kernel(E *__restrict__ vt, int rows, int64_t ld, int batch,
-                                                          int T, int Tp) {
-    const int w = Tp - T;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t n = (int64_t)rows * batch * w;
-    if (i >= n) return;
-    const int c = (int)(i % w);
-    const int64_t rb = i / w;
-    const int bb = (int)(rb % batch);
-    const int64_t r = rb / batch;
-    vt[r * ld + (int64_t)bb * Tp + vt_perm(T + c)] = E(0);
-}
-
 // V [B*T][ldv] (natural token order) from V^T [rows][B*Tp] (vt_perm order)
 template <typename E>
 __global__ __launch_bounds__(256) void vt_to_v_kernel(const E *__restrict__ vt, E *__restrict__ v, int rows,
@@ -162,16 +147,6 @@ hipError_t launch_attn_fwd(int dtype, const AttnArgs &a, hipStream_t st) {
     case F16: return dispatch_nv<F16>(a, st);
     default: return dispatch_nv<BF16>(a, st);
     }
-}
-
-hipError_t launch_zero_vt_pad(int dtype, void *vt, int rows, int64_t ld, int batch, int T, hipStream_t st) {
-    const int Tp = vt_pad(T);
-    if (Tp == T) return hipSuccess;
-    const int64_t n = (int64_t)rows * batch * (Tp - T);
-    const dim3 grid((unsigned)((n + 255) / 256)), block(256);
-    if (dtype == F32) zero_vt_pad_kernel<float><<<grid, block, 0, st>>>(static_cast<float *>(vt), rows, ld, batch, T, Tp);
-    else zero_vt_pad_kernel<uint16_t><<<grid, block, 0, st>>>(static_cast<uint16_t *>(vt), rows, ld, batch, T, Tp);
-    return hipGetLastError();
 }
 
 hipError_t launch_vt_to_v(int dtype, const void *vt, void *v, int rows, int64_t ldt, int batch, int T, int ldv,

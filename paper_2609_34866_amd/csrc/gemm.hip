@@ -5,30 +5,26 @@
 // [tokens][d_model] and B = W_hat [R][d_model] (one row per output channel), both
 // k-contiguous, accumulated in fp32 and stored in the storage dtype.
 //
-// gfx950 design (16-bit dtypes, gemm_w4_kernel)
-//  * 256 threads = 4 wavefronts in a 2 x 2 arrangement, one wave per SIMD; a workgroup
-//    computes a 256 x 256 tile, each wave 128 x 128 as 4 x 4 blocks of
-//    v_mfma_f32_32x32x16_{bf16,f16} (256 accumulator registers).  Per k-step a wave reads
-//    4 + 4 operand fragments for 16 MFMAs, two thirds of the LDS traffic per flop of a
-//    128 x 64 wave tile.
-//  * k-tiles of 64 go straight from global memory into LDS (buffer_load_dwordx4 ... lds: a
-//    scalar resource and k offset, one fixed per-lane offset per instruction, so no vector
-//    address arithmetic) through two 64 KiB stages.  The MUBUF form keeps the LDS counter
-//    ordered, so each MFMA waits only for its own fragments.
-//  * One barrier per stage, before its last k-step.  The stage's refill is spread over that
-//    k-step and the first k-step of the next stage (the other slot is being read then): the
-//    vector-memory path cannot take all of a stage's loads in one k-step without stalling
-//    the wave that issues them.
-//  * Fragment reads for the next k-step are issued every other MFMA slot; 16-byte chunks
-//    are XOR-swizzled per row so the 16 rows served per LDS cycle hit distinct banks.
-//  * The MFMA operands are swapped (B first), so a lane's accumulators hold four
-//    consecutive output columns of one row.  Storage-dtype outputs go through LDS (the ring
-//    is free after the k loop) and leave as whole 512-byte rows; the transposed value
-//    output and fp32 outputs are stored from registers, 8 and 16 bytes per lane.
-//  * Workgroup ids are remapped so that each XCD (ids congruent mod 8 land on the same
-//    XCD) walks a contiguous range of tiles, grouped 8 M-tiles at a time so that
-//    concurrently running tiles share A and B panels in that XCD's L2.
-//  * fp32 inputs use gemm_nt_kernel (4 waves, 128 x 128 tiles, v_mfma_f32_32x32x2_f32).
+// Two kernels (launch_project and the other launchers choose by the sizes, see persistent_pays):
+//  * gemm_w4p_kernel (16-bit): persistent, 256 x 256 tiles, one workgroup of four waves per CU, each
+//    wave 128 x 128 as 4 x 4 blocks of v_mfma_f32_32x32x16_{bf16,f16} (256 accumulator registers; per
+//    k-step a wave reads 4 + 4 operand fragments for 16 MFMAs).
+//  * gemm_small_kernel (every dtype): 128 x 128 or 64 x 64 tiles, two or three workgroups per CU, for
+//    the shapes whose 256-tiles would leave CUs idle, for short K, and for fp32.
+// Common to both:
+//  * k-tiles go straight from global memory into LDS (buffer_load_dwordx4 ... lds: a scalar resource and
+//    k offset, one fixed per-lane offset per instruction, so no vector address arithmetic).  The MUBUF
+//    form keeps the LDS counter ordered, so each MFMA waits only for its own fragments.
+//  * 16-byte chunks are XOR-swizzled per row so the 16 rows served per LDS cycle hit distinct banks.
+//  * The MFMA operands are swapped (B first), so a lane's accumulators hold four consecutive output
+//    columns of one row; outputs leave from registers, 16 bytes per lane.
+//  * Workgroup ids are remapped so that each XCD (ids congruent mod 8 land on the same XCD) walks a
+//    contiguous range of tiles, grouped 8 M-tiles at a time so that concurrently running tiles share A
+//    and B panels in that XCD's L2.
+//  * A projection's [Q|K] and value tiles go in one launch (the value tiles with the operands swapped),
+//    so that neither part leaves the chip half empty: at 4 x 2048 tokens of d 4096 640 + 128 tiles took
+//    3 + 1 rounds of the 256 CUs, together 3 (372 -> 308 us); at 1 x 1999 160 + 32 tiles 189 -> 92 us,
+//    of which 54 us went into 2-byte stores of the ragged value tiles.
 #include <map>
 #include <mutex>
 #include <utility>
@@ -41,32 +37,6 @@
 namespace jab {
 namespace {
 
-template <int DT, int BM, int BN, int NS, int CPR_ = 4, int NW_ = 4>
-struct GemmCfg {
-    typedef typename Mma<DT>::elem elem;
-    static constexpr int EPC = 16 / (int)sizeof(elem);  // elements per 16-byte chunk
-    static constexpr int CPR = CPR_;                    // chunks per k-tile row (4: 64 bytes, 8: 128 bytes)
-    static constexpr int BK = CPR * EPC;                // k elements per stage
-    static constexpr int NW = NW_;                      // waves per workgroup: a 2 x NW/2 grid
-    static constexpr int WM = BM / 2, WN = BN / (NW / 2);
-    static constexpr int FM = WM / 32, FN = WN / 32;
-    static constexpr int KS = BK / Mma<DT>::K;          // MFMA k-steps per stage
-    static constexpr int IA = BM * CPR / 64 / NW, IB = BN * CPR / 64 / NW;   // loads per wave per stage
-    static constexpr int STAGE_BYTES = (BM + BN) * CPR * 16;
-    static constexpr size_t LDS_BYTES = (size_t)NS * STAGE_BYTES;
-};
-
-// Physical 16-byte chunk of logical chunk c in row r of a k-tile row of CPR chunks.  A
-// 16-byte-per-lane LDS read is served 16 lanes (256 bytes, the 64 banks) at a time; the
-// 16 rows such a group touches would collide on a few bank positions, so the chunk index
-// is rotated per row: by (r/4) mod 4 for 64-byte rows, by (r/2) mod 8 for 128-byte rows,
-// which spreads each group over all 16 slots.
-template <int CPR>
-__device__ inline int swz(int r, int c) {
-    if constexpr (CPR == 4) return c ^ ((r >> 2) & 3);
-    else return c ^ ((r >> 1) & 7);
-}
-
 // Output modes:
 //   OUT_DT : C[m][n] in the storage dtype
 //   OUT_F32: C[m][n] = alpha * (A B^T) in fp32
@@ -76,186 +46,9 @@ __device__ inline int swz(int r, int c) {
 //            bits 2 and 3 of t inside each block of 32 tokens (the key order in which an
 //            MFMA lane consumes softmax probabilities, so each lane's eight keys are one
 //            contiguous 16-byte read).
-enum { OUT_DT = 0, OUT_F32 = 1, OUT_VT = 2 };
+//   OUT_QKV: (persistent kernel) [Q|K] tiles as OUT_DT and value tiles as OUT_VT in one launch
+enum { OUT_DT = 0, OUT_F32 = 1, OUT_VT = 2, OUT_QKV = 3 };
 
-template <int DT, int BM, int BN, int NS, int MINB, int OUT, int CPR, int NW>
-__global__ __launch_bounds__(64 * NW, MINB) void gemm_nt_kernel(const void *__restrict__ Ap,
-                                                          const void *__restrict__ Bp,
-                                                          void *__restrict__ Cp, int M, int N, int K,
-                                                          int lda, int ldb, int ldc, int tiles_m,
-                                                          int tiles_n, float alpha, int seq_T,
-                                                          int seq_Tp, int ksplit, void *__restrict__ Cp2) {
-    typedef GemmCfg<DT, BM, BN, NS, CPR, NW> G;
-    typedef typename G::elem elem;
-    typedef Mma<DT> MM;
-    extern __shared__ __align__(16) unsigned char smem[];
-
-    const elem *A = static_cast<const elem *>(Ap);
-    const elem *B = static_cast<const elem *>(Bp);
-
-    // ---- tile order: XCD-contiguous ranges, then groups of 8 M-tiles
-    const int nwg = gridDim.x;
-    int pid = blockIdx.x;
-    if ((nwg & 7) == 0)
-        pid = (pid & 7) * (nwg >> 3) + (pid >> 3);
-    // split-K: workgroups past the tile count take the second half of k into the second output
-    const int split = pid / (tiles_m * tiles_n);
-    pid -= split * tiles_m * tiles_n;
-    if (split) {
-        Cp = Cp2;
-        A += (int64_t)(K / ksplit);
-        B += (int64_t)(K / ksplit);
-    }
-    const int group_tiles = 8 * tiles_n;
-    const int first_m = (pid / group_tiles) * 8;
-    const int gsz = min(tiles_m - first_m, 8);
-    const int pm = first_m + (pid % group_tiles) % gsz;
-    const int pn = (pid % group_tiles) / gsz;
-    const int bm0 = pm * BM, bn0 = pn * BN;
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm0 = (wave / (NW / 2)) * G::WM, wn0 = (wave % (NW / 2)) * G::WN;
-
-    // ---- per-lane global source of each direct-to-LDS load.  A wave instruction fills
-    // 64 consecutive chunks (1 KiB) of the stage; chunk p holds row p/4, physical chunk
-    // p%4, i.e. logical chunk swz(row, p%4).  Rows past the matrix edge are clamped to
-    // the last row: they only feed output rows / columns that are never stored.
-    const elem *srcA[G::IA], *srcB[G::IB];
-#pragma unroll
-    for (int i = 0; i < G::IA; ++i) {
-        const int p = (wave + NW * i) * 64 + lane, r = p / CPR;
-        const int row = min(bm0 + r, M - 1);
-        srcA[i] = A + (int64_t)row * lda + swz<CPR>(r, p % CPR) * G::EPC;
-    }
-#pragma unroll
-    for (int i = 0; i < G::IB; ++i) {
-        const int p = (wave + NW * i) * 64 + lane, r = p / CPR;
-        const int row = min(bn0 + r, N - 1);
-        srcB[i] = B + (int64_t)row * ldb + swz<CPR>(r, p % CPR) * G::EPC;
-    }
-
-    f32x16 acc[G::FM][G::FN];
-#pragma unroll
-    for (int i = 0; i < G::FM; ++i)
-#pragma unroll
-        for (int j = 0; j < G::FN; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-    // ---- operand fetch from LDS for k-step ks of a stage
-    auto frag = [&](const unsigned char *S, int r, int ks) -> typename MM::operand {
-        if constexpr (DT == F32) {
-            const int k = ks * MM::K + (lane >> 5);          // one element per lane
-            const float *p = reinterpret_cast<const float *>(S + (r * CPR + swz<CPR>(r, k >> 2)) * 16);
-            return p[k & 3];
-        } else {
-            const int c = ks * 2 + (lane >> 5);               // eight elements per lane
-            const u32x4 v = *reinterpret_cast<const u32x4 *>(S + (r * CPR + swz<CPR>(r, c)) * 16);
-            return __builtin_bit_cast(typename MM::operand, v);
-        }
-    };
-
-    const int nk = K / G::BK / ksplit;                       // K is a multiple of ksplit * BK
-    // A stage is split into U units of KU k-steps (one unit = 16 MFMAs of 32x32 for the
-    // 16-bit dtypes).  Unit fragments are double-buffered in registers.
-    constexpr int KU0 = 16 / (G::FM * G::FN) > 0 ? 16 / (G::FM * G::FN) : 1;
-    constexpr int KU = KU0 < G::KS / 2 ? KU0 : G::KS / 2;
-    constexpr int U = G::KS / KU;
-    static_assert(G::KS % KU == 0 && U >= 2 && U % 2 == 0, "a stage holds an even number of units");
-    constexpr int PS = G::IA + G::IB;                        // load instructions per wave per stage
-    constexpr int NREAD = KU * (G::FM + G::FN);              // fragment reads per unit
-    constexpr int NMMA = KU * G::FM * G::FN;                 // MFMAs per unit
-    constexpr int NSLOT = NMMA > NREAD ? (NMMA > PS ? NMMA : PS) : (NREAD > PS ? NREAD : PS);
-    typename MM::operand fa[2][KU][G::FM], fb[2][KU][G::FN];
-    // r-th fragment read of unit u of a stage, in the order the MFMAs consume them:
-    // per k-step a[0], b[0..FN-1], a[1..FM-1].
-    auto read_one = [&](const unsigned char *S, int u, int r, int buf) {
-        const int k = r / (G::FM + G::FN), q = r % (G::FM + G::FN), ks = u * KU + k;
-        if (q == 0)
-            fa[buf][k][0] = frag(S, wm0 + (lane & 31), ks);
-        else if (q <= G::FN)
-            fb[buf][k][q - 1] = frag(S + BM * CPR * 16, wn0 + 32 * (q - 1) + (lane & 31), ks);
-        else
-            fa[buf][k][q - G::FN] = frag(S, wm0 + 32 * (q - G::FN) + (lane & 31), ks);
-    };
-    auto mma_one = [&](int m, int buf) {
-        const int k = m / (G::FM * G::FN), i = (m / G::FN) % G::FM, j = m % G::FN;
-        acc[i][j] = MM::mma(fa[buf][k][i], fb[buf][k][j], acc[i][j]);
-    };
-    // one direct-to-LDS load instruction of k-tile `ktile` into stage slot `slot`
-    auto issue_one = [&](int idx, int ktile, int slot) {
-        unsigned char *st = smem + (slot % NS) * G::STAGE_BYTES;
-        const int k0 = (ktile < nk ? ktile : nk - 1) * G::BK;   // past K: harmless re-load
-        if (idx < G::IA)
-            lds_dma16((const void *)(srcA[idx] + k0), st + (wave + NW * idx) * 1024);
-        else
-            lds_dma16((const void *)(srcB[idx - G::IA] + k0), st + BM * CPR * 16 + (wave + NW * (idx - G::IA)) * 1024);
-    };
-
-    // Branch-free steady state with an explicit instruction order: each MFMA slot of a
-    // unit carries at most one LDS fragment read (of the next unit) and one
-    // global->LDS load, fenced by sched_barrier, so the matrix core never waits on a
-    // block of memory instructions.  One barrier per stage, before its last unit: by then
-    // every wave has read (and waited for) all fragments of the stage, so its slot is
-    // refilled with k-tile kt+NS right away, and the next stage has landed.
-#pragma unroll
-    for (int s0 = 0; s0 < NS; ++s0)
-#pragma unroll
-        for (int i = 0; i < PS; ++i) issue_one(i, s0, s0);
-    wait_vmcnt<(NS - 1) * PS>();
-    raw_barrier();
-#pragma unroll
-    for (int r = 0; r < NREAD; ++r) read_one(smem, 0, r, 0);
-    for (int kt = 0; kt < nk; ++kt) {
-        const unsigned char *S = smem + (kt % NS) * G::STAGE_BYTES;
-        const unsigned char *Sn = smem + ((kt + 1) % NS) * G::STAGE_BYTES;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int cur = u & 1;
-            if (u == U - 1) {
-                wait_lgkm0();                                 // this stage's reads are done
-                wait_vmcnt<(NS - 2) * PS>();                  // k-tile kt+1 has landed
-                raw_barrier();
-            }
-#pragma unroll
-            for (int m = 0; m < NSLOT; ++m) {
-                if (m < NMMA) mma_one(m, cur);
-                if (m < NREAD) {
-                    if (u < U - 1) read_one(S, u + 1, m, cur ^ 1);
-                    else read_one(Sn, 0, m, cur ^ 1);
-                }
-                if (u == U - 1 && m < PS) issue_one(m, kt + NS, kt);   // refill this stage's slot
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-    }
-    wait_vmcnt<0>();
-
-    // ---- epilogue: D layout -> C rows / columns
-#pragma unroll
-    for (int i = 0; i < G::FM; ++i) {
-#pragma unroll
-        for (int j = 0; j < G::FN; ++j) {
-            const int col = bn0 + wn0 + 32 * j + (lane & 31);
-            if (col >= N) continue;
-            int64_t ccol = col;
-            if constexpr (OUT == OUT_VT)
-                ccol = (int64_t)(col / seq_T) * seq_Tp + vt_perm(col % seq_T);
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int row = bm0 + wm0 + 32 * i + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-                if (row < M) {
-                    if constexpr (OUT == OUT_F32)
-                        static_cast<float *>(Cp)[(int64_t)row * ldc + ccol] = alpha * acc[i][j][e];
-                    else
-                        static_cast<elem *>(Cp)[(int64_t)row * ldc + ccol] = from_f32<DT>(acc[i][j][e]);
-                }
-            }
-        }
-    }
-}
-
-// ---------------------------------------------------------------- 16-bit dtypes
 // XOR key of LDS row r (16-byte chunks of a row of CPR chunks): rotates the chunk index so the
 // 16 rows one LDS cycle serves land on 16 distinct chunk slots
 template <int CPR>
@@ -264,275 +57,267 @@ __device__ inline int w4_key(int r) {
     else return (r >> 2) & 3;
 }
 
-// C tile staged in LDS for the storage-dtype output: 256 rows of 512 bytes; the 16-byte chunk c
-// of row m sits at chunk c ^ (m & 15) and its two 8-byte halves are exchanged when bit 4 of m is
-// set, so the 32 rows written by one half-wave (same logical half-chunk) cover all 64 banks and
-// a row read back by 32 lanes is conflict-free too.
-__device__ inline int ctile_off(int m, int c, int h) {
-    return m * 512 + ((c ^ (m & 15)) << 4) + ((h ^ ((m >> 4) & 1)) << 3);
+// ---------------------------------------------------------------- small tiles
+// One GEMM launch of the small-tile kernel: the product A B^T (rows of A and B k-contiguous) and,
+// for a projection (OUT_DT with nv > 0), the transposed values from the nv rows of B that follow
+// its first N: C2[r][pos] over the padded token positions of a batch of sequences.
+struct SmallArgs {
+    const void *A, *B;
+    void *C, *C2;
+    int M, N, K, lda, ldb, ldc;
+    int nv, ldv, seq_T, seq_Tp, n_tok;   // values: rows, row stride, sequence length, padded, batch * padded
+    float alpha;
+    int ksplit;                          // OUT_F32: parts of K, part p > 0 at C2 + (p - 1) part_stride
+    int64_t part_stride;
+    int tiles_m, tiles_n, tiles_vm, tiles_vn;
+    const float4 *rtab;                  // rotary embedding (RDH > 0): the transposed table
+};
+
+// Tiles of BT x BT, four waves in a 2 x 2 arrangement (BT / 2 square each), for every dtype; the
+// shapes whose 256 x 256 tiles would leave CUs idle, the fp32 products, and k-tiles of 32 (CPR 4).
+// A projection's [Q|K] tiles and value tiles are work items of one launch: a value tile has the
+// weights as its A panel and the tokens as its B panel, in padded token positions, so every block
+// of 32 positions lies in one sequence, leaves in 16-byte stores and holds its pad positions'
+// zeros.
+//
+// The k-tiles (CPR 16-byte chunks per row) stream into a ring of NS stages by MUBUF DMA, one barrier
+// per k-tile; two workgroups per CU cover each other's start-up, barriers and epilogues.  An operand
+// chunk of 16 bytes is one 32x32x16 product of the 16-bit dtypes, and four 32x32x2 products of fp32
+// (half h of the wave takes chunk 2 c + h, element s of both halves is step s: a permutation of k
+// that A and B share), so fp32 reads LDS 16 bytes at a time too.  For the 16-bit dtypes the products
+// and their order are gemm_w4p_kernel's, so the output bits are the same (but for the value tiles
+// that kernel starts at another k-tile).
+template <int DT, int BT, int CPR>
+struct SmallCfg {
+    typedef typename Mma<DT>::elem elem;
+    static constexpr int ES = (int)sizeof(elem), EPC = 16 / ES, BK = CPR * EPC;
+    static constexpr int U = CPR / 2;                      // chunk steps per k-tile
+    static constexpr int FB = BT / 64;                     // 32-row blocks per wave and direction
+    static constexpr int ROWB = CPR * 16, PANEL = BT * ROWB, STAGE = 2 * PANEL;
+    // 64 KiB of stages for the 128-tile (two workgroups per CU), three stages for the 64-tile (three;
+    // measured at 8 x 1024 x 768 x 2304 fp16: four stages 61 us, three 54; the 128-tile with two
+    // stages of 128-byte rows 42 us, with four or five of 64-byte rows 49, with three of 128 51)
+    static constexpr int NS = BT == 64 ? 3 : 65536 / STAGE;
+    static constexpr int DPP = BT * CPR / 256, DPW = 2 * DPP;   // DMA instructions per wave: panel, k-tile
+    static constexpr int RPI = 64 / CPR;                   // rows per DMA instruction
+    static constexpr size_t LDS_BYTES = (size_t)NS * STAGE;
+    static_assert(NS >= 2 && BT % 64 == 0 && DPP >= 1, "small-tile configuration");
+};
+
+template <int DT>
+__device__ inline f32x16 mma_chunk(u32x4 a, u32x4 b, f32x16 c) {
+    if constexpr (DT == F32) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const uint32_t x = a[s], y = b[s];
+            c = Mma<F32>::mma(__builtin_bit_cast(float, x), __builtin_bit_cast(float, y), c);
+        }
+        return c;
+    } else {
+        typedef typename Mma<DT>::operand opnd;
+        return Mma<DT>::mma(__builtin_bit_cast(opnd, a), __builtin_bit_cast(opnd, b), c);
+    }
 }
 
-template <int DT, int OUT, int CPR>
-__global__ __launch_bounds__(256, 1) void gemm_w4_kernel(const void *__restrict__ Ap, const void *__restrict__ Bp,
-                                                         void *__restrict__ Cp, int M, int N, int K, int lda,
-                                                         int ldb, int ldc, int tiles_m, int tiles_n, float alpha,
-                                                         int seq_T, int seq_Tp, int ksplit, void *__restrict__ Cp2) {
-    typedef typename Mma<DT>::elem elem;
-    typedef typename Mma<DT>::operand opnd;
-    constexpr int BK = CPR * 8;               // k elements per stage
-    constexpr int U = BK / 16;                // k-steps per stage
-    constexpr int ROWB = CPR * 16;            // bytes per LDS row of a stage
-    constexpr int HALF = 256 * ROWB;          // bytes of the A part of a stage (B follows)
-    constexpr int STAGE = 2 * HALF;
-    constexpr int NS = 2;                     // stages in the ring
-    constexpr int DPW = 2 * 256 * CPR / 64 / 4;   // DMA instructions per wave per stage (A, then B)
-    constexpr int DPA = DPW / 2;
-    constexpr int RPI = 64 / CPR;             // rows per DMA instruction
-    // k-steps over which a stage refill is spread: two when a stage has four (the second part then
-    // still lands two k-steps before it is waited for), else one
-    constexpr int SPR = U >= 4 ? 2 : 1;
-    constexpr int PER = DPW / SPR;            // refill instructions per k-step
-    static_assert(SPR <= U && 16 % PER == 0 && DPW % SPR == 0, "refill spread");
+// RDH > 0 (128-tile, 16-bit, OUT_DT): the rotary embedding on the [Q|K] tiles, heads of RDH columns, as
+// in gemm_w4p_kernel's epilogue.  A pair (c, c + RDH / 2) has to sit in one wave: at RDH 128 wave
+// column wc takes the 32-column blocks wc and wc + 2 of the tile instead of 2 wc and 2 wc + 1.
+template <int DT, int BT, int CPR, int OUT, int RDH>
+__global__ __launch_bounds__(256, 2) void gemm_small_kernel(SmallArgs g) {
+    typedef SmallCfg<DT, BT, CPR> S;
+    static_assert(RDH == 0 || (OUT == OUT_DT && BT == 128 && DT != F32 && (RDH == 64 || RDH == 128)), "rotary epilogue");
+    constexpr int CB0 = RDH == 128 ? 1 : S::FB, CBJ = RDH == 128 ? 2 : 1;   // column block CB0 wc + CBJ j
+    typedef typename S::elem elem;
     extern __shared__ __align__(16) unsigned char smem[];
-
-    // ---- tile order: XCD-contiguous ranges, then groups of 8 M-tiles; split-K halves
-    const int nwg = gridDim.x;
-    int pid = blockIdx.x;
-    if ((nwg & 7) == 0) pid = (pid & 7) * (nwg >> 3) + (pid >> 3);
-    const int split = pid / (tiles_m * tiles_n);
-    pid -= split * tiles_m * tiles_n;
-    const int k_begin = split * (K / ksplit);
-    if (split) Cp = Cp2;
-    const int group_tiles = 8 * tiles_n;
-    const int first_m = (pid / group_tiles) * 8;
-    const int gsz = min(tiles_m - first_m, 8);
-    const int pm = first_m + (pid % group_tiles) % gsz;
-    const int pn = (pid % group_tiles) / gsz;
-    const int bm0 = pm * 256, bn0 = pn * 256;
-
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int wr = wave >> 1, wc = wave & 1;
-    const int half = lane >> 5, l32 = lane & 31;
+    const int wr = wave >> 1, wc = wave & 1, half = lane >> 5, l32 = lane & 31;
 
-    // ---- DMA sources.  Instruction d < DPA of this wave fills rows RPI (wave + 4 d) .. + RPI - 1
-    // of the A part (d >= DPA: of the B part); lane i writes row + i / CPR, physical chunk i % CPR,
-    // which holds logical chunk (i % CPR) ^ key(row).  Rows past the matrix edge read the last
-    // row: they only feed outputs that are never stored.
-    const char *Ab = static_cast<const char *>(Ap) + ((int64_t)bm0 * lda + k_begin) * (int64_t)sizeof(elem);
-    const char *Bb = static_cast<const char *>(Bp) + ((int64_t)bn0 * ldb + k_begin) * (int64_t)sizeof(elem);
-    const i32x4 rsA = buffer_rsrc(Ab), rsB = buffer_rsrc(Bb);
-    uint32_t voffA[DPA], voffB[DPA];
-#pragma unroll
-    for (int i = 0; i < DPA; ++i) {
-        const int r = RPI * (wave + 4 * i) + lane / CPR, pc = lane % CPR;
-        const int c = pc ^ w4_key<CPR>(r);
-        const int ra = min(bm0 + r, M - 1) - bm0, rb = min(bn0 + r, N - 1) - bn0;
-        voffA[i] = (uint32_t)(ra * lda * 2 + c * 16);
-        voffB[i] = (uint32_t)(rb * ldb * 2 + c * 16);
+    // ---- work item: XCD x (ids congruent to x mod 8) takes a contiguous range; [Q|K] tiles (times
+    // the parts of K) first, in groups of eight row tiles, then the value tiles
+    const int n_items = gridDim.x, x = blockIdx.x & 7;
+    int pid = x * (n_items >> 3) + min(x, n_items & 7) + (blockIdx.x >> 3);
+    const int tiles = g.tiles_m * g.tiles_n;
+    const bool val = OUT == OUT_DT && pid >= tiles;
+    int part = 0, tm = g.tiles_m, tn = g.tiles_n;
+    if (val) {
+        pid -= tiles;
+        tm = g.tiles_vm;
+        tn = g.tiles_vn;
+    } else if (OUT == OUT_F32) {
+        part = pid / tiles;
+        pid -= part * tiles;
     }
-    const int nk = K / BK / ksplit;
-    // d-th DMA instruction of this wave for k-tile `ktile` into ring slot `slot` (k-tiles past the
-    // end re-load the last one into a slot that is never read)
-    auto issue = [&](int d, int ktile, int slot) {
-        const int kk = (ktile < nk ? ktile : nk - 1) * BK * 2;
-        unsigned char *st = smem + slot * STAGE;
-        if (d < DPA) buffer_dma16(rsA, voffA[d], kk, st + (wave + 4 * d) * 1024);
-        else buffer_dma16(rsB, voffB[d - DPA], kk, st + HALF + (wave + 4 * (d - DPA)) * 1024);
+    const int group_tiles = 8 * tn;
+    const int first_m = (pid / group_tiles) * 8;
+    const int gsz = min(tm - first_m, 8);
+    const int bm0 = (first_m + (pid % group_tiles) % gsz) * BT, bn0 = (pid % group_tiles) / gsz * BT;
+    const int nkt = g.K / S::BK;
+    const int kt0 = part * nkt / g.ksplit, nk = (part + 1) * nkt / g.ksplit - kt0;
+
+    // ---- panels.  Value tile: A panel = rows bm0.. of the value weights, B panel = the tokens of
+    // padded positions bn0..; rows past an edge (and pad positions) read a valid row, for outputs
+    // that are not stored (or stored as zero)
+    const int lda = val ? g.ldb : g.lda, ldb = val ? g.lda : g.ldb;
+    const elem *Ap = static_cast<const elem *>(val ? g.B : g.A) + (val ? (int64_t)g.N * lda : 0);
+    const elem *Bp = static_cast<const elem *>(val ? g.A : g.B);
+    const int rows_a = val ? g.nv : g.M;
+    auto token = [&](int n) -> int {          // source row of padded position n
+        const int s = n / g.seq_Tp;
+        return s * g.seq_T + min(n - s * g.seq_Tp, g.seq_T - 1);
+    };
+    const int rb0 = val ? token(min(bn0, g.n_tok - 1)) : bn0;
+    const i32x4 rsA = buffer_rsrc(Ap + (int64_t)bm0 * lda + (int64_t)kt0 * S::BK);
+    const i32x4 rsB = buffer_rsrc(Bp + (int64_t)rb0 * ldb + (int64_t)kt0 * S::BK);
+    uint32_t voffA[S::DPP], voffB[S::DPP];
+#pragma unroll
+    for (int i = 0; i < S::DPP; ++i) {
+        const int r = S::RPI * (wave + 4 * i) + lane / CPR, c = (lane % CPR) ^ w4_key<CPR>(r);
+        const int ra = min(bm0 + r, rows_a - 1) - bm0;
+        const int rb = (val ? token(min(bn0 + r, g.n_tok - 1)) : min(bn0 + r, g.N - 1)) - rb0;
+        voffA[i] = (uint32_t)(ra * lda * S::ES + c * 16);
+        voffB[i] = (uint32_t)(rb * ldb * S::ES + c * 16);
+    }
+    auto issue = [&](int kt, int slot) {      // k-tile kt (past the end: the last again, never read)
+        const int kk = min(kt, nk - 1) * S::BK * S::ES;
+        unsigned char *st = smem + slot * S::STAGE;
+#pragma unroll
+        for (int i = 0; i < S::DPP; ++i) {
+            buffer_dma16(rsA, voffA[i], kk, st + (wave + 4 * i) * 1024);
+            buffer_dma16(rsB, voffB[i], kk, st + S::PANEL + (wave + 4 * i) * 1024);
+        }
     };
 
-    // ---- fragment reads: lane row l32 of the wave's rows, logical chunk 2 ks + half.  The XOR key
-    // of a row depends only on l32, so the four A (B) fragments of a k-step are one per-lane base
-    // plus constant offsets.
+    // ---- fragment reads: row l32 of a 32-row block, logical chunk 2 u + half
     const int key = w4_key<CPR>(l32);
-    uint32_t rda[U], rdb[U];
+    uint32_t rda[S::U], rdb[S::U];
 #pragma unroll
-    for (int ks = 0; ks < U; ++ks) {
-        const int pc = (2 * ks + half) ^ key;
-        rda[ks] = (uint32_t)((wr * 128 + l32) * ROWB + pc * 16);
-        rdb[ks] = (uint32_t)(HALF + (wc * 128 + l32) * ROWB + pc * 16);
+    for (int u = 0; u < S::U; ++u) {
+        const int pc = (2 * u + half) ^ key;
+        rda[u] = (uint32_t)((wr * (BT / 2) + l32) * S::ROWB + pc * 16);
+        rdb[u] = (uint32_t)(S::PANEL + (wc * CB0 * 32 + l32) * S::ROWB + pc * 16);
     }
-    opnd fa[2][4], fb[2][4];
-    // r-th fragment read of a k-step, in the order the MFMAs consume them: a0, b0..b3, a1..a3
-    auto rd = [&](int r, int slot, int ks, int buf) {
-        const unsigned char *base = smem + slot * STAGE;
-        if (r == 0) fa[buf][0] = __builtin_bit_cast(opnd, *(const u32x4 *)(base + rda[ks]));
-        else if (r <= 4) fb[buf][r - 1] = __builtin_bit_cast(opnd, *(const u32x4 *)(base + rdb[ks] + (r - 1) * 32 * ROWB));
-        else fa[buf][r - 4] = __builtin_bit_cast(opnd, *(const u32x4 *)(base + rda[ks] + (r - 4) * 32 * ROWB));
-    };
-
-    f32x16 acc[4][4];
+    f32x16 acc[S::FB][S::FB];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < S::FB; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < S::FB; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
 #pragma unroll
-    for (int s0 = 0; s0 < NS; ++s0)
-#pragma unroll
-        for (int d = 0; d < DPW; ++d) issue(d, s0, s0);
-    wait_vmcnt<DPW>();
-    raw_barrier();
-#pragma unroll
-    for (int r = 0; r < 8; ++r) rd(r, 0, 0, 0);
-
-    // Steady state.  k-step u of stage kt: 16 MFMAs (acc[i][j] += B_j A_i, swapped so a lane's
-    // accumulators run along output columns), a fragment read of the next k-step every other
-    // MFMA slot, and refill loads.  Before the last k-step, one barrier: every wave has read
-    // (and waited for) the stage's other fragments, and stage kt+1 has landed; the stage's slot
-    // is refilled with k-tile kt+2 over that k-step and the first k-step of stage kt+1.
+    for (int s0 = 0; s0 < S::NS - 1; ++s0) issue(s0, s0);
     int slot = 0;
     for (int kt = 0; kt < nk; ++kt) {
-        const int nslot = slot ^ 1;
+        // k-tile kt has landed for every wave, and every wave has read k-tile kt - 1, whose slot
+        // takes k-tile kt + NS - 1
+        wait_lgkm0();
+        wait_vmcnt<(S::NS - 2) * S::DPW>();
+        raw_barrier();
+        issue(kt + S::NS - 1, slot == 0 ? S::NS - 1 : slot - 1);
+        const unsigned char *st = smem + slot * S::STAGE;
+        u32x4 fa[S::U][S::FB], fb[S::U][S::FB];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int cur = u & 1;
-            if (u == U - 1) {
-                wait_lgkm0();
-                wait_vmcnt<0>();
-                raw_barrier();
+        for (int u = 0; u < S::U; ++u)
+#pragma unroll
+            for (int i = 0; i < S::FB; ++i) {
+                fa[u][i] = *reinterpret_cast<const u32x4 *>(st + rda[u] + i * 32 * S::ROWB);
+                fb[u][i] = *reinterpret_cast<const u32x4 *>(st + rdb[u] + i * CBJ * 32 * S::ROWB);
             }
 #pragma unroll
-            for (int m = 0; m < 16; ++m) {
-                const int i = m >> 2, j = m & 3;
-                acc[i][j] = Mma<DT>::mma(fb[cur][j], fa[cur][i], acc[i][j]);
-                if ((m & 1) == 0) {
-                    if (u < U - 1) rd(m >> 1, slot, u + 1, cur ^ 1);
-                    else rd(m >> 1, nslot, 0, cur ^ 1);
-                }
-                constexpr int ST = 16 / PER;
-                if (m % ST == 0) {
-                    if (u == U - 1) issue(m / ST, kt + NS, slot);
-                    else if (u + 1 < SPR && kt > 0) issue((u + 1) * PER + m / ST, kt - 1 + NS, nslot);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-        slot = nslot;
+        for (int u = 0; u < S::U; ++u)
+#pragma unroll
+            for (int i = 0; i < S::FB; ++i)
+#pragma unroll
+                for (int j = 0; j < S::FB; ++j) acc[i][j] = mma_chunk<DT>(fb[u][j], fa[u][i], acc[i][j]);
+        slot = slot == S::NS - 1 ? 0 : slot + 1;
     }
     wait_vmcnt<0>();
 
-    // ---- epilogue.  acc[i][j][4 g + t] = C[row][col + t] with row = wr*128 + 32 i + l32 and
-    // col = wc*128 + 32 j + 8 g + 4 half (tile coordinates).
-    // Storage-dtype outputs go through LDS when every 32-token block of the transposed value output
-    // lies inside one sequence (T a multiple of 32): the tile is written to LDS in destination
-    // order and leaves as whole rows.
-    if (OUT == OUT_DT || (OUT == OUT_VT && (seq_T & 31) == 0)) {
-        // every wave's loads and fragment reads are done before the ring is reused
-        wait_lgkm0();
-        raw_barrier();
+    // ---- epilogue from registers: acc[i][j][4 q + t] = C[row][col + t], row = 32 i + l32, col =
+    // 32 (CB0 wc + CBJ j) + 8 q + 4 half (tile coordinates); 16 bytes per lane and store
+    if constexpr (RDH > 0) {
+        if (!val) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int m = wr * 128 + 32 * i + l32;
+            for (int i = 0; i < S::FB; ++i) {
+                const int t = min(bm0 + wr * (BT / 2) + 32 * i + l32, g.M - 1) % g.seq_T;
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const uint32_t lo = pack2<DT>(acc[i][j][4 * g], acc[i][j][4 * g + 1]);
-                    const uint32_t hi = pack2<DT>(acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
-                    // tile column wc*128 + 32 j + 8 g + 4 half (+0..3); for the value output its
-                    // position inside the 32-token block has bits 2 and 3 exchanged
-                    const int c = OUT == OUT_DT ? 16 * wc + 4 * j + g : 16 * wc + 4 * j + 2 * (g >> 1) + half;
-                    const int h = OUT == OUT_DT ? half : (g & 1);
-                    *reinterpret_cast<uint2 *>(smem + ctile_off(m, c, h)) = make_uint2(lo, hi);
+                for (int e2 = 0; e2 < 8; ++e2) {      // elements 2 e2 and 2 e2 + 1 of a block: one float4
+                    const int q = (RDH == 128 ? 16 * wc : 0) + 4 * (e2 >> 1) + 2 * half + (e2 & 1);
+                    const float4 cs = g.rtab[(int64_t)q * g.seq_T + t];
+                    const float a0 = acc[i][0][2 * e2], b0 = acc[i][1][2 * e2];
+                    const float a1 = acc[i][0][2 * e2 + 1], b1 = acc[i][1][2 * e2 + 1];
+                    acc[i][0][2 * e2] = __builtin_fmaf(a0, cs.x, -(b0 * cs.y));
+                    acc[i][1][2 * e2] = __builtin_fmaf(b0, cs.x, a0 * cs.y);
+                    acc[i][0][2 * e2 + 1] = __builtin_fmaf(a1, cs.z, -(b1 * cs.w));
+                    acc[i][1][2 * e2 + 1] = __builtin_fmaf(b1, cs.z, a1 * cs.w);
                 }
-        }
-        wait_lgkm0();
-        raw_barrier();
-        // 32 rounds of 2 rows x 32 chunks: one store instruction writes two whole 512-byte rows.
-        // A lane keeps its chunk c (8 columns) in every round.
-        const int c = lane & 31;
-        int64_t dcol;
-        int ncol;                                  // valid columns of the chunk
-        if constexpr (OUT == OUT_DT) {
-            dcol = bn0 + 8 * c;
-            ncol = min(8, N - (bn0 + 8 * c));
-        } else {
-            const int n = bn0 + 8 * c;             // tokens of this chunk's 32-block start at n & ~31
-            const int sb = n / seq_T;
-            dcol = (int64_t)sb * seq_Tp + (n - sb * seq_T);
-            ncol = min(8, N - n);
-        }
-#pragma unroll 4
-        for (int it = 0; it < 32; ++it) {
-            const int m = it * 8 + wave * 2 + half;
-            u32x4 v = *reinterpret_cast<const u32x4 *>(smem + ctile_off(m, c, 0) - ((((m >> 4) & 1)) << 3));
-            if ((m >> 4) & 1) v = u32x4{v[2], v[3], v[0], v[1]};
-            const int row = bm0 + m;
-            if (row >= M || ncol <= 0) continue;
-            elem *dst = static_cast<elem *>(Cp) + (int64_t)row * ldc + dcol;
-            if (ncol == 8) {
-                *reinterpret_cast<u32x4 *>(dst) = v;
-            } else {
-                for (int t = 0; t < ncol; ++t) dst[t] = (elem)(v[t >> 1] >> (16 * (t & 1)));
             }
         }
-        return;
     }
-    if constexpr (OUT == OUT_DT) {
-        return;
-    } else if constexpr (OUT == OUT_F32) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int row = bm0 + wr * 128 + 32 * i + l32;
-            if (row >= M) continue;
+    for (int i = 0; i < S::FB; ++i) {
+        const int row = bm0 + wr * (BT / 2) + 32 * i + l32;
+        if (row >= rows_a) continue;
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < S::FB; ++j) {
+            const int colb = bn0 + 32 * (CB0 * wc + CBJ * j);
+            if (val) {
+                if constexpr (OUT == OUT_DT) {
+                    if (colb >= g.n_tok) continue;
+                    const int left = g.seq_T - colb % g.seq_Tp;      // tokens of the block
+                    elem *crow = static_cast<elem *>(g.C2) + (int64_t)row * g.ldv + colb;
+                    float v[16];
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int col = bn0 + wc * 128 + 32 * j + 8 * g + 4 * half;   // columns col .. col + 3
-                    if (col >= N) continue;
-                    float *dst = static_cast<float *>(Cp) + (int64_t)row * ldc + col;
-                    const f32x4 v = f32x4{alpha * acc[i][j][4 * g], alpha * acc[i][j][4 * g + 1],
-                                          alpha * acc[i][j][4 * g + 2], alpha * acc[i][j][4 * g + 3]};
-                    if (col + 4 <= N) {
-                        *reinterpret_cast<f32x4 *>(dst) = v;
+                    for (int e = 0; e < 16; ++e)
+                        v[e] = 8 * (e >> 2) + 4 * half + (e & 3) < left ? acc[i][j][e] : 0.f;
+                    // bits 2 and 3 of the token exchanged: tokens 16 p + 8 b + 4 half + 0..3 sit at
+                    // positions 16 p + 8 half + 4 b + 0..3
+                    if constexpr (DT == F32) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            *reinterpret_cast<f32x4 *>(crow + 16 * (q >> 1) + 8 * half + 4 * (q & 1)) =
+                                f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
                     } else {
-                        for (int t = 0; t < 4 && col + t < N; ++t) dst[t] = v[t];
+#pragma unroll
+                        for (int p = 0; p < 2; ++p)
+                            *reinterpret_cast<u32x4 *>(crow + 16 * p + 8 * half) =
+                                u32x4{pack2<DT>(v[8 * p], v[8 * p + 1]), pack2<DT>(v[8 * p + 2], v[8 * p + 3]),
+                                      pack2<DT>(v[8 * p + 4], v[8 * p + 5]), pack2<DT>(v[8 * p + 6], v[8 * p + 7])};
                     }
                 }
-        }
-    } else {
-        // Column n = token b*T + t goes to b*Tp + perm(t).  With T a multiple of 4, four consecutive
-        // tokens starting at a multiple of 4 stay in one sequence and in order (perm leaves bits 0
-        // and 1 alone): one 8-byte store at the position of the first.
-        const bool quad = (seq_T & 3) == 0;
+            } else if constexpr (OUT == OUT_F32 || DT == F32) {
+                const float al = OUT == OUT_F32 ? g.alpha : 1.f;
+                float *base = static_cast<float *>(OUT == OUT_F32 && part ? g.C2 : g.C) +
+                              (OUT == OUT_F32 && part ? (part - 1) * g.part_stride : 0) + (int64_t)row * g.ldc;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+                for (int q = 0; q < 4; ++q) {
+                    const int col = colb + 8 * q + 4 * half;
+                    const f32x4 v = f32x4{al * acc[i][j][4 * q], al * acc[i][j][4 * q + 1], al * acc[i][j][4 * q + 2],
+                                          al * acc[i][j][4 * q + 3]};
+                    if (col + 4 <= g.N) *reinterpret_cast<f32x4 *>(base + col) = v;
+                }
+            } else {
+                elem *crow = static_cast<elem *>(g.C) + (int64_t)row * g.ldc;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int col = bn0 + wc * 128 + 32 * j + 8 * g + 4 * half;
-                if (col >= N) continue;
-                const int sb = col / seq_T;
-                const int dcol = sb * seq_Tp + vt_perm(col - sb * seq_T);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int row = bm0 + wr * 128 + 32 * i + l32;
-                    if (row >= M) continue;
-                    elem *base = static_cast<elem *>(Cp) + (int64_t)row * ldc;
-                    if (quad && col + 4 <= N) {
-                        const uint32_t lo = pack2<DT>(acc[i][j][4 * g], acc[i][j][4 * g + 1]);
-                        const uint32_t hi = pack2<DT>(acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
-                        *reinterpret_cast<uint2 *>(base + dcol) = make_uint2(lo, hi);
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const int n = col + e;
-                            if (n < N) {
-                                const int nb = n / seq_T;
-                                base[nb * seq_Tp + vt_perm(n - nb * seq_T)] = from_f32<DT>(acc[i][j][4 * g + e]);
-                            }
-                        }
-                    }
+                for (int p = 0; p < 2; ++p) {
+                    uint32_t a0 = pack2<DT>(acc[i][j][8 * p], acc[i][j][8 * p + 1]);
+                    uint32_t a1 = pack2<DT>(acc[i][j][8 * p + 2], acc[i][j][8 * p + 3]);
+                    uint32_t b0 = pack2<DT>(acc[i][j][8 * p + 4], acc[i][j][8 * p + 5]);
+                    uint32_t b1 = pack2<DT>(acc[i][j][8 * p + 6], acc[i][j][8 * p + 7]);
+                    // exchange halves: each lane then holds columns 16 p + 8 half + 0..7.  The lanes
+                    // of a row (l32 of both halves) are active together
+                    asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\tv_permlane32_swap_b32 %2, %3\n\ts_nop 1"
+                                 : "+v"(a0), "+v"(b0), "+v"(a1), "+v"(b1));
+                    const int col = colb + 16 * p + 8 * half;
+                    if (col + 8 <= g.N) *reinterpret_cast<u32x4 *>(crow + col) = u32x4{a0, a1, b0, b1};
                 }
             }
+        }
     }
 }
 
-// Persistent form of gemm_w4_kernel for the storage-dtype and transposed-value outputs: one
-// workgroup per CU walks the tiles blockIdx.x, + gridDim.x, ... (in the same remapped order).  The
+// The persistent kernel: one workgroup per CU walks the tiles blockIdx.x, + gridDim.x, ... (in the same remapped order).  The
 // operand that streams the tokens has an LDS ring of three k-tiles, the weights one of two (160 KiB
 // at k-tiles of 64).  The rings run on across tiles: the refills of a tile's last stages bring the
 // next tile's first two k-tiles, and the last stage's fragment reads already fetch its first k-step, so
@@ -563,8 +348,9 @@ __global__ __launch_bounds__(256, 1) void gemm_w4p_kernel(const void *__restrict
                                                           int ldb, int ldc, int tiles_m, int tiles_n, int seq_T,
                                                           int seq_Tp, int n_work, const float4 *__restrict__ rtab,
                                                           float alpha, int ksplit, void *__restrict__ Cp2,
-                                                          int *__restrict__ queue) {
-    static_assert(RDH == 0 || (OUT == OUT_DT && (RDH == 64 || RDH == 128)), "rotary epilogue");
+                                                          int *__restrict__ queue_arg, int nv, int ldv, int n_tok) {
+    int *const queue = OUT == OUT_QKV ? nullptr : queue_arg;   // its launches have few items per workgroup
+    static_assert(RDH == 0 || ((OUT == OUT_DT || OUT == OUT_QKV) && (RDH == 64 || RDH == 128)), "rotary epilogue");
     typedef typename Mma<DT>::elem elem;
     typedef typename Mma<DT>::operand opnd;
     constexpr int BK = CPR * 8;
@@ -592,12 +378,32 @@ __global__ __launch_bounds__(256, 1) void gemm_w4p_kernel(const void *__restrict
     // A and B panels (all wave-uniform)
     struct Tile {
         int bm0, bn0, k0, ks;
+        bool val;                                     // OUT_QKV: a tile of the transposed values
         void *out;
         i32x4 rsA, rsB;
+    };
+    // OUT_QKV: the source row of padded token position n (a pad position reads a valid row)
+    auto token = [&](int n) -> int {
+        const int sq = n / seq_Tp;
+        return sq * seq_T + min(n - sq * seq_Tp, seq_T - 1);
     };
     auto decode = [&](int work, Tile &t) {
         int pid = work;
         if ((n_work & 7) == 0) pid = (pid & 7) * (n_work >> 3) + (pid >> 3);
+        t.val = OUT == OUT_QKV && pid >= tiles_m * tiles_n;
+        if constexpr (OUT == OUT_QKV) {
+            if (t.val) {                              // A: the value weights (rows N.. of B), B: the tokens
+                pid -= tiles_m * tiles_n;
+                const int tvm = (nv + 255) >> 8;
+                t.bm0 = min((pid % tvm) * 256, nv - 256);
+                t.bn0 = min((pid / tvm) * 256, n_tok - 256);
+                t.k0 = t.ks = 0;
+                t.out = Cp2;
+                t.rsA = buffer_rsrc(static_cast<const char *>(Bp) + (int64_t)(N + t.bm0) * ldb * (int64_t)sizeof(elem));
+                t.rsB = buffer_rsrc(static_cast<const char *>(Ap) + (int64_t)token(t.bn0) * lda * (int64_t)sizeof(elem));
+                return;
+            }
+        }
         const int part = pid / (tiles_m * tiles_n);
         pid -= part * tiles_m * tiles_n;
         t.k0 = part * nk;
@@ -628,6 +434,26 @@ __global__ __launch_bounds__(256, 1) void gemm_w4p_kernel(const void *__restrict
         voffA[i] = (uint32_t)(r * lda * 2 + c * 16);
         voffB[i] = (uint32_t)(r * ldb * 2 + c * 16);
     }
+    // OUT_QKV (lda == ldb) with sequences that are not whole blocks of 32 tokens: a value tile's rows
+    // of X skip at the sequence ends, so its per-lane offsets are its own; they are set for the first
+    // tile and then, inside stage nk - 2, for the next one (before its first B loads)
+    const bool ragged = OUT == OUT_QKV && seq_T != seq_Tp;
+    auto set_voffB = [&](const Tile &t) {
+        if constexpr (OUT == OUT_QKV) {
+            // row 8 wave + 32 i + lane / 8, whose chunk key does not depend on i.  The lane id goes
+            // through an opaque copy, so that nothing here is kept in registers between the tiles
+            static_assert(CPR == 8, "rows of eight chunks");
+            int ln = lane;
+            asm volatile("" : "+v"(ln));
+            const int r0 = 8 * wave + (ln >> 3), c16 = ((ln & 7) ^ w4_key<CPR>(r0)) * 16;
+            const int base = t.val ? token(t.bn0) : 0;
+#pragma unroll
+            for (int i = 0; i < DPA; ++i) {
+                const int rr = t.val ? token(t.bn0 + r0 + 32 * i) - base : r0 + 32 * i;
+                voffB[i] = (uint32_t)(rr * ldb * 2 + c16);
+            }
+        }
+    };
     // DMA instruction d of k-tile ktile into the operand's ring slot `slot`
     auto issue = [&](const Tile &t, int d, int ktile, int slot) {
         int kx = ktile + t.ks;
@@ -692,6 +518,7 @@ __global__ __launch_bounds__(256, 1) void gemm_w4p_kernel(const void *__restrict
     }
     int par = 0;                                      // the queue's mailbox slot of this tile
 
+    if (ragged) set_voffB(cur);
     // prologue, as a previous tile's last stages leave the rings: k-tile 0 of both operands, k-tile
     // 1 of the deep one and the first half of the shallow one's (its second half goes out in the
     // first k-step of stage 0); then k-tile 0 has landed
@@ -710,8 +537,10 @@ __global__ __launch_bounds__(256, 1) void gemm_w4p_kernel(const void *__restrict
     int dslot = 0, sslot = 0;                         // the stage's deep and shallow ring slots
     for (;;) {
         // Stage kt of the current tile (FIRST: kt = 0, whose first k-step starts the accumulators
-        // from zero).  The schedule is gemm_w4_kernel's; the refills past the tile's last k-tile
-        // load the next tile's first ones.
+        // from zero).  k-step u: 16 MFMAs, a fragment read of the next k-step every other MFMA slot, and
+        // refill loads; one barrier per stage, before its last k-step, by when every wave has read (and
+        // waited for) the stage's other fragments and the next stage has landed.  The refills past the
+        // tile's last k-tile load the next tile's first ones.
         // Refills, one DMA instruction every fourth MFMA slot: k-step 0 sends the second half of
         // the shallow operand's k-tile kt + 1 (into the slot stage kt - 1 left), k-steps 1 and 2 the
         // deep operand's k-tile kt + 2 (into the deep slot stage kt - 1 left), the last k-step,
@@ -731,6 +560,8 @@ __global__ __launch_bounds__(256, 1) void gemm_w4p_kernel(const void *__restrict
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int cb = u & 1;
+                if constexpr (OUT == OUT_QKV && !FIRST)
+                    if (u == 1 && ragged && kt == nk - 2) set_voffB(nxt);
                 if (u == U - 1) {
                     wait_lgkm0();
                     wait_vmcnt<DPA>();
@@ -756,25 +587,22 @@ __global__ __launch_bounds__(256, 1) void gemm_w4p_kernel(const void *__restrict
             dslot = nd;
             sslot = ns;
         };
-        // rotary epilogue: the table entries of row block i (this lane's position, its 32 head
-        // columns: tb[4 (2 jp + pp) + k] holds the (cos, sin) of columns (32 jp for RDH 128) +
-        // 16 pp + 8 (k / 2) + 4 half + 2 (k % 2) and + 1, from the transposed table rtab[q][t], so
-        // a load's 32 positions are one contiguous run); block 0's are loaded before the tile's
-        // last stage, block i + 1's while block i is rotated
-        f32x4 tab[2][16];
-        auto tload = [&](int i, f32x4 (&tb)[16]) {
+        // rotary epilogue: the table entries of step 2 i + jp (row block i, pairs jp of the wave's
+        // columns): this lane's position and 16 of its head columns, tb[4 pp + k] holds the (cos, sin)
+        // of columns (32 jp for RDH 128) + 16 pp + 8 (k / 2) + 4 half + 2 (k % 2) and + 1, from the
+        // transposed table rtab[q][t], so a load's 32 positions are one contiguous run; step 0's are
+        // loaded before the tile's last stage, each next step's while the previous one is rotated
+        f32x4 tab[2][8];
+        auto tload = [&](int st, f32x4 (&tb)[8]) {
             if constexpr (RDH > 0) {
-                const int t = (cur.bm0 + wr * 128 + 32 * i + l32) % seq_T;
+                const int t = (cur.bm0 + wr * 128 + 32 * (st >> 1) + l32) % seq_T, jp = st & 1;
 #pragma unroll
-                for (int jp = 0; jp < 2; ++jp)
+                for (int pp = 0; pp < 2; ++pp)
 #pragma unroll
-                    for (int pp = 0; pp < 2; ++pp)
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            const int q = (RDH == 128 ? 16 * jp : 0) + 8 * pp + 4 * (k >> 1) + 2 * half + (k & 1);
-                            tb[4 * (2 * jp + pp) + k] =
-                                __builtin_bit_cast(f32x4, rtab[(int64_t)q * seq_T + t]);
-                        }
+                    for (int k = 0; k < 4; ++k) {
+                        const int q = (RDH == 128 ? 16 * jp : 0) + 8 * pp + 4 * (k >> 1) + 2 * half + (k & 1);
+                        tb[4 * pp + k] = __builtin_bit_cast(f32x4, rtab[(int64_t)q * seq_T + t]);
+                    }
             }
         };
         int taken = 0;
@@ -831,7 +659,9 @@ __global__ __launch_bounds__(256, 1) void gemm_w4p_kernel(const void *__restrict
                         __builtin_amdgcn_sched_barrier(0);
                     }
             }
-        } else if constexpr (RDH > 0) {
+        } else {
+            auto store_rope = [&]() {
+              if constexpr (RDH > 0) {
             // Rotary embedding of the half-split pairs (column c of a head with c + RDH/2), token
             // row % seq_T.  A wave's 128 columns start on a head boundary (tiles start at multiples
             // of 256 or end at N, N a multiple of RDH), so a pair sits in one lane: blocks j and
@@ -840,17 +670,17 @@ __global__ __launch_bounds__(256, 1) void gemm_w4p_kernel(const void *__restrict
             // (a, b) -> (fma(a, cos, -b sin), fma(b, cos, a sin)), then round to the dtype once.
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                if (i + 1 < 4) tload(i + 1, tab[(i + 1) & 1]);
                 const int row = cur.bm0 + wr * 128 + 32 * i + l32;
-                elem *crow = static_cast<elem *>(Cp) + (int64_t)row * ldc;
+                elem *crow = static_cast<elem *>(cur.out) + (int64_t)row * ldc;
 #pragma unroll
                 for (int jp = 0; jp < 2; ++jp) {
+                    if (2 * i + jp + 1 < 8) tload(2 * i + jp + 1, tab[(jp + 1) & 1]);
                     const int j1 = RDH == 128 ? jp : 2 * jp, j2 = RDH == 128 ? jp + 2 : 2 * jp + 1;
 #pragma unroll
                     for (int pp = 0; pp < 2; ++pp) {
                         // elements 8 pp + e: head columns (32 jp for RDH 128) + 16 pp + 8 (e / 4) +
                         // 4 half + e % 4; tq[e / 2] holds the (cos, sin) of elements 2 (e / 2) and + 1
-                        const f32x4 *tq = &tab[i & 1][4 * (2 * jp + pp)];
+                        const f32x4 *tq = &tab[jp][4 * pp];
                         float v1[8], v2[8];
 #pragma unroll
                         for (int e = 0; e < 8; ++e) {
@@ -884,40 +714,68 @@ __global__ __launch_bounds__(256, 1) void gemm_w4p_kernel(const void *__restrict
                     }
                 }
             }
-        } else
+              }
+            };
+            // the storage-dtype tile (TR false) or the transposed values (TR true)
+            auto store_tile = [&](auto tr_c) {
+                constexpr bool TR = decltype(tr_c)::value;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int row = cur.bm0 + wr * 128 + 32 * i + l32;
-            elem *crow = static_cast<elem *>(Cp) + (int64_t)row * ldc;
+                for (int i = 0; i < 4; ++i) {
+                    const int row = cur.bm0 + wr * 128 + 32 * i + l32;
+                    elem *crow = static_cast<elem *>(cur.out) + (int64_t)row * (TR && OUT == OUT_QKV ? ldv : ldc);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int colb = cur.bn0 + wc * 128 + 32 * j;
+                    for (int j = 0; j < 4; ++j) {
+                        const int colb = cur.bn0 + wc * 128 + 32 * j;
 #pragma unroll
-                for (int pp = 0; pp < 2; ++pp) {
-                    float v[8];
+                        for (int pp = 0; pp < 2; ++pp) {
+                            float v[8];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v[e]) : "a"(acc[i][j][8 * pp + e]));
-                    uint32_t a0 = pack2<DT>(v[0], v[1]), a1 = pack2<DT>(v[2], v[3]);
-                    uint32_t b0 = pack2<DT>(v[4], v[5]), b1 = pack2<DT>(v[6], v[7]);
-                    int64_t dcol;
-                    if constexpr (OUT == OUT_DT) {
-                        // a lane holds columns 16 pp + 4 half + 0..3 (a) and 16 pp + 8 + 4 half + 0..3
-                        // (b); exchanging a of the upper half-wave with b of the lower one leaves
-                        // each lane eight consecutive columns, 16 pp + 8 half + 0..7
-                        asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\tv_permlane32_swap_b32 %2, %3\n\ts_nop 1"
-                                     : "+v"(a0), "+v"(b0), "+v"(a1), "+v"(b1));
-                        dcol = colb + 16 * pp + 8 * half;
-                    } else {
-                        // tokens 16 pp + 4 half + 0..3 and 16 pp + 8 + 4 half + 0..3 of the 32-token
-                        // block colb: with bits 2 and 3 exchanged they are the eight consecutive
-                        // positions 16 pp + 8 half + 0..7 (the block lies in one sequence)
-                        const int sb = colb / seq_T;
-                        dcol = (int64_t)sb * seq_Tp + (colb - sb * seq_T) + 16 * pp + 8 * half;
+                            for (int e = 0; e < 8; ++e)
+                                asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v[e]) : "a"(acc[i][j][8 * pp + e]));
+                            if constexpr (TR && OUT == OUT_QKV) {
+                                // pad positions hold zeros (colb is a padded position)
+                                if (ragged) {
+                                    const int left = seq_T - colb % seq_Tp - 16 * pp - 4 * half;
+#pragma unroll
+                                    for (int e = 0; e < 8; ++e) v[e] = 8 * (e >> 2) + (e & 3) < left ? v[e] : 0.f;
+                                }
+                            }
+                            uint32_t a0 = pack2<DT>(v[0], v[1]), a1 = pack2<DT>(v[2], v[3]);
+                            uint32_t b0 = pack2<DT>(v[4], v[5]), b1 = pack2<DT>(v[6], v[7]);
+                            int64_t dcol;
+                            if constexpr (!TR) {
+                                // a lane holds columns 16 pp + 4 half + 0..3 (a) and 16 pp + 8 + 4 half +
+                                // 0..3 (b); exchanging a of the upper half-wave with b of the lower one
+                                // leaves each lane eight consecutive columns, 16 pp + 8 half + 0..7
+                                asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\tv_permlane32_swap_b32 %2, %3\n\ts_nop 1"
+                                             : "+v"(a0), "+v"(b0), "+v"(a1), "+v"(b1));
+                                dcol = colb + 16 * pp + 8 * half;
+                            } else {
+                                // tokens 16 pp + 4 half + 0..3 and 16 pp + 8 + 4 half + 0..3 of the
+                                // 32-token block colb: with bits 2 and 3 exchanged they are the eight
+                                // consecutive positions 16 pp + 8 half + 0..7 (the block lies in one
+                                // sequence; OUT_QKV: colb is already the padded position)
+                                if constexpr (OUT == OUT_QKV) {
+                                    dcol = colb + 16 * pp + 8 * half;
+                                } else {
+                                    const int sb = colb / seq_T;
+                                    dcol = (int64_t)sb * seq_Tp + (colb - sb * seq_T) + 16 * pp + 8 * half;
+                                }
+                            }
+                            *reinterpret_cast<u32x4 *>(crow + dcol) = u32x4{a0, a1, b0, b1};
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
                     }
-                    *reinterpret_cast<u32x4 *>(crow + dcol) = u32x4{a0, a1, b0, b1};
-                    __builtin_amdgcn_sched_barrier(0);
                 }
+            };
+            if constexpr (OUT == OUT_QKV) {
+                if (cur.val) store_tile(std::integral_constant<bool, true>());
+                else if constexpr (RDH > 0) store_rope();
+                else store_tile(std::integral_constant<bool, false>());
+            } else if constexpr (RDH > 0) {
+                store_rope();
+            } else {
+                store_tile(std::integral_constant<bool, OUT == OUT_VT>());
             }
         }
         if (!has_next) break;
@@ -934,69 +792,6 @@ __global__ __launch_bounds__(256, 1) void gemm_w4p_kernel(const void *__restrict
     finish();
 }
 
-}  // namespace
-
-template <int DT, int BM, int BN, int NS, int MINB, int OUT, int CPR = 4, int NW = 4>
-hipError_t run_gemm(const void *A, const void *B, void *C, int M, int N, int K, int lda, int ldb,
-                    int ldc, float alpha, hipStream_t st, int seq_T = 1, int seq_Tp = 1,
-                    void *C2 = nullptr, int *ksplit_used = nullptr) {
-    typedef GemmCfg<DT, BM, BN, NS, CPR, NW> G;
-    if (K % G::BK != 0) return hipErrorInvalidValue;
-    const int tm = (M + BM - 1) / BM, tn = (N + BN - 1) / BN;
-    // With a second output, split K in two when the tiles alone would leave a partial last round
-    // of workgroups on the CUs and two halves fill the rounds better.
-    int ksplit = 1;
-    if (C2 != nullptr && (K / G::BK) % 2 == 0) {
-        int dev = 0, ncu = 0;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && ncu > 0) {
-            const int slots = ncu * MINB, t = tm * tn;
-            const double e1 = (double)t / (((t + slots - 1) / slots) * slots);
-            const double e2 = (double)(2 * t) / (((2 * t + slots - 1) / slots) * slots);
-            if (e2 > e1 + 0.05) ksplit = 2;
-        }
-    }
-    if (ksplit_used) *ksplit_used = ksplit;
-    hipError_t e = hipFuncSetAttribute((const void *)gemm_nt_kernel<DT, BM, BN, NS, MINB, OUT, CPR, NW>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::LDS_BYTES);
-    if (e != hipSuccess) return e;
-    gemm_nt_kernel<DT, BM, BN, NS, MINB, OUT, CPR, NW><<<dim3(tm * tn * ksplit), dim3(64 * NW), G::LDS_BYTES, st>>>(
-        A, B, C, M, N, K, lda, ldb, ldc, tm, tn, alpha, seq_T, seq_Tp, ksplit, C2);
-    return hipGetLastError();
-}
-
-// Split K in two (second half into C2) when the tiles alone would leave a partial last round of
-// workgroups on the CUs and two halves fill the rounds better.
-inline int choose_ksplit(int tiles, int k_tiles, int slots_per_cu) {
-    if (k_tiles % 2 != 0) return 1;
-    int dev = 0, ncu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu <= 0)
-        return 1;
-    const int slots = ncu * slots_per_cu;
-    const double e1 = (double)tiles / (((tiles + slots - 1) / slots) * slots);
-    const double e2 = (double)(2 * tiles) / (((2 * tiles + slots - 1) / slots) * slots);
-    return e2 > e1 + 0.05 ? 2 : 1;
-}
-
-template <int DT, int OUT, int CPR>
-hipError_t run_gemm_w4(const void *A, const void *B, void *C, int M, int N, int K, int lda, int ldb, int ldc,
-                       float alpha, hipStream_t st, int seq_T, int seq_Tp, void *C2, int *ksplit_used) {
-    constexpr int BK = CPR * 8;
-    // two ring stages; the storage-dtype output reuses LDS for a 256 x 256 C tile
-    constexpr size_t RING = 2 * 2 * 256 * CPR * 16;
-    constexpr size_t LDS = OUT == OUT_DT && RING < 256 * 512 ? 256 * 512 : RING;
-    if (K % BK != 0) return hipErrorInvalidValue;
-    const int tm = (M + 255) / 256, tn = (N + 255) / 256;
-    const int ksplit = C2 != nullptr ? choose_ksplit(tm * tn, K / BK, 1) : 1;
-    if (ksplit_used) *ksplit_used = ksplit;
-    hipError_t e = hipFuncSetAttribute((const void *)gemm_w4_kernel<DT, OUT, CPR>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
-    if (e != hipSuccess) return e;
-    gemm_w4_kernel<DT, OUT, CPR><<<dim3(tm * tn * ksplit), dim3(256), LDS, st>>>(
-        A, B, C, M, N, K, lda, ldb, ldc, tm, tn, alpha, seq_T, seq_Tp, ksplit, C2);
-    return hipGetLastError();
-}
 
 // the persistent GEMMs' tile queues: 4 KiB per (device, stream), allocated on the first launch on
 // that stream and held until the process ends
@@ -1026,82 +821,138 @@ int *gemm_queue(int dev, hipStream_t st) {
     return q;
 }
 
-template <int DT, int OUT, int CPR, int RDH = 0>
-hipError_t run_gemm_w4p(const void *A, const void *B, void *C, int M, int N, int K, int lda, int ldb, int ldc,
-                        hipStream_t st, int seq_T, int seq_Tp, const float4 *rtab = nullptr, float alpha = 1.f,
-                        void *C2 = nullptr, int *ksplit_used = nullptr) {
-    constexpr size_t LDS = 5 * 256 * CPR * 16;       // rings of three and two k-tiles
-    int dev = 0, ncu = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
-    const int tm = (M + 255) / 256, tn = (N + 255) / 256;
-    // with a second output: K in two parts when they fill the CUs' rounds better than the tiles alone
-    // (each part keeps at least three k-tiles)
+constexpr int CUS = 256;          // MI355X; the shape rules use it, the persistent grid asks the device
+int device_cus(int *dev) {
+    int ncu = 0;
+    if (hipGetDevice(dev) != hipSuccess ||
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, *dev) != hipSuccess)
+        return 0;
+    return ncu;
+}
+
+// One product A B^T (and, OUT_QKV, the transposed values that go with it) as the launchers below see it
+struct Gemm {
+    int dtype;
+    const void *A, *B;
+    void *C;
+    int M, N, K, lda, ldb, ldc;
+    float alpha = 1.f;
+    int seq_T = 1, seq_Tp = 1;
+    // OUT_F32: parts of K (part p > 0 at C2 + (p - 1) part_stride); OUT_QKV: C2 the values' output
+    void *C2 = nullptr;
     int ksplit = 1;
-    if (C2 != nullptr && (K / (CPR * 8)) % 2 == 0 && K / (CPR * 8) >= 6) {
-        const int t = tm * tn;
-        const double e1 = (double)t / (((t + ncu - 1) / ncu) * ncu);
-        const double e2 = (double)(2 * t) / (((2 * t + ncu - 1) / ncu) * ncu);
-        if (e2 > e1 + 0.05) ksplit = 2;
-    }
-    if (ksplit_used) *ksplit_used = ksplit;
-    const int n_work = tm * tn * ksplit;
-    e = hipFuncSetAttribute((const void *)gemm_w4p_kernel<DT, OUT, CPR, RDH>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
+    int64_t part_stride = 0;
+    // values: rows of B after its first N, output row stride, padded token positions
+    int nv = 0, ldv = 0, n_tok = 0;
+    const float4 *rtab = nullptr;
+};
+
+template <int DT, int OUT, int RDH = 0>
+hipError_t run_gemm_w4p(const Gemm &g, hipStream_t st) {
+    constexpr int CPR = 8;
+    constexpr size_t LDS = 5 * 256 * CPR * 16;       // rings of three and two k-tiles
+    int dev = 0;
+    const int ncu = device_cus(&dev);
+    if (ncu <= 0) return hipErrorInvalidDevice;
+    const int tm = (g.M + 255) / 256, tn = (g.N + 255) / 256;
+    const int n_work = tm * tn * g.ksplit + (OUT == OUT_QKV ? (g.nv + 255) / 256 * ((g.n_tok + 255) / 256) : 0);
+    hipError_t e = hipFuncSetAttribute((const void *)gemm_w4p_kernel<DT, OUT, CPR, RDH>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
     if (e != hipSuccess) return e;
     // the queue pays where a workgroup has many work items (measured: 80 per workgroup, the [Q|K]
     // projection of 128 x 2048 tokens at d 4096, 8.22 -> 8.00 ms; 10 and 2 per workgroup, the
     // projections of 16 x 2048 tokens, 1.8 and 8 % slower than the static order)
     const int grid = min(n_work, ncu);
-    int *queue = grid % 8 == 0 && n_work >= 32 * grid && K / (CPR * 8) / ksplit >= 6 &&
+    int *queue = grid % 8 == 0 && n_work >= 32 * grid && g.K / (CPR * 8) / g.ksplit >= 6 &&
                          (int)(kQueueBytes / 4) >= 16 + 2 * grid
                      ? gemm_queue(dev, st) : nullptr;
     gemm_w4p_kernel<DT, OUT, CPR, RDH><<<dim3(grid), dim3(256), LDS, st>>>(
-        A, B, C, M, N, K, lda, ldb, ldc, tm, tn, seq_T, seq_Tp, n_work, rtab, alpha, ksplit, C2, queue);
+        g.A, g.B, g.C, g.M, g.N, g.K, g.lda, g.ldb, g.ldc, tm, tn, g.seq_T, g.seq_Tp, n_work, g.rtab, g.alpha,
+        g.ksplit, g.C2, queue, g.nv, g.ldv, g.n_tok);
     return hipGetLastError();
 }
 
 // The persistent kernel takes whole 256 x 256 tiles, 16-byte aligned output rows and at least three
-// k-tiles; a split K (fp32 output with a second buffer) only where the tiles are whole in both
-// directions (no tile moved back over its neighbour: the two parts are summed by the caller); for
-// the transposed value output, 32-token blocks inside one sequence.
-template <int OUT, int CPR>
-bool persistent_fits(int M, int N, int K, int ldc, int seq_T, const void *C2) {
-    if (C2 != nullptr && (OUT != OUT_F32 || M % 256 != 0 || N % 256 != 0)) return false;
-    if (M < 256 || N < 256 || K % (CPR * 8) != 0 || K / (CPR * 8) < 3) return false;
-    if (OUT == OUT_F32) return ldc % 4 == 0 && N % 4 == 0;
-    if (ldc % 8 != 0) return false;
-    if (OUT == OUT_DT) return N % 8 == 0;
-    return seq_T % 32 == 0;
+// k-tiles; a split K (fp32 output) only in two and where the tiles are whole in both directions (no
+// tile moved back over its neighbour: the two parts are summed by the caller); for the transposed
+// value output, 32-token blocks inside one sequence (OUT_QKV works on padded positions instead).
+template <int OUT>
+bool persistent_fits(const Gemm &g) {
+    if (g.dtype == F32 || g.M < 256 || g.N < 256 || g.K % 64 != 0 || g.K / 64 / g.ksplit < 3) return false;
+    if (g.ksplit > 1 && (OUT != OUT_F32 || g.ksplit > 2 || g.K % 128 != 0 || g.M % 256 != 0 || g.N % 256 != 0))
+        return false;
+    if (OUT == OUT_F32) return g.ldc % 4 == 0 && g.N % 4 == 0;
+    if (g.ldc % 8 != 0) return false;
+    if (OUT == OUT_VT) return g.seq_T % 32 == 0;
+    if (g.N % 8 != 0) return false;
+    return OUT != OUT_QKV || (g.nv >= 256 && g.n_tok >= 256 && g.lda == g.ldb && g.ldv % 8 == 0);
 }
 
-namespace {
+template <int DT, int BT, int CPR, int OUT, int RDH = 0>
+hipError_t run_gemm_small_cfg(const Gemm &g, hipStream_t st) {
+    typedef SmallCfg<DT, BT, CPR> S;
+    SmallArgs a;
+    a.A = g.A; a.B = g.B; a.C = g.C; a.C2 = g.C2;
+    a.M = g.M; a.N = g.N; a.K = g.K; a.lda = g.lda; a.ldb = g.ldb; a.ldc = g.ldc;
+    a.nv = g.nv; a.ldv = g.ldv; a.seq_T = g.seq_T; a.seq_Tp = g.seq_Tp; a.n_tok = g.n_tok;
+    a.alpha = g.alpha; a.ksplit = g.ksplit; a.part_stride = g.part_stride;
+    a.tiles_m = g.C ? (g.M + BT - 1) / BT : 0;
+    a.tiles_n = g.C ? (g.N + BT - 1) / BT : 0;
+    a.tiles_vm = (g.nv + BT - 1) / BT;
+    a.tiles_vn = (g.n_tok + BT - 1) / BT;
+    a.rtab = g.rtab;
+    hipError_t e = hipFuncSetAttribute((const void *)gemm_small_kernel<DT, BT, CPR, OUT, RDH>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::LDS_BYTES);
+    if (e != hipSuccess) return e;
+    const int n = a.tiles_m * a.tiles_n * g.ksplit + (OUT == OUT_DT ? a.tiles_vm * a.tiles_vn : 0);
+    if (n == 0) return hipSuccess;
+    gemm_small_kernel<DT, BT, CPR, OUT, RDH><<<dim3(n), dim3(256), S::LDS_BYTES, st>>>(a);
+    return hipGetLastError();
+}
 
-template <int OUT>
-hipError_t dispatch(int dtype, const void *A, const void *B, void *C, int M, int N, int K, int lda,
-                    int ldb, int ldc, float alpha, hipStream_t st, int seq_T = 1, int seq_Tp = 1,
-                    void *C2 = nullptr, int *ksplit_used = nullptr) {
-    if (ksplit_used) *ksplit_used = 1;
-    if (M <= 0 || N <= 0 || K <= 0) return hipSuccess;
-    // 16-bit dtypes: 128-byte k-rows when K allows (each load covers whole cache lines), else 64-byte rows
-    const bool wide = K % 64 == 0;
-    switch (dtype) {
-    case F32:
-        return run_gemm<F32, 128, 128, 4, 1, OUT>(A, B, C, M, N, K, lda, ldb, ldc, alpha, st, seq_T, seq_Tp, C2, ksplit_used);
-    case F16:
-        if (wide && persistent_fits<OUT, 8>(M, N, K, ldc, seq_T, C2))
-            return run_gemm_w4p<F16, OUT, 8>(A, B, C, M, N, K, lda, ldb, ldc, st, seq_T, seq_Tp, nullptr, alpha, C2,
-                                             ksplit_used);
-        return wide ? run_gemm_w4<F16, OUT, 8>(A, B, C, M, N, K, lda, ldb, ldc, alpha, st, seq_T, seq_Tp, C2, ksplit_used)
-                    : run_gemm_w4<F16, OUT, 4>(A, B, C, M, N, K, lda, ldb, ldc, alpha, st, seq_T, seq_Tp, C2, ksplit_used);
-    default:
-        if (wide && persistent_fits<OUT, 8>(M, N, K, ldc, seq_T, C2))
-            return run_gemm_w4p<BF16, OUT, 8>(A, B, C, M, N, K, lda, ldb, ldc, st, seq_T, seq_Tp, nullptr, alpha, C2,
-                                              ksplit_used);
-        return wide ? run_gemm_w4<BF16, OUT, 8>(A, B, C, M, N, K, lda, ldb, ldc, alpha, st, seq_T, seq_Tp, C2, ksplit_used)
-                    : run_gemm_w4<BF16, OUT, 4>(A, B, C, M, N, K, lda, ldb, ldc, alpha, st, seq_T, seq_Tp, C2, ksplit_used);
+int tiles_of(const Gemm &g, int bt) {
+    auto up = [bt](int v) { return (v + bt - 1) / bt; };
+    return (g.C ? up(g.M) * up(g.N) * g.ksplit : 0) + up(g.nv) * up(g.n_tok);
+}
+
+// The 128-tile from one tile per CU on for the 16-bit dtypes (measured, 64-tile against 128-tile, us:
+// K 768, 144 tiles 13.0 / 13.0, 288 18.6 / 18.6, 342 21.4 / 19.1; K 4096, 192 41.5 / 42.0, 384 76 / 61;
+// at 48 tiles of K 4096 20 / 39) and from eight per CU for fp32 (whose 64-tile fills the matrix cores
+// too: 576 tiles 128 / 155, 2304 442 / 433)
+template <int DT, int OUT, int RDH>
+hipError_t run_gemm_small(const Gemm &g, hipStream_t st) {
+    if (g.K % 32 != 0) return hipErrorInvalidValue;
+    if constexpr (RDH > 0) {
+        return g.K % 64 == 0 ? run_gemm_small_cfg<DT, 128, 8, OUT, RDH>(g, st)
+                             : run_gemm_small_cfg<DT, 128, 4, OUT, RDH>(g, st);
+    } else {
+        const bool big = tiles_of(g, 128) >= (DT == F32 ? 8 : 1) * CUS;
+        if constexpr (DT != F32)
+            if (g.K % 64 != 0)
+                return big ? run_gemm_small_cfg<DT, 128, 4, OUT>(g, st) : run_gemm_small_cfg<DT, 64, 4, OUT>(g, st);
+        return big ? run_gemm_small_cfg<DT, 128, 8, OUT>(g, st) : run_gemm_small_cfg<DT, 64, 8, OUT>(g, st);
     }
+}
+
+template <int OUT, int RDH = 0>
+hipError_t small(const Gemm &g, hipStream_t st) {
+    if constexpr (RDH == 0)
+        if (g.dtype == F32) return run_gemm_small<F32, OUT, 0>(g, st);
+    if (g.dtype == F32) return hipErrorInvalidValue;
+    return g.dtype == F16 ? run_gemm_small<F16, OUT, RDH>(g, st) : run_gemm_small<BF16, OUT, RDH>(g, st);
+}
+template <int OUT, int RDH = 0>
+hipError_t persistent(const Gemm &g, hipStream_t st) {
+    return g.dtype == F16 ? run_gemm_w4p<F16, OUT, RDH>(g, st) : run_gemm_w4p<BF16, OUT, RDH>(g, st);
+}
+
+// Where the 256-tiles fill their rounds of one workgroup per CU to at least 70 %, and K is long enough to
+// carry a tile's start and end.  Measured (persistent against 128-tiles, us): K 4096, 75 % of one round
+// 92 / 103, 75 % of two 186 / 194, 38 % of one 80 / 61; K 768, 88 % of one 32 / 33, 56 % of two 47 / 42,
+// 75 % of three 71 / 70, 90 % of five 122 / 142; K 256, three whole rounds 59 / 52.
+bool persistent_pays(const Gemm &g) {
+    const int64_t t = tiles_of(g, 256);
+    return g.K / g.ksplit >= 512 && 10 * t >= 7 * ((t + CUS - 1) / CUS) * CUS;
 }
 
 }  // namespace
@@ -1111,33 +962,85 @@ GemmQueueNoAlloc::~GemmQueueNoAlloc() { --g_queue_noalloc; }
 
 hipError_t launch_gemm_nt(int dtype, const void *A, const void *B, void *C, int M, int N, int K,
                           int lda, int ldb, int ldc, hipStream_t st) {
-    return dispatch<OUT_DT>(dtype, A, B, C, M, N, K, lda, ldb, ldc, 1.f, st);
+    if (M <= 0 || N <= 0 || K <= 0) return hipSuccess;
+    Gemm g{dtype, A, B, C, M, N, K, lda, ldb, ldc};
+    return persistent_fits<OUT_DT>(g) && persistent_pays(g) ? persistent<OUT_DT>(g, st) : small<OUT_DT>(g, st);
 }
 
 hipError_t launch_gemm_nt_f32out(int dtype, const void *A, const void *B, float *C, int M, int N, int K,
                                  int lda, int ldb, int ldc, float alpha, hipStream_t st, float *C2,
                                  int *ksplit_used) {
-    return dispatch<OUT_F32>(dtype, A, B, C, M, N, K, lda, ldb, ldc, alpha, st, 1, 1, C2, ksplit_used);
+    if (ksplit_used) *ksplit_used = 1;
+    if (M <= 0 || N <= 0 || K <= 0) return hipSuccess;
+    Gemm g{dtype, A, B, C, M, N, K, lda, ldb, ldc, alpha};
+    g.C2 = C2;
+    g.part_stride = (int64_t)M * ldc;
+    // K in two parts when they fill the CUs' rounds better than the tiles alone
+    if (C2 != nullptr && K % 128 == 0) {
+        const int t = tiles_of(g, 256);
+        const double e1 = (double)t / (((t + CUS - 1) / CUS) * CUS);
+        const double e2 = (double)(2 * t) / (((2 * t + CUS - 1) / CUS) * CUS);
+        if (e2 > e1 + 0.05) g.ksplit = 2;
+    }
+    if (ksplit_used) *ksplit_used = g.ksplit;
+    return persistent_fits<OUT_F32>(g) && persistent_pays(g) ? persistent<OUT_F32>(g, st) : small<OUT_F32>(g, st);
 }
 
-bool gemm_rope_fuses(int dtype, int M, int N, int K, int ldc, int head_dim) {
-    return dtype != F32 && (head_dim == 64 || head_dim == 128) && N % head_dim == 0 && K % 64 == 0 &&
-           persistent_fits<OUT_DT, 8>(M, N, K, ldc, 1, nullptr);
+bool gemm_rope_fuses(int dtype, int head_dim) { return dtype != F32 && (head_dim == 64 || head_dim == 128); }
+
+namespace {
+Gemm projection(int dtype, const void *x, const void *w, void *qk, void *vt, int batch, int seq_T, int nqk, int nv,
+                int K, int ldv, const float4 *rope_tab_t) {
+    Gemm g{dtype, x, w, qk, batch * seq_T, nqk, K, K, K, nqk};
+    g.seq_T = seq_T; g.seq_Tp = (seq_T + 31) / 32 * 32;
+    g.C2 = vt; g.nv = nv; g.ldv = ldv; g.n_tok = vt ? batch * g.seq_Tp : 0;
+    g.rtab = rope_tab_t;
+    return g;
+}
+// a projection whose [Q|K] part goes to the persistent kernel
+bool qk_persistent(const Gemm &g) { return persistent_fits<OUT_DT>(g) && persistent_pays(g); }
+// ... and its values with it: one round less where both leave one part empty, and no second launch; a
+// launch of its own keeps the values' k-tile rotation and the [Q|K] tile queue (from 32 rounds on).
+// Measured, one launch / two, us, at d 4096, 5120 + 1024 columns: 8 K tokens 307 / 371, 16 K 611 / 612,
+// 32 K 1203 / 1212, 64 K (24 rounds) 2450 / 2510.  Sequences that are not whole blocks of 32 tokens
+// always go together: only this form takes them
+bool qkv_persistent(const Gemm &g) {
+    return qk_persistent(g) && persistent_fits<OUT_QKV>(g) &&
+           (g.seq_Tp != g.seq_T || tiles_of(g, 256) <= 24 * CUS);
+}
+}  // namespace
+
+bool project_is_one_launch(int dtype, int batch, int seq_T, int nqk, int nv, int K, int ldv) {
+    char some = 0;                                    // tiles count where there is an output
+    const Gemm g = projection(dtype, nullptr, nullptr, &some, &some, batch, seq_T, nqk, nv, K, ldv, nullptr);
+    return qk_persistent(g) ? qkv_persistent(g) : true;
 }
 
-hipError_t launch_gemm_nt_rope(int dtype, const void *A, const void *B, void *C, int M, int N, int K, int lda,
-                               int ldb, int ldc, int head_dim, int seq_T, const float4 *tab, hipStream_t st) {
-    if (!gemm_rope_fuses(dtype, M, N, K, ldc, head_dim) || seq_T <= 0 || tab == nullptr) return hipErrorInvalidValue;
-    if (dtype == F16)
-        return head_dim == 64 ? run_gemm_w4p<F16, OUT_DT, 8, 64>(A, B, C, M, N, K, lda, ldb, ldc, st, seq_T, 1, tab)
-                              : run_gemm_w4p<F16, OUT_DT, 8, 128>(A, B, C, M, N, K, lda, ldb, ldc, st, seq_T, 1, tab);
-    return head_dim == 64 ? run_gemm_w4p<BF16, OUT_DT, 8, 64>(A, B, C, M, N, K, lda, ldb, ldc, st, seq_T, 1, tab)
-                          : run_gemm_w4p<BF16, OUT_DT, 8, 128>(A, B, C, M, N, K, lda, ldb, ldc, st, seq_T, 1, tab);
-}
-
-hipError_t launch_gemm_nt_vt(int dtype, const void *A, const void *B, void *C, int M, int N, int K,
-                             int lda, int ldb, int ldc, int seq_T, hipStream_t st) {
-    return dispatch<OUT_VT>(dtype, A, B, C, M, N, K, lda, ldb, ldc, 1.f, st, seq_T, (seq_T + 31) / 32 * 32);
+hipError_t launch_project(int dtype, const void *x, const void *w, void *qk, void *vt, int batch, int seq_T, int nqk,
+                          int nv, int K, int ldv, int head_dim, const float4 *rope_tab_t, hipStream_t st) {
+    if (qk == nullptr) {
+        // V^T = W_V X^T: the operands swapped
+        const int M = batch * seq_T;
+        Gemm t{dtype, static_cast<const char *>(w) + (size_t)nqk * K * (dtype == F32 ? 4 : 2), x, vt, nv, M, K, K, K, ldv};
+        t.seq_T = seq_T; t.seq_Tp = (seq_T + 31) / 32 * 32;
+        if (persistent_fits<OUT_VT>(t) && persistent_pays(t)) return persistent<OUT_VT>(t, st);
+        return small<OUT_DT>(projection(dtype, x, w, nullptr, vt, batch, seq_T, nqk, nv, K, ldv, nullptr), st);
+    }
+    const bool rope = rope_tab_t != nullptr;
+    if (rope && (!gemm_rope_fuses(dtype, head_dim) || nqk % head_dim != 0)) return hipErrorInvalidValue;
+    Gemm g = projection(dtype, x, w, qk, vt, batch, seq_T, nqk, nv, K, ldv, rope_tab_t);
+    if (!qk_persistent(g)) {
+        if (!rope) return small<OUT_DT>(g, st);
+        return head_dim == 64 ? small<OUT_DT, 64>(g, st) : small<OUT_DT, 128>(g, st);
+    }
+    if (vt != nullptr) {
+        if (!qkv_persistent(g)) return hipErrorInvalidValue;
+        if (!rope) return persistent<OUT_QKV>(g, st);
+        return head_dim == 64 ? persistent<OUT_QKV, 64>(g, st) : persistent<OUT_QKV, 128>(g, st);
+    }
+    g.nv = 0;
+    if (!rope) return persistent<OUT_DT>(g, st);
+    return head_dim == 64 ? persistent<OUT_DT, 64>(g, st) : persistent<OUT_DT, 128>(g, st);
 }
 
 }  // namespace jab

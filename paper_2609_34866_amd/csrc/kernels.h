@@ -36,18 +36,20 @@ struct GemmQueueNoAlloc {
 // C stored in dtype with row stride ldc.
 hipError_t launch_gemm_nt(int dtype, const void *A, const void *B, void *C, int M, int N, int K,
                           int lda, int ldb, int ldc, hipStream_t st);
-// Transposed values for attention: A = W_V [Hkv*dh][d], B = X [B*T][d]; C[r][b*Tp + perm(t)]
-// (Tp = T rounded up to 32, perm = vt_perm within blocks of 32 tokens), ldc >= B*Tp.
-// [Q|K] projection with the rotary embedding in the epilogue (the persistent kernel; every
-// output column in a query or key head of head_dim columns, row r at position r % seq_T, tab the
-// transposed table tab_t of launch_rope_table).  gemm_rope_fuses: whether a shape
-// takes this path (16-bit, head_dim 64 or 128, the persistent kernel's shape conditions);
-// launch_gemm_nt_rope returns hipErrorInvalidValue where it does not.
-bool gemm_rope_fuses(int dtype, int M, int N, int K, int ldc, int head_dim);
-hipError_t launch_gemm_nt_rope(int dtype, const void *A, const void *B, void *C, int M, int N, int K, int lda,
-                               int ldb, int ldc, int head_dim, int seq_T, const float4 *tab_t, hipStream_t st);
-hipError_t launch_gemm_nt_vt(int dtype, const void *A, const void *B, void *C, int M, int N, int K,
-                             int lda, int ldb, int ldc, int seq_T, hipStream_t st);
+// The projection of a batch of sequences: x [B*T][K], w [nqk + nv][K] (both row stride K);
+//   qk [B*T][nqk] = x w[0..nqk)^T in dtype (NULL: the values alone),
+//   vt [nv][ldv] (NULL: qk alone): the transposed values, token t of sequence b at column b*Tp +
+//   vt_perm(t) (Tp = T rounded up to 32, vt_perm within blocks of 32 tokens), pad columns zero,
+//   ldv >= B*Tp.
+// project_is_one_launch: whether both go in one launch; else they are asked for one after the other.
+// rope_tab_t (NULL: none): the rotary embedding in the epilogue, every output column of qk in a query
+// or key head of head_dim columns, row r at position r % T, the transposed table of
+// launch_rope_table.  gemm_rope_fuses: whether the epilogue takes the rotation (16-bit, head_dim 64 or
+// 128); launch_project returns hipErrorInvalidValue where it does not.
+bool gemm_rope_fuses(int dtype, int head_dim);
+bool project_is_one_launch(int dtype, int batch, int seq_T, int nqk, int nv, int K, int ldv);
+hipError_t launch_project(int dtype, const void *x, const void *w, void *qk, void *vt, int batch, int seq_T, int nqk,
+                          int nv, int K, int ldv, int head_dim, const float4 *rope_tab_t, hipStream_t st);
 // Same product with an fp32 C = alpha * (A B^T).  With C2 (same shape) the product may be split
 // in two halves of K: *ksplit_used = 2 means C holds the first half's product and C2 the
 // second's (their sum is the result), 1 means C holds all of it.
@@ -56,8 +58,6 @@ hipError_t launch_gemm_nt_f32out(int dtype, const void *A, const void *B, float 
                                  int *ksplit_used = nullptr);
 
 // ---- backward
-// zero the padding columns of transposed values (T not a multiple of 32)
-hipError_t launch_zero_vt_pad(int dtype, void *vt, int rows, int64_t ld, int batch, int T, hipStream_t st);
 // V [B*T][ldv] in natural token order from transposed values [rows][ldt]
 hipError_t launch_vt_to_v(int dtype, const void *vt, void *v, int rows, int64_t ldt, int batch, int T, int ldv,
                           hipStream_t st);
