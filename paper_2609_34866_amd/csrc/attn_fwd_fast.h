@@ -1,7 +1,7 @@
-// attn_fwd_fast.h -- the causal GQA attention kernel for the common configuration: 16-bit
-// dtype, head_dim 64 or 128, one value tensor, and a workgroup whose four waves are four query
-// heads of one key/value group over the same 32 queries (included by attn_fwd.hip after
-// attn_fwd_impl.h, whose helpers it uses).
+// attn_fwd_fast.h -- the causal GQA attention kernel of the 16-bit dtypes at head_dim 64 and 128: a
+// workgroup's four waves share one key/value head, as four query heads over the same 32 queries, two
+// heads over two query tiles or one head over four (included by attn_fwd.hip after attn_fwd_impl.h,
+// whose helpers it uses).
 //
 // Paper: Method, "Layer-wise PTQ" (causal softmax attention) and eq. joint_loss (squared
 // Frobenius distance to the teacher output); same arithmetic as attn_fwd_kernel.
@@ -95,7 +95,10 @@ struct FastCfg {
     static constexpr int NV_READ = NDB * 2;          // V^T fragment reads per value tensor and block
     static constexpr int MP1 = NDB * 2;              // MFMAs O^T += V^T P^T per value tensor
     static constexpr int MP = NV * MP1;              // MFMAs of phase O
-    static constexpr int WPC = NV == 1 ? 2 : 1;      // workgroups per CU
+    // workgroups per CU (head_dim 64: bound by the exponentials, 16 cycles each against half the products
+    // of head_dim 128; measured at 32 x 1024 with 12 heads, two / three / four per CU: 88 / 79 / 227 us,
+    // four spills)
+    static constexpr int WPC = NV == 1 ? (DH == 64 ? 3 : 2) : 1;
     // Four value tensors at head_dim 128: their accumulators take the 256 accumulation registers,
     // so the V^T fragments are read as the products need them (VLEAD ahead) instead of all in
     // phase S, and a slot's key and value parts are refilled at different blocks (SV).
@@ -109,10 +112,18 @@ struct FastCfg {
     static_assert(LDS_BYTES * WPC <= 160 * 1024, "LDS");
 };
 
-template <int DT, int DH, int NV>
+// WT: query tiles per workgroup.  Its four waves share one key/value head: four query heads over one
+// tile of 32 queries (WT 1, query heads per key/value head a multiple of 4), two heads over two
+// consecutive tiles (WT 2, two heads per key/value head) or one head over four (WT 4, multi-head
+// attention).  A "group tile" is WT consecutive query tiles, its key blocks those of its last one; a
+// wave whose own diagonal comes earlier idles through the rest (barriers and its share of the loads
+// only), so a query's arithmetic is the same for every WT.
+// single: a workgroup takes one group tile instead of a pair (grids that would leave CUs idle).
+template <int DT, int DH, int NV, int WT>
 __global__ __launch_bounds__(256, (FastCfg<DT, DH, NV>::WPC)) void attn_fast_kernel(AttnArgs a, float scale_log2,
-                                                                                 int nqt, int n_ht) {
+                                                                                 int nqt, int n_ht, int single) {
     typedef FastCfg<DT, DH, NV> C;
+    constexpr int HG = 4 / WT;                         // query heads per workgroup
     typedef typename Mma<DT>::elem elem;
     typedef Mma<DT> MM;
     typedef typename MM::operand opnd;
@@ -124,16 +135,32 @@ __global__ __launch_bounds__(256, (FastCfg<DT, DH, NV>::WPC)) void attn_fast_ker
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
 
-    // ---- the pair: pair p of group g = p / P (g = b n_ht + ht, P = ceil(nqt / 2)) holds query tiles
-    // nqt - 1 - p % P (first) and p % P (second; none when they coincide, the middle tile of an odd
-    // nqt).  With a grid that is a multiple of 8, XCD x (workgroup ids congruent to x mod 8) takes a
-    // contiguous eighth of the pairs.
+    // the wave's head and query tile of the group tile
+    const int wh = WT == 1 ? wave : wave % HG, wt = WT == 1 ? 0 : wave / HG;
+
+    // ---- the pair: pair p of group g = p / P (g = b n_ht + ht, P = ceil(nqg / 2)) holds group tiles
+    // nqg - 1 - p % P (first) and p % P (second; none when they coincide, the middle tile of an odd
+    // nqg).  With a grid that is a multiple of 8, XCD x (workgroup ids congruent to x mod 8) takes a
+    // contiguous eighth of the pairs.  single: the longest group tiles of all groups first, an XCD's
+    // groups its own where they divide evenly.
     const int nwg = gridDim.x;
-    int pair = blockIdx.x;
-    if ((nwg & 7) == 0) pair = (pair & 7) * (nwg >> 3) + (pair >> 3);
-    const int P = (nqt + 1) >> 1;
-    const int grp = pair / P, pp = pair - grp * P;
-    const int n_tiles = pp == nqt - 1 - pp ? 1 : 2;
+    const int nqg = (nqt + WT - 1) / WT;
+    int grp, pp, n_tiles;
+    if (single) {
+        const int ng = nwg / nqg;
+        const int per = (ng & 7) == 0 ? ng >> 3 : ng;
+        const int x = (ng & 7) == 0 ? (int)blockIdx.x & 7 : 0, i = (ng & 7) == 0 ? (int)blockIdx.x >> 3 : (int)blockIdx.x;
+        grp = x * per + i % per;
+        pp = i / per;                                  // group tile nqg - 1 - pp
+        n_tiles = 1;
+    } else {
+        int pair = blockIdx.x;
+        if ((nwg & 7) == 0) pair = (pair & 7) * (nwg >> 3) + (pair >> 3);
+        const int P = (nqg + 1) >> 1;
+        grp = pair / P;
+        pp = pair - grp * P;
+        n_tiles = pp == nqg - 1 - pp ? 1 : 2;
+    }
 
     // ---- DMA offsets (tile-invariant).  Load i < PK of this wave fills key-tile chunks 64 (wave +
     // 4 i) + lane: key row p / CK, physical chunk p % CK holding logical chunk (p % CK) ^
@@ -157,14 +184,16 @@ __global__ __launch_bounds__(256, (FastCfg<DT, DH, NV>::WPC)) void attn_fast_ker
     // ---- a tile: its query tile, head group and sequence, and the buffer resources of its keys
     // and values (wave-uniform)
     struct Tile {
-        int qt, ht, b;
+        int qg, ht, b;                                 // group tile
         i32x4 rsk, rsv[NV];
     };
-    auto make_tile = [&](int qt, int grp, Tile &t) {
-        t.qt = qt;
+    // its last key block (kept in the tile, the index cost registers in the block loop)
+    auto last_block = [&](const Tile &t) { return WT == 1 ? t.qg : min(t.qg * WT + WT, nqt) - 1; };
+    auto make_tile = [&](int qg, int grp, Tile &t) {
+        t.qg = qg;
         t.ht = grp % n_ht;
         t.b = grp / n_ht;
-        const int kvh = (t.ht * 4) / G;                // G is a multiple of 4: one kv head per workgroup
+        const int kvh = (t.ht * HG) / G;               // G is a multiple of HG: one kv head per workgroup
         t.rsk = buffer_rsrc(static_cast<const elem *>(a.k) + (int64_t)t.b * T * a.ld + kvh * DH);
 #pragma unroll
         for (int v = 0; v < NV; ++v)
@@ -172,7 +201,7 @@ __global__ __launch_bounds__(256, (FastCfg<DT, DH, NV>::WPC)) void attn_fast_ker
     };
     // i-th of the wave's PW loads of block j of tile t (block index clamped to the tile's last)
     auto issue_t = [&](const Tile &t, int i, int j, unsigned char *slot) {
-        const int jb = j < t.qt ? j : t.qt;
+        const int jl = last_block(t), jb = j < jl ? j : jl;
         if (i < C::PK) {
             buffer_dma16(t.rsk, dvoff[i], jb * kstride, slot + (wave + 4 * i) * 1024);
         } else {                                       // value tensor v, piece pc of its tile
@@ -203,9 +232,9 @@ __global__ __launch_bounds__(256, (FastCfg<DT, DH, NV>::WPC)) void attn_fast_ker
     // this wave's queries of tile t as B operands of S^T = K Q^T
     opnd qf[C::NKC];
     auto load_q = [&](const Tile &t) {
-        const int qrow = t.qt * 32 + l32;
+        const int qrow = (t.qg * WT + wt) * 32 + l32;
         const elem *qp = static_cast<const elem *>(a.q) + ((int64_t)t.b * T + min(qrow, T - 1)) * a.ld +
-                         (t.ht * 4 + wave) * DH;
+                         (t.ht * HG + wh) * DH;
 #pragma unroll
         for (int kc = 0; kc < C::NKC; ++kc) {
             u32x4 v = *reinterpret_cast<const u32x4 *>(qp + kc * 16 + half * 8);
@@ -215,7 +244,7 @@ __global__ __launch_bounds__(256, (FastCfg<DT, DH, NV>::WPC)) void attn_fast_ker
     };
 
     Tile cur;
-    make_tile(nqt - 1 - pp, grp, cur);
+    make_tile(nqg - 1 - pp, grp, cur);
     load_q(cur);
     issue_prologue(cur);
     constexpr int CR = DH / 4;                         // 16-byte chunks per teacher row
@@ -224,10 +253,12 @@ __global__ __launch_bounds__(256, (FastCfg<DT, DH, NV>::WPC)) void attn_fast_ker
 
   for (int n_tile = 0;; ++n_tile) {
     // ---- the current tile
-    const int qt = cur.qt, ht = cur.ht, b = cur.b;
-    const int h = ht * 4 + wave;
+    const int qt = cur.qg * WT + wt, ht = cur.ht, b = cur.b;   // (WT > 1: qt may lie past the last tile)
+    const int h = ht * HG + wh;
     const int q0 = qt * 32;
-    const int jlast = qt;                              // blocks 0 .. qt; block qt is the diagonal
+    // key blocks 0 .. jlast pass through the ring; the wave computes 0 .. jw, block jw its diagonal
+    const int jlast = last_block(cur);
+    const int jw = WT == 1 ? jlast : (qt < nqt ? qt : 0);
     const int64_t row0 = (int64_t)b * T;
     auto issue = [&](int i, int j, unsigned char *slot) { issue_t(cur, i, j, slot); };
 
@@ -236,17 +267,16 @@ __global__ __launch_bounds__(256, (FastCfg<DT, DH, NV>::WPC)) void attn_fast_ker
     // epilogue's reads (32 rows, one logical chunk) hit distinct banks.  Load i of a wave fills
     // chunks 64 (wave + 4 i) + lane of the slot; rows past the sequence read its last row.
     const bool pre_aref = NV == 1 && (a.mode & ATT_LOSS) && jlast >= 3;
-    const i32x4 rsa = buffer_rsrc(a.a_ref + (row0 + q0) * ac + ht * 4 * DH);
-    uint32_t aoff[NV == 1 ? C::PW : 1];
-    if constexpr (NV == 1) {
-#pragma unroll
-        for (int i = 0; i < C::PW; ++i) {
+    const int qb0 = cur.qg * WT * 32;                  // the group tile's first query
+    const i32x4 rsa = buffer_rsrc(a.a_ref + (row0 + qb0) * ac + ht * HG * DH);
+    // i-th load of wave wa's tile (its per-lane offset formed here: kept through the tile, the offsets
+    // cost registers that head_dim 128 does not have)
+    auto issue_aref = [&](int i, int wa, unsigned char *slot) {
+        if constexpr (NV == 1) {
             const int pch = (wave + 4 * i) * 64 + lane, r = pch / CR, c = (pch % CR) ^ (r & 15);
-            aoff[i] = (uint32_t)(min(r, T - 1 - q0) * ac * 4 + c * 16);
+            const int row = min((wa / HG) * 32 + r, T - 1 - qb0);
+            buffer_dma16(rsa, (uint32_t)(row * ac * 4 + c * 16), (wa % HG) * DH * 4, slot + (wave + 4 * i) * 1024);
         }
-    }
-    auto issue_aref = [&](int i, int wa, unsigned char *slot) {   // i-th load of wave wa's tile
-        if constexpr (NV == 1) buffer_dma16(rsa, aoff[i], wa * DH * 4, slot + (wave + 4 * i) * 1024);
     };
     static_assert(NV > 1 || 32 * DH * 4 == C::BLK, "a teacher tile fills one slot");
 
@@ -315,7 +345,7 @@ __global__ __launch_bounds__(256, (FastCfg<DT, DH, NV>::WPC)) void attn_fast_ker
 #pragma unroll
         for (int kc = 0; kc < C::NKC; ++kc) sa = MM::mma(kf[kc], qf[kc], kc == 0 ? f32x16{} : sa);
         {
-            if (jlast == 0)
+            if (jw == 0)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) mask_el(0, sa, e);
             float m = sa[0];
@@ -468,26 +498,48 @@ __global__ __launch_bounds__(256, (FastCfg<DT, DH, NV>::WPC)) void attn_fast_ker
             if constexpr (NEXT && CHECKED) mx = halves_max(m);
         };
 
+        // a block past the wave's diagonal: the barrier and its share of the refills
+        auto idle = [&](int j) {
+            unsigned char *st0 = smem + (j & (C::NS - 1)) * C::BLK;
+            wait_lgkm0();
+            wait_vmcnt<(C::NS - 3) * C::PW>();
+            raw_barrier();
+#pragma unroll
+            for (int k = 0; k < C::PW; ++k) {
+                if constexpr (C::SV) {
+                    if (k < C::PK) issue(k, j + 4, st0);
+                    else issue(k, j + 3, smem + ((j + 3) & (C::NS - 1)) * C::BLK);
+                } else if (pre_aref && j + C::NS > jlast) {
+                    issue_aref(k, j + C::NS - jlast - 1, st0);
+                } else {
+                    issue(k, j + C::NS, st0);
+                }
+            }
+        };
+
         int j = 0;
-        // groups of four blocks whose refills are real blocks (j + 3 + NS <= jlast, so the next
-        // block is unmasked too); the last NS blocks always run with a run-time slot
-        for (; j + 3 + C::NS <= jlast; j += 4) {
+        // groups of four blocks whose refills are real blocks (j + 3 + NS <= jlast) and whose next
+        // blocks are unmasked for every wave (WT 1: that follows; else j + 4 below the group tile's
+        // first query tile); the last NS blocks always run with a run-time slot
+        for (; j + 3 + C::NS <= jlast && (WT == 1 || j + 4 < cur.qg * WT); j += 4) {
             fblock(j, std::integral_constant<int, 0>(), sa, sb, yes(), no());
             fblock(j + 1, std::integral_constant<int, 1>(), sb, sa, yes(), no());
             fblock(j + 2, std::integral_constant<int, 2>(), sa, sb, yes(), no());
             fblock(j + 3, std::integral_constant<int, 3>(), sb, sa, yes(), no());
         }
         // the rest: unmasked blocks one at a time, the block before the diagonal, the diagonal
-        for (; j + 1 < jlast; ++j) {
+        for (; j + 1 < jw; ++j) {
             fblock(j, dyn(), sa, sb, yes(), no());
             const f32x16 t = sa; sa = sb; sb = t;
         }
-        if (j + 1 == jlast) {
+        if (j + 1 == jw) {
             fblock(j, dyn(), sa, sb, yes(), yes());
             const f32x16 t = sa; sa = sb; sb = t;
             ++j;
         }
         fblock(j, dyn(), sa, sb, no(), no());
+        if constexpr (WT > 1)
+            for (++j; j <= jlast; ++j) idle(j);
         wait_vmcnt<0>();
         l_run = halves_sum(l_run);                     // the query's row sum (both lanes)
     };
@@ -600,7 +652,7 @@ __global__ __launch_bounds__(256, (FastCfg<DT, DH, NV>::WPC)) void attn_fast_ker
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
             const double tse = wave_sum_f64((double)sse[v]);
-            if (lane == 0) {
+            if (lane == 0 && (WT == 1 || qt < nqt)) {
                 double *ps = a.partials[v] + ((int64_t)b * Hq * nq32 + (int64_t)h * nq32 + qt) * 2;
                 ps[0] = tse;
                 ps[1] = ta2;
@@ -613,19 +665,40 @@ __global__ __launch_bounds__(256, (FastCfg<DT, DH, NV>::WPC)) void attn_fast_ker
 }
 
 // NV > 1 takes the squared-error loss of NV value tensors (ATT_LOSS alone)
-template <int DT, int DH, int NV = 1>
-hipError_t launch_attn_fast(const AttnArgs &a, hipStream_t st) {
+template <int DT, int DH, int NV, int WT>
+hipError_t launch_attn_fast_wt(const AttnArgs &a, hipStream_t st) {
     typedef FastCfg<DT, DH, NV> C;
     if (NV > 1 && a.mode != ATT_LOSS) return hipErrorInvalidValue;
-    const int nqt = (a.seq_len + 31) / 32;
-    const int n_ht = a.n_heads / 4;
+    const int nqt = (a.seq_len + 31) / 32, nqg = (nqt + WT - 1) / WT;
+    const int n_ht = a.n_heads / (4 / WT);
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)DH);
-    hipError_t e = hipFuncSetAttribute((const void *)attn_fast_kernel<DT, DH, NV>,
+    hipError_t e = hipFuncSetAttribute((const void *)attn_fast_kernel<DT, DH, NV, WT>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS_BYTES);
     if (e != hipSuccess) return e;
-    const int n_pairs = (nqt + 1) / 2 * n_ht * a.batch;
-    attn_fast_kernel<DT, DH, NV><<<dim3(n_pairs), dim3(256), C::LDS_BYTES, st>>>(a, scale_log2, nqt, n_ht);
+    const int n_pairs = (nqg + 1) / 2 * n_ht * a.batch;
+    // pairs that do not give each CU two workgroups: one group tile per workgroup, the longest first
+    // (measured, pairs / single, us: 1 x 512 of 12 heads 15.2 / 10.5, 1 x 1024 19.8 / 15.0, 8 x 777 25.4 /
+    // 22.1; at 1 x 1999 of 32 heads of 128, one pair per CU, equal)
+    const bool single = n_pairs <= 512;
+    attn_fast_kernel<DT, DH, NV, WT><<<dim3(single ? nqg * n_ht * a.batch : n_pairs), dim3(256), C::LDS_BYTES, st>>>(
+        a, scale_log2, nqt, n_ht, single);
     return hipGetLastError();
+}
+
+// Four value tensors at head_dim 128 fill the accumulation registers and fit only without WT's
+// per-wave tiles (WT 2 and 4 spilled 315 registers): such groups go two at a time
+template <int DH>
+int fast_max_nv(const AttnArgs &a) { return DH == 64 || a.n_heads / a.n_kv_heads % 4 == 0 ? 4 : 2; }
+
+template <int DT, int DH, int NV = 1>
+hipError_t launch_attn_fast(const AttnArgs &a, hipStream_t st) {
+    const int G = a.n_heads / a.n_kv_heads;
+    if (G % 4 == 0) return launch_attn_fast_wt<DT, DH, NV, 1>(a, st);
+    if constexpr (NV <= 2 || DH == 64) {
+        if (G == 2) return launch_attn_fast_wt<DT, DH, NV, 2>(a, st);
+        if (G == 1) return launch_attn_fast_wt<DT, DH, NV, 4>(a, st);
+    }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace

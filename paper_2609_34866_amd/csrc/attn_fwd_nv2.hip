@@ -11,10 +11,6 @@ hipError_t run_attn_nv2(const AttnArgs &a, hipStream_t st) {
 }
 
 template hipError_t run_attn_nv2<F16, 16>(const AttnArgs &, hipStream_t);
-template hipError_t run_attn_nv2<F16, 64>(const AttnArgs &, hipStream_t);
-template hipError_t run_attn_nv2<F16, 128>(const AttnArgs &, hipStream_t);
 template hipError_t run_attn_nv2<BF16, 16>(const AttnArgs &, hipStream_t);
-template hipError_t run_attn_nv2<BF16, 64>(const AttnArgs &, hipStream_t);
-template hipError_t run_attn_nv2<BF16, 128>(const AttnArgs &, hipStream_t);
 
 }  // namespace jab
