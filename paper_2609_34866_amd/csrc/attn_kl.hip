@@ -158,19 +158,28 @@ __global__ __launch_bounds__(256) void attn_kl_kernel(KlArgs a, float scale_log2
     kl_finish(m_s, l_s, acc_d, acc_p, lse_t, scale_log2, qrow < T, a.partials + (((int64_t)b * Hq + h) * nqt + qt) * 2);
 }
 
-// The common configuration (16-bit, head_dim 64 or 128, query heads per key/value head a multiple
-// of 4, T a multiple of 32): a workgroup of 4 waves is 4 query heads of one key/value group over
-// the same 32 queries, and the student's and the teacher's key blocks stream into a ring of four
-// LDS slots (buffer_load ... lds, a block's loads shared by the four waves) three blocks ahead of
-// use.  Block j: its 2 x NKC score MFMAs on fragments read during block j - 1; one barrier (block
-// j + 1 has landed, and every wave has read block j's slot, which is then refilled with block
+// The 16-bit dtypes at head_dim 64 and 128: a workgroup of 4 waves shares one key/value head, as in
+// attn_fast_kernel (WT query tiles of 32 by 4 / WT query heads: WT 1 for query heads per key/value head
+// a multiple of 4, 2 for two, 4 for one), and the student's and the teacher's key blocks stream into a
+// ring of four LDS slots (buffer_load ... lds, a block's loads shared by the four waves) three blocks
+// ahead of use.  Block j: its 2 x NKC score MFMAs on fragments read during block j - 1; one barrier
+// (block j + 1 has landed, and every wave has read block j's slot, which is then refilled with block
 // j + 4); the fragment reads of block j + 1; then block j's vector work, under which those reads
-// land.  Only the diagonal block is masked.  Same per-row arithmetic as attn_kl_kernel.
-template <int DT, int DH>
-__global__ __launch_bounds__(256, 2) void attn_kl_ring_kernel(KlArgs a, float scale_log2, int nqt, int n_ht) {
+// land.  Only a wave's diagonal block is masked; past it the wave takes part in the barriers and loads
+// alone.  Same per-row arithmetic as attn_kl_kernel.
+// Bound by the vector unit: per block and wave 32 exponentials (16 cycles each) and about 110 other
+// operations against 2 NKC products of 32 cycles.  At head_dim 64 three workgroups share a CU.
+// Measured, attn_kl_kernel / this, us: 32 x 1024 with 12 heads of 64 and their own keys 271 / 136,
+// 8 x 777 59 / 31, 1 x 1999 with 32 query and 8 key heads of 128 169 / 53.  A branch-free move of the
+// reference was slower (701 / 711 at 16 x 2048).
+// RAG: T not a multiple of 32 (the check of the last block's rows in every block's loads costs 8 %).
+template <int DT, int DH, int WT, bool RAG>
+__global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_kl_ring_kernel(KlArgs a, float scale_log2, int nqt,
+                                                                             int n_ht) {
     typedef Mma<DT> MM;
     typedef typename MM::operand opnd;
     typedef typename MM::elem elem;
+    constexpr int HG = 4 / WT;                         // query heads per workgroup
     static_assert(DT != F32 && (DH == 64 || DH == 128), "ring configuration");
     constexpr int NKC = DH / 16;                       // k-steps of a score tile
     constexpr int CK = DH * 2 / 16;                    // 16-byte chunks per key row
@@ -185,28 +194,32 @@ __global__ __launch_bounds__(256, 2) void attn_kl_ring_kernel(KlArgs a, float sc
     const int nwg = gridDim.x;
     int lin = blockIdx.x;
     if ((nwg & 7) == 0) lin = (lin & 7) * (nwg >> 3) + (lin >> 3);
-    const int qt = nqt - 1 - lin % nqt;                // longest tiles first
-    const int ht = (lin / nqt) % n_ht;
-    const int b = lin / (nqt * n_ht);
+    const int nqg = (nqt + WT - 1) / WT;
+    const int qg = nqg - 1 - lin % nqg;                // longest group tiles first
+    const int ht = (lin / nqg) % n_ht;
+    const int b = lin / (nqg * n_ht);
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int h = ht * 4 + wave;
-    const int kvh = (ht * 4) / (Hq / a.n_kv_heads);
-    const int q0 = qt * 32, qrow = q0 + l32;           // T is a multiple of 32: every query is valid
-    const int jlast = qt;
+    const int h = ht * HG + (WT == 1 ? wave : wave % HG);
+    const int kvh = (ht * HG) / (Hq / a.n_kv_heads);
+    const int qt = qg * WT + (WT == 1 ? 0 : wave / HG);
+    const int qrow = qt * 32 + l32, qrc = min(qrow, T - 1);   // rows past the sequence: never counted
+    // key blocks 0 .. jlast pass through the ring, the wave's own are 0 .. jw
+    const int jlast = min(qg * WT + WT, nqt) - 1;
+    const int jw = WT == 1 ? jlast : (qt < nqt ? qt : 0);
     const int64_t row0 = (int64_t)b * T;
     const elem *qs = static_cast<const elem *>(a.qs), *qt_ = static_cast<const elem *>(a.qt);
 
     opnd qfs[NKC], qft[NKC];
     {
-        const int64_t r = (row0 + qrow) * a.ld + h * DH;
+        const int64_t r = (row0 + qrc) * a.ld + h * DH;
 #pragma unroll
         for (int kc = 0; kc < NKC; ++kc) {
             qfs[kc] = __builtin_bit_cast(opnd, *reinterpret_cast<const u32x4 *>(qs + r + s_k<DT, DH>(kc, half)));
             qft[kc] = __builtin_bit_cast(opnd, *reinterpret_cast<const u32x4 *>(qt_ + r + s_k<DT, DH>(kc, half)));
         }
     }
-    const float lse_t = a.lse_t[((int64_t)b * Hq + h) * T + qrow];
+    const float lse_t = a.lse_t[((int64_t)b * Hq + h) * T + qrc];
 
     // DMA: load i < PK of this wave fills key-tile chunks 64 (wave + 4 i) + lane: key row p / CK,
     // physical chunk p % CK holding logical chunk (p % CK) ^ swz_key(row) (the attention kernels'
@@ -224,10 +237,16 @@ __global__ __launch_bounds__(256, 2) void attn_kl_ring_kernel(KlArgs a, float sc
     const int kstride = a.ld * 2 * 32;
     auto issue = [&](int j, unsigned char *slot) {
         const int jb = min(j, jlast);
+        const int rows = T - jb * 32;                  // keys of the block
 #pragma unroll
         for (int i = 0; i < PK; ++i) {
-            buffer_dma16(rss, dvoff[i], jb * kstride, slot + (wave + 4 * i) * 1024);
-            buffer_dma16(rst, dvoff[i], jb * kstride, slot + K_BYTES + (wave + 4 * i) * 1024);
+            uint32_t v = dvoff[i];
+            if (RAG && rows < 32) {                         // the sequence's ragged last block: its last key again
+                const int p = (wave + 4 * i) * 64 + lane, r = p / CK, c = (p % CK) ^ swz_key<CK>(r);
+                v = (uint32_t)(min(r, rows - 1) * a.ld * 2 + c * 16);
+            }
+            buffer_dma16(rss, v, jb * kstride, slot + (wave + 4 * i) * 1024);
+            buffer_dma16(rst, v, jb * kstride, slot + K_BYTES + (wave + 4 * i) * 1024);
         }
     };
     uint32_t koff[NKC];
@@ -308,40 +327,61 @@ __global__ __launch_bounds__(256, 2) void attn_kl_ring_kernel(KlArgs a, float sc
     typedef std::integral_constant<bool, true> yes;
     typedef std::integral_constant<bool, false> no;
     int j = 0;
-    for (; j + 2 <= jlast; j += 2) {                   // blocks j, j + 1 before the diagonal
+    for (; j + 2 <= jw; j += 2) {                      // blocks j, j + 1 before the diagonal
         step(j, sA, tA, sB, tB, yes(), no());
         step(j + 1, sB, tB, sA, tA, yes(), no());
     }
-    if (j < jlast) {                                   // block jlast - 1, then the diagonal
+    if (j < jw) {                                      // block jw - 1, then the diagonal
         step(j, sA, tA, sB, tB, yes(), no());
         step(j + 1, sB, tB, sA, tA, no(), yes());
     } else {
         step(j, sA, tA, sB, tB, no(), yes());
     }
+    if constexpr (WT > 1) {
+        for (j = jw + 1; j <= jlast; ++j) {            // past the wave's diagonal
+            wait_lgkm0();
+            wait_vmcnt<(NS - 2) * PW>();
+            raw_barrier();
+            issue(j + NS, smem + (j & (NS - 1)) * BLK);
+        }
+    }
     wait_vmcnt<0>();                                   // no DMA into LDS outlives the workgroup
-    kl_finish(m_s, l_s, acc_d, acc_p, lse_t, scale_log2, true, a.partials + (((int64_t)b * Hq + h) * nqt + qt) * 2);
+    if (WT == 1 || qt < nqt)
+        kl_finish(m_s, l_s, acc_d, acc_p, lse_t, scale_log2, qrow < T,
+                  a.partials + (((int64_t)b * Hq + h) * nqt + qt) * 2);
+}
+
+template <int DT, int DH, int WT, bool RAG>
+hipError_t run_kl_ring(const KlArgs &a, hipStream_t st) {
+    const int nqt = (a.seq_len + 31) / 32;
+    constexpr int LDS = 4 * 2 * 32 * DH * 2;
+    hipError_t e = hipFuncSetAttribute((const void *)attn_kl_ring_kernel<DT, DH, WT, RAG>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+    if (e != hipSuccess) return e;
+    const int n_ht = a.n_heads / (4 / WT);
+    attn_kl_ring_kernel<DT, DH, WT, RAG><<<dim3((nqt + WT - 1) / WT * n_ht * a.batch), dim3(256), LDS, st>>>(
+        a, 1.4426950408889634f / sqrtf((float)DH), nqt, n_ht);
+    return hipGetLastError();
 }
 
 template <int DT, int DH>
 hipError_t run_kl(const KlArgs &a, hipStream_t st) {
-    const int nqt = (a.seq_len + 31) / 32;
     if constexpr (DT != F32 && (DH == 64 || DH == 128)) {
-        if ((a.n_heads / a.n_kv_heads) % 4 == 0 && a.seq_len % 32 == 0) {
-            constexpr int LDS = 4 * 2 * 32 * DH * 2;
-            hipError_t e = hipFuncSetAttribute((const void *)attn_kl_ring_kernel<DT, DH>,
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-            if (e != hipSuccess) return e;
-            const int n_ht = a.n_heads / 4;
-            attn_kl_ring_kernel<DT, DH><<<dim3(nqt * n_ht * a.batch), dim3(256), LDS, st>>>(
-                a, 1.4426950408889634f / sqrtf((float)DH), nqt, n_ht);
-            return hipGetLastError();
+        const int G = a.n_heads / a.n_kv_heads;
+        if (a.seq_len % 32 != 0) {
+            if (G == 1) return run_kl_ring<DT, DH, 4, true>(a, st);
+            return G == 2 ? run_kl_ring<DT, DH, 2, true>(a, st) : run_kl_ring<DT, DH, 1, true>(a, st);
         }
-    }
-    const int64_t n_waves = (int64_t)a.batch * a.n_heads * nqt;
-    const float scale_log2 = 1.4426950408889634f / sqrtf((float)DH);
-    attn_kl_kernel<DT, DH><<<dim3((unsigned)((n_waves + 3) / 4)), dim3(256), 0, st>>>(a, scale_log2, nqt,
+        if (G == 1) return run_kl_ring<DT, DH, 4, false>(a, st);
+        return G == 2 ? run_kl_ring<DT, DH, 2, false>(a, st) : run_kl_ring<DT, DH, 1, false>(a, st);
+    } else {
+        const int nqt = (a.seq_len + 31) / 32;
+        const int64_t n_waves = (int64_t)a.batch * a.n_heads * nqt;
+        const float scale_log2 = 1.4426950408889634f / sqrtf((float)DH);
+        attn_kl_kernel<DT, DH><<<dim3((unsigned)((n_waves + 3) / 4)), dim3(256), 0, st>>>(a, scale_log2, nqt,
                                                                                      (int)n_waves);
-    return hipGetLastError();
+        return hipGetLastError();
+    }
 }
 
 template <int DT>

@@ -1,0 +1,68 @@
+"""GPU attention with one, two and four query heads per key/value head: the kernels give a query the
+same arithmetic whatever share of a workgroup its head group takes, so a block whose key/value weights
+are repeated per query head has bitwise the results of the grouped block.  The lengths are the edges
+of the 32-query tiles and of the groups of two and four such tiles."""
+import pytest
+import torch
+
+from paper_2609_34866_amd import inputs, jab
+
+from gpu_helpers import small
+
+pytestmark = pytest.mark.gpu
+
+LENGTHS = (1, 31, 33, 64, 97, 128, 129, 200, 288, 421)
+
+
+def _repeat_kv(w, hq, dh, rep):
+    """Rows [Q | K | V] with one key/value head -> the same with `rep` copies of it."""
+    q, k, v = w[:hq * dh], w[hq * dh:(hq + 1) * dh], w[(hq + 1) * dh:]
+    return torch.cat([q] + [k] * rep + [v] * rep, 0).contiguous()
+
+
+def _everything(p, x, w, bits=(3, 3, 3)):
+    """Teacher output and log-sum-exp, the loss, the KL loss, a sweep of four value widths, the gradients."""
+    a, qk, lse = jab.attn_ref_kl(p, x, w)
+    scale, zero = jab.quant_init(p, w, bits)
+    out = jab.loss_fwd(p, x, w, bits, scale, zero, a)
+    kl = jab.loss_fwd_kl(p, x, w, bits, scale, zero, a, qk, lse)
+    widths = (2, 3, 4, 8)
+    sets = [jab.quant_init(p, w, (b, b, b)) for b in widths]
+    triples = [(3, 2, b) for b in widths] + [(4, 4, 2), (4, 4, 3), (4, 4, 8)]
+    sweep, _ = jab.loss_sweep(p, x, w, widths, [s for s, _ in sets], [z for _, z in sets], triples, a)
+    one = jab.loss_fwd(p, x, w, (0, 0, 0), scale, zero, a)
+    same = jab.loss_fwd_kl(p, x, w, (0, 0, 0), scale, zero, a, qk, lse)
+    assert float(one[0]) == 0.0 and float(same[3 + p.batch]) == 0.0       # the float point: exactly 0
+    return {"a": a, "lse": lse, "loss": out, "kl": kl, "sweep": sweep}
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("boost", [1.0, 12.0])
+def test_head_groups_agree_bitwise(dh, dtype, boost):
+    """boost scales W_Q: at 12 most queries overshoot their first block's maximum by more than 2^R, so
+    the tiles take the checked second pass."""
+    for T in LENGTHS:
+        base = small(batch=2, seq_len=T, d_model=128, n_heads=4, n_kv_heads=1, head_dim=dh, group_size=64, dtype=dtype)
+        x, w = inputs.make_x(base).cuda(), inputs.make_w(base)
+        w[:4 * dh] = (w[:4 * dh].float() * boost).to(w.dtype)
+        got = {}
+        for hkv in (1, 2, 4):
+            wl = base.with_(n_kv_heads=hkv)
+            got[hkv] = _everything(jab.problem_of(wl), x, _repeat_kv(w, 4, dh, hkv).cuda())
+        for hkv in (2, 4):
+            for k, v in got[1].items():
+                assert torch.equal(v, got[hkv][k]), (T, hkv, k)
+
+
+@pytest.mark.parametrize("hkv", [4, 2])
+def test_grouped_tiles_are_causal_for_any_value(hkv):
+    """A query's result does not see later tokens of its group tile, not even infinite ones (0 * inf)."""
+    wl = small(batch=1, seq_len=140, d_model=128, n_heads=4, n_kv_heads=hkv, head_dim=64, group_size=64, dtype="bf16")
+    x, w = inputs.make_x(wl).cuda(), inputs.make_w(wl).cuda()
+    p = jab.problem_of(wl)
+    a = jab.attn_ref(p, x, w)
+    y = x.clone()
+    y[0, 96:, 3] = float("inf")                        # the fourth 32-token block on
+    b = jab.attn_ref(p, y, w)
+    assert torch.equal(a[:, :96], b[:, :96])
