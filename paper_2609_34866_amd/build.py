@@ -42,9 +42,9 @@ def _compile(src: str) -> str:
     return obj
 
 
-# Translation units with matrix products written as inline asm (attn_fwd_fast.h's mma_v): their
+# Translation units with matrix products written as inline asm (mfma_asm.h's mma_v): their
 # device assembly is generated and checked for the hazards the compiler does not see.
-ASM_CHECKED = ["attn_fwd_fast_multi.hip"]
+ASM_CHECKED = ["attn_fwd_fast_multi.hip", "attn_jvp.hip"]
 MFMA_WINDOW = 19        # wait states between a product and any other access to its result
 
 

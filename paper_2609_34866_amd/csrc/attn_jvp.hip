@@ -24,7 +24,8 @@
 //    UK^T += V^T (P zK)^T, W^T += Vd^T P^T.  The row sums l, sum P zQ, sum P zK, sum P zQ^2,
 //    sum P zK^2, sum P zQ zK are lane-local fp32 sums (one half-wave exchange at the end); at the
 //    end a_hat = O / l, aQ = UQ / l - (mQ / l) a_hat, ...
-//  * Workgroups of 4 waves, one per SIMD (the four fp32 accumulator sets of 32 queries x head_dim
+//  * attn_jvp_kernel (fp32, fp16, head_dim 16; bf16 at head_dim 64 and 128: attn_jvp_fast_kernel below).
+//    Workgroups of 4 waves, one per SIMD (the four fp32 accumulator sets of 32 queries x head_dim
 //    take 256 registers at head_dim 128); each wave owns 32 queries of one query head, and the
 //    workgroup's waves share a key/value head, so one copy of the K, Kd, V^T, Vd^T tiles of a block
 //    serves them all.  The tiles stream from global memory into an LDS ring by direct-to-LDS loads,
@@ -33,6 +34,7 @@
 //    so the tangent-weighted probabilities stay in fp16 range); a rescale multiplies every
 //    accumulator and row sum by the same factor.  Deterministic: no atomics, fixed orders.
 #include "attn_fwd_impl.h"
+#include "mfma_asm.h"
 
 namespace jab {
 namespace {
@@ -372,6 +374,407 @@ __global__ __launch_bounds__(256, 1) void attn_jvp_kernel(JvpArgs a, float scale
     }
 }
 
+// ---------------------------------------------------------------- bf16, head_dim 64 and 128
+// One pass over all output rows with one wave per SIMD: the four accumulator sets of head_dim 128 fill
+// the 256 accumulation registers, the scores' results stay in architectural ones (mma_v).  A block's
+// work is software-pipelined over two phases:
+//   phase 1 of block j: the value products of block j - 1 (8 NDB products) with block j's softmax and
+//     tangent sums (about 16 vector operations per score) in their shadow;
+//   phase 2: the three score products of block j + 1 (3 NKC products).
+// Before the last group of value products, one barrier: block j + 1 has landed for every wave, and
+// every wave has read block j - 1's values, whose slot takes block j + 3; the first key fragments of
+// block j + 1 are read under those products.
+// As in attn_fast_kernel, a query's reference is the maximum of its first block and stays there (no
+// maximum, compare or branch per block); a query whose row sum then exceeds 2^R, R = 64, or whose sums are
+// not finite repeats the tile with a reference that moves on an overshoot beyond 2^R (infinite for the
+// queries that are not flagged, so their arithmetic is the same in both passes).  The products of
+// probabilities up to 2^64 and logit tangents stay far below the end of the fp32 and bf16 range; fp16,
+// which ends at 2^16, keeps attn_jvp_kernel and its reference that is never exceeded.
+// Measured, attn_jvp_kernel (two passes at head_dim 128, nothing overlapped) / this, us per probe: 4 x 2048
+// with 32 / 8 heads of 128 1457 / 519 (41 % matrix-core busy), 1 x 999 174 / 56, 8 x 1024 with 12 heads of
+// 64 185 / 98.  About 1.4 us per block (56 products, 0.9 us, and 215 + 16 vector operations that share
+// the wave's issue slots) and 19 us per tile (loads, start-up, epilogue).  A rescale inside the one
+// pass made the compiler move all 256 accumulators through the architectural registers every block.
+template <int DT, int DH>
+struct JvpFast {
+    static constexpr int NKC = DH / 16, NDB = DH / 32;
+    static constexpr int CK = DH * 2 / 16;             // chunks per key row
+    static constexpr int KB = 32 * CK * 16, VB = DH * 4 * 16;
+    static constexpr int STAGE = 2 * KB + 2 * VB;      // K | Kd | V^T | Vd^T
+    static constexpr int NS = 4;
+    static constexpr int PK = KB / 4096, PV = VB / 4096;   // DMA instructions per wave and tile
+    static constexpr int PW = 2 * PK + 2 * PV;
+    static constexpr int NG = 2 * NDB;                 // value groups (k-step g, row block d): 4 products each
+    static constexpr float R = 64.f;
+    static constexpr int LDS_BYTES = NS * STAGE + 16;  // the pass flags follow the ring
+    static_assert(DT == BF16 && LDS_BYTES <= 160 * 1024, "bf16; LDS");
+};
+
+template <int DT, int DH, int WT>
+__global__ __launch_bounds__(256, 1) void attn_jvp_fast_kernel(JvpArgs a, float scale_log2, float inv_sqrt, int nqt,
+                                                               int n_ht) {
+    typedef JvpFast<DT, DH> C;
+    typedef typename Mma<DT>::elem elem;
+    typedef Mma<DT> MM;
+    typedef typename MM::operand opnd;
+    constexpr int HG = 4 / WT;                         // heads x query tiles of the workgroup's waves
+    extern __shared__ __align__(16) unsigned char smem[];
+
+    const int T = a.seq_len, Hq = a.n_heads, Tp = vt_pad(T);
+    const int nwg = gridDim.x, nqg = (nqt + WT - 1) / WT;
+    int lin = blockIdx.x;
+    if ((nwg & 7) == 0) lin = (lin & 7) * (nwg >> 3) + (lin >> 3);
+    const int qg = nqg - 1 - lin % nqg;                // longest group tiles first
+    const int ht = (lin / nqg) % n_ht, b = lin / (nqg * n_ht);
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int h = ht * HG + (WT == 1 ? wave : wave % HG);
+    const int kvh = ht * HG / (Hq / a.n_kv_heads);
+    const int qt = qg * WT + (WT == 1 ? 0 : wave / HG);
+    const int q0 = qt * 32, qrow = q0 + l32;
+    // key blocks 0 .. jlast pass through the ring; the wave's are 0 .. jw, block jw its diagonal
+    const int jlast = min(qg * WT + WT, nqt) - 1;
+    const int jw = WT == 1 ? jlast : (qt < nqt ? qt : 0);
+    const int64_t row0 = (int64_t)b * T;
+
+    opnd qf[C::NKC], qdf[C::NKC];
+    {
+        const int64_t r = (row0 + min(qrow, T - 1)) * a.ld + h * DH + half * 8;
+#pragma unroll
+        for (int kc = 0; kc < C::NKC; ++kc) {
+            u32x4 v = *reinterpret_cast<const u32x4 *>(static_cast<const elem *>(a.q) + r + kc * 16);
+            u32x4 vd = *reinterpret_cast<const u32x4 *>(static_cast<const elem *>(a.qd) + r + kc * 16);
+            if (qrow >= T) { v = u32x4{0u, 0u, 0u, 0u}; vd = v; }
+            qf[kc] = __builtin_bit_cast(opnd, v);
+            qdf[kc] = __builtin_bit_cast(opnd, vd);
+        }
+    }
+
+    // ---- DMA, as attn_fast_kernel: load i < PK of a key tile fills chunks 64 (wave + 4 i) + lane (row
+    // p / CK, logical chunk (p % CK) ^ swz_key(row)), a value tile likewise.  Keys past the sequence read
+    // the rows that follow (the next sequence, the slack rows); blocks past the tile its last block.
+    const i32x4 rsk = buffer_rsrc(static_cast<const elem *>(a.k) + row0 * a.ld + kvh * DH);
+    const i32x4 rskd = buffer_rsrc(static_cast<const elem *>(a.kd) + row0 * a.ld + kvh * DH);
+    const i32x4 rsv = buffer_rsrc(static_cast<const elem *>(a.vt) + (int64_t)kvh * DH * a.ldv + (int64_t)b * Tp);
+    const i32x4 rsvd = buffer_rsrc(static_cast<const elem *>(a.vdt) + (int64_t)kvh * DH * a.ldv + (int64_t)b * Tp);
+    uint32_t kvoff[C::PK], vvoff[C::PV];
+#pragma unroll
+    for (int i = 0; i < C::PK; ++i) {
+        const int p = (wave + 4 * i) * 64 + lane, r = p / C::CK, c = (p % C::CK) ^ swz_key<C::CK>(r);
+        kvoff[i] = (uint32_t)(r * a.ld * 2 + c * 16);
+    }
+#pragma unroll
+    for (int i = 0; i < C::PV; ++i) {
+        const int p = (wave + 4 * i) * 64 + lane, r = p / 4, c = (p % 4) ^ swz_key<4>(r);
+        vvoff[i] = (uint32_t)(r * (int)a.ldv * 2 + c * 16);
+    }
+    const int kstride = a.ld * 64;                     // bytes between key blocks
+    auto issue_one = [&](int i, int j) {               // i-th of the wave's PW loads of block j
+        const int jb = min(j, jlast);
+        unsigned char *st = smem + (j & (C::NS - 1)) * C::STAGE + wave * 1024;
+        if (i < C::PK) buffer_dma16(rsk, kvoff[i], jb * kstride, st + i * 4096);
+        else if (i < 2 * C::PK) buffer_dma16(rskd, kvoff[i - C::PK], jb * kstride, st + C::KB + (i - C::PK) * 4096);
+        else if (i < 2 * C::PK + C::PV) buffer_dma16(rsv, vvoff[i - 2 * C::PK], jb * 64, st + 2 * C::KB + (i - 2 * C::PK) * 4096);
+        else buffer_dma16(rsvd, vvoff[i - 2 * C::PK - C::PV], jb * 64, st + 2 * C::KB + C::VB + (i - 2 * C::PK - C::PV) * 4096);
+    };
+    auto issue = [&](int j) {
+#pragma unroll
+        for (int i = 0; i < C::PW; ++i) issue_one(i, j);
+    };
+
+    // ---- fragment reads: per-lane offsets, the slot and the tile added
+    uint32_t koff[C::NKC], voff[2];
+#pragma unroll
+    for (int kc = 0; kc < C::NKC; ++kc)
+        koff[kc] = (uint32_t)(l32 * C::CK * 16 + (((2 * kc + half) ^ swz_key<C::CK>(l32)) * 16));
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+        voff[g] = (uint32_t)(2 * C::KB + l32 * 64 + (((2 * g + half) ^ swz_key<4>(l32)) * 16));
+    auto slot = [&](int j) -> const unsigned char * { return smem + (j & (C::NS - 1)) * C::STAGE; };
+    auto rd = [](const unsigned char *p) -> opnd { return __builtin_bit_cast(opnd, *reinterpret_cast<const u32x4 *>(p)); };
+    // the two value fragments of group t = g NDB + d
+    auto rd_v = [&](const unsigned char *st, int t, opnd &v, opnd &vd) {
+        const unsigned char *p = st + voff[t / C::NDB] + (t % C::NDB) * 2048;
+        v = rd(p);
+        vd = rd(p + C::VB);
+    };
+
+    f32x16 o[C::NDB], uq[C::NDB], uk[C::NDB], wv[C::NDB];
+    float m_run, l_run, mq_run, mk_run, cqq, ckk, cqk;
+    float thr = INFINITY;                              // checked pass: the overshoot that moves the reference
+    f32x16 s, sq, sk;                                  // scores of the next softmax block
+    float mx = 0.f;                                    // ... and their maximum (log2 units)
+    uint32_t pp[8], pq[8], pk[8];                      // the last softmax block's P, P zQ, P zK, packed
+    // the key fragments stream through four registers sets: read f < NKC is K's k-step f, the others Kd's
+    constexpr int LA = 3;                              // reads ahead of their products
+    opnd kf[LA + 1];
+    auto rd_key = [&](const unsigned char *st, int f) {
+        kf[f % (LA + 1)] = rd(f < C::NKC ? st + koff[f] : st + C::KB + koff[f - C::NKC]);
+    };
+
+    // the score products of block j (phase 2; its first LA fragments are read): s and sq side by side,
+    // then sk; MAX: the maximum of s.  s and sq are complete 19 wait states after their last products, which sk's take up
+    auto scores = [&](int j, auto mask_c, auto max_c) {
+        constexpr bool MASK = decltype(mask_c)::value, MAX = decltype(max_c)::value;
+        static_assert(C::NKC >= 4, "sk's products cover the last ones of s and sq");
+        const unsigned char *st = slot(j);
+        const int lim = qrow - 32 * j - 4 * half;
+        SCHED_FENCE();
+#pragma unroll
+        for (int f = 0; f < 2 * C::NKC; ++f) {
+            const int kc = f % C::NKC;
+            if (f + LA < 2 * C::NKC) rd_key(st, f + LA);
+            if (f < C::NKC) {
+                s = mma_v<DT>(kf[f % (LA + 1)], qf[kc], s, kc == 0, false);
+                sq = mma_v<DT>(kf[f % (LA + 1)], qdf[kc], sq, kc == 0, false);
+            } else {
+                sk = mma_v<DT>(kf[f % (LA + 1)], qf[kc], sk, kc == 0, kc == C::NKC - 1);
+            }
+            SCHED_FENCE();
+        }
+        float m = -INFINITY;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            if (MASK && 8 * (e >> 2) + (e & 3) > lim) { s[e] = -INFINITY; sq[e] = 0.f; sk[e] = 0.f; }
+            if constexpr (MAX) m = fmaxf(m, s[e]);
+        }
+        if constexpr (MAX) mx = halves_max(m) * scale_log2;
+    };
+
+    // value products of block j (its packed probabilities in pp, pq, pk) from group t on; NEXTV: phase 1,
+    // with the softmax of the scores in s, sq, sk under them and the barrier before the last group
+    auto product = [&](int t, const opnd &v, const opnd &vd, const opnd &bp, const opnd &bq, const opnd &bk) {
+        const int d = t % C::NDB;
+        o[d] = MM::mma(v, bp, o[d]);
+        uq[d] = MM::mma(v, bq, uq[d]);
+        uk[d] = MM::mma(v, bk, uk[d]);
+        wv[d] = MM::mma(vd, bp, wv[d]);
+    };
+    auto operand = [](const uint32_t (&x)[8], int g) -> opnd {
+        return __builtin_bit_cast(opnd, u32x4{x[4 * g], x[4 * g + 1], x[4 * g + 2], x[4 * g + 3]});
+    };
+
+    typedef std::integral_constant<bool, true> yes;
+    typedef std::integral_constant<bool, false> no;
+    // phase 1 of block j (VAL: block j - 1's value products; NEXT: block j + 1 is the wave's too)
+    auto phase1 = [&](int j, auto val_c, auto next_c, auto checked_c) {
+        constexpr bool VAL = decltype(val_c)::value, NEXT = decltype(next_c)::value;
+        constexpr bool CHECKED = decltype(checked_c)::value;
+        // the reference of block j
+        bool moved = false;
+        float alpha = 1.f;
+        if constexpr (!VAL) {
+            m_run = mx;                                // block 0's maximum
+        } else if constexpr (CHECKED) {
+            const bool move = mx > m_run + thr;
+            moved = __any(move);
+            if (moved) {
+                const float m_new = move ? mx : m_run;
+                alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+                l_run *= alpha; mq_run *= alpha; mk_run *= alpha; cqq *= alpha; ckk *= alpha; cqk *= alpha;
+                m_run = m_new;
+            }
+        }
+        const unsigned char *sv = slot(j - 1);
+        opnd vf[2], vdf[2];
+        opnd bp[2], bq[2], bk[2];
+        if constexpr (VAL) {
+#pragma unroll
+            for (int g = 0; g < 2; ++g) { bp[g] = operand(pp, g); bq[g] = operand(pq, g); bk[g] = operand(pk, g); }
+            rd_v(sv, 0, vf[0], vdf[0]);
+        }
+        float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[0], scale_log2, -m_run));
+        float p1 = 0.f, tq1 = 0.f, tk1 = 0.f;
+        SCHED_FENCE();
+        constexpr int EPG = 16 / C::NG;                // scores per value group
+#pragma unroll
+        for (int t = 0; t < C::NG; ++t) {
+            if constexpr (VAL)
+                if (t + 1 < C::NG) rd_v(sv, t + 1, vf[(t + 1) & 1], vdf[(t + 1) & 1]);
+            if (t == C::NG - 1) {
+                // every wave has read block j - 1's values; block j + 1 has landed
+                wait_lgkm0();
+                wait_vmcnt<C::PW>();
+                raw_barrier();
+#pragma unroll
+                for (int f = 0; f < LA; ++f)
+                    if (NEXT) rd_key(slot(j + 1), f);
+                issue(j + 3);
+            }
+#pragma unroll
+            for (int x = 0; x < EPG; ++x) {
+                const int e = t * EPG + x;
+                if constexpr (VAL) {
+                    // the group's four products spread over its scores
+                    const int d = t % C::NDB, g = t / C::NDB;
+                    const opnd &v = vf[t & 1], &vd = vdf[t & 1];
+                    if (x * 4 / EPG == 0 && x == 0) o[d] = MM::mma(v, bp[g], o[d]);
+                    if (EPG == 2 ? x == 0 : x == 1) uq[d] = MM::mma(v, bq[g], uq[d]);
+                }
+                const float pe = p;
+                if (e + 1 < 16) p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e + 1], scale_log2, -m_run));
+                // logit tangents in natural units: the factor goes with the probability
+                const float pi = pe * inv_sqrt;
+                const float tq = pi * sq[e], tk = pi * sk[e];
+                l_run += pe;
+                mq_run += tq;
+                mk_run += tk;
+                if constexpr (VAL) {
+                    const int d = t % C::NDB, g = t / C::NDB;
+                    const opnd &v = vf[t & 1], &vd = vdf[t & 1];
+                    if (EPG == 2 ? x == 1 : x == 2) uk[d] = MM::mma(v, bk[g], uk[d]);
+                    if (x == EPG - 1) wv[d] = MM::mma(vd, bp[g], wv[d]);
+                }
+                cqq = __builtin_fmaf(tq, sq[e], cqq);  // times inv_sqrt at the end
+                ckk = __builtin_fmaf(tk, sk[e], ckk);
+                cqk = __builtin_fmaf(tq, sk[e], cqk);
+                if (e & 1) {
+                    pp[e >> 1] = pack2<DT>(p1, pe);
+                    pq[e >> 1] = pack2<DT>(tq1, tq);
+                    pk[e >> 1] = pack2<DT>(tk1, tk);
+                } else {
+                    p1 = pe; tq1 = tq; tk1 = tk;
+                }
+                SCHED_FENCE();
+            }
+        }
+        if (CHECKED && VAL && moved) {
+            // the accumulators still held block j - 1's reference.  In place in the accumulation registers (the compiler's own form would stage
+            // all of them through the architectural ones), in a basic block of its own
+#pragma unroll
+            for (int d = 0; d < C::NDB; ++d)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    auto mul = [&](f32x16 &acc) {
+                        float x = acc[e], y;
+                        asm volatile("v_accvgpr_read_b32 %1, %0\n\tv_mul_f32 %1, %1, %2\n\tv_accvgpr_write_b32 %0, %1"
+                                     : "+a"(x), "=&v"(y) : "v"(alpha));
+                        acc[e] = x;
+                    };
+                    mul(o[d]); mul(uq[d]); mul(uk[d]); mul(wv[d]);
+                }
+        }
+    };
+
+    auto tile_pass = [&](auto checked) {
+#pragma unroll
+        for (int d = 0; d < C::NDB; ++d)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) { o[d][e] = 0.f; uq[d][e] = 0.f; uk[d][e] = 0.f; wv[d][e] = 0.f; }
+        l_run = mq_run = mk_run = cqq = ckk = cqk = 0.f;
+        // blocks 0 .. 2 in flight, block 0's scores
+        issue(0);
+        issue(1);
+        issue(2);
+        wait_vmcnt<2 * C::PW>();
+        raw_barrier();
+#pragma unroll
+        for (int f = 0; f < LA; ++f) rd_key(smem, f);
+        if (jw == 0) {
+            scores(0, yes(), yes());
+            phase1(0, no(), no(), checked);
+        } else {
+            scores(0, no(), yes());
+            phase1(0, no(), yes(), checked);
+            for (int j = 1; j < jw; ++j) {
+                scores(j, no(), checked);
+                phase1(j, yes(), yes(), checked);
+            }
+            scores(jw, yes(), checked);
+            phase1(jw, yes(), no(), checked);
+        }
+        {   // the value products of the diagonal block
+            const unsigned char *sv = slot(jw);
+#pragma unroll
+            for (int t = 0; t < C::NG; ++t) {
+                opnd v, vd;
+                rd_v(sv, t, v, vd);
+                product(t, v, vd, operand(pp, t / C::NDB), operand(pq, t / C::NDB), operand(pk, t / C::NDB));
+            }
+        }
+        if constexpr (WT > 1) {
+            for (int j = jw + 1; j <= jlast; ++j) {    // past the wave's diagonal
+                wait_lgkm0();
+                wait_vmcnt<C::PW>();
+                raw_barrier();
+                issue(j + 3);
+            }
+        }
+        wait_vmcnt<0>();                               // no load into LDS outlives the pass
+    };
+    tile_pass(no());
+    {
+        // flagged queries (NaN sums too): the four waves decide together, they share the ring
+        const float l = halves_sum(l_run);
+        const float fin = (mq_run + mk_run) * 0.f + (cqq + ckk + cqk) * 0.f;   // 0, or NaN
+        const bool bad = !(l <= __builtin_exp2f(C::R) && halves_sum(fin) == 0.f) && qrow < T;
+        int *flags = reinterpret_cast<int *>(smem + C::NS * C::STAGE);
+        const int any_bad = __any(bad) ? 1 : 0;
+        wait_lgkm0();
+        raw_barrier();                                 // every wave is done with the ring
+        if (lane == 0) flags[wave] = any_bad;
+        wait_lgkm0();
+        raw_barrier();
+        if (flags[0] | flags[1] | flags[2] | flags[3]) {
+            thr = bad ? C::R : INFINITY;
+            tile_pass(yes());
+        }
+    }
+
+    // ---- epilogue: the unit tangents of the output and their dot products per query row
+    l_run = halves_sum(l_run);
+    mq_run = halves_sum(mq_run);
+    mk_run = halves_sum(mk_run);
+    cqq = halves_sum(cqq) * inv_sqrt;
+    ckk = halves_sum(ckk) * inv_sqrt;
+    cqk = halves_sum(cqk) * inv_sqrt;
+    if (q0 >= T) return;
+    const bool valid = qrow < T;
+    const float inv_l = valid ? 1.f / l_run : 0.f;
+    const float mq = mq_run * inv_l, mk = mk_run * inv_l;
+    float e6[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int d = 0; d < C::NDB; ++d)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const float ah = o[d][e] * inv_l;
+            const float aq = uq[d][e] * inv_l - mq * ah;
+            const float ak = uk[d][e] * inv_l - mk * ah;
+            const float av = wv[d][e] * inv_l;
+            e6[0] = __builtin_fmaf(aq, aq, e6[0]);
+            e6[1] = __builtin_fmaf(ak, ak, e6[1]);
+            e6[2] = __builtin_fmaf(av, av, e6[2]);
+            e6[3] = __builtin_fmaf(aq, ak, e6[3]);
+            e6[4] = __builtin_fmaf(aq, av, e6[4]);
+            e6[5] = __builtin_fmaf(ak, av, e6[5]);
+        }
+    double r[kJvpParts];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) r[i] = valid ? (double)e6[i] : 0.0;   // each half holds half the columns
+    const bool once = valid && half == 0;              // the Fisher-information terms are per row
+    r[6] = once ? (double)(cqq * inv_l - mq * mq) : 0.0;
+    r[7] = once ? (double)(ckk * inv_l - mk * mk) : 0.0;
+    r[8] = once ? (double)(cqk * inv_l - mq * mk) : 0.0;
+    double *out = a.partials + (((int64_t)b * Hq + h) * nqt + qt) * kJvpParts;
+#pragma unroll
+    for (int i = 0; i < kJvpParts; ++i) {
+        const double t = wave_sum_f64(r[i]);
+        if (lane == 0) out[i] = t;
+    }
+}
+
+template <int DT, int DH, int WT>
+hipError_t run_jvp_fast(const JvpArgs &a, hipStream_t st) {
+    typedef JvpFast<DT, DH> C;
+    const int nqt = (a.seq_len + 31) / 32, n_ht = a.n_heads / (4 / WT);
+    hipError_t e = hipFuncSetAttribute((const void *)attn_jvp_fast_kernel<DT, DH, WT>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
+    if (e != hipSuccess) return e;
+    attn_jvp_fast_kernel<DT, DH, WT><<<dim3((nqt + WT - 1) / WT * n_ht * a.batch), dim3(256), C::LDS_BYTES, st>>>(
+        a, 1.4426950408889634f / sqrtf((float)DH), 1.f / sqrtf((float)DH), nqt, n_ht);
+    return hipGetLastError();
+}
+
 // Sum of the [n][9] partials in a fixed order, in two stages: block c of stage 1 sums the
 // contiguous chunk [c n / 256, (c + 1) n / 256) (thread t takes its entries t, t + 256, ... in
 // ascending order, then a fixed tree over the threads) into chunk[c][9]; stage 2 sums the 256
@@ -422,28 +825,34 @@ __global__ void curv_forms_kernel(const double *__restrict__ e, double lambda, d
 template <int DT, int DH>
 hipError_t run_jvp(const JvpArgs &a, hipStream_t st, int64_t *n_partials) {
     typedef JvpCfg<DT, DH> C;
-    *n_partials = (int64_t)C::NPASS * a.batch * a.n_heads * ((a.seq_len + 31) / 32);
+    constexpr bool FAST = DT == BF16 && (DH == 64 || DH == 128);
+    *n_partials = (int64_t)(FAST ? 1 : C::NPASS) * a.batch * a.n_heads * ((a.seq_len + 31) / 32);
     // buffer offsets from a sequence's rows (keys) or a key/value head's rows (values) are 32-bit
     if ((int64_t)(a.seq_len + 32) * a.ld * C::ES >= (1ll << 31) || (int64_t)DH * a.ldv * C::ES >= (1ll << 31))
         return hipErrorInvalidValue;
     const int G = a.n_heads / a.n_kv_heads;
-    const int hpw = G % 4 == 0 ? 4 : G;                // query heads per workgroup tile (1, 2 or 4)
-    const int QT = 4 * 32 / hpw;
-    const int nqt = (a.seq_len + QT - 1) / QT;
-    const int n_ht = a.n_heads / hpw;
-    const float scale_log2 = 1.4426950408889634f / sqrtf((float)DH);
-    const float inv_sqrt = 1.f / sqrtf((float)DH);
-    const size_t lds = (size_t)C::NS * C::STAGE;
-    hipError_t e = hipFuncSetAttribute((const void *)attn_jvp_kernel<DT, DH>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    for (int pass = 0; pass < C::NPASS; ++pass) {
-        attn_jvp_kernel<DT, DH><<<dim3(nqt * n_ht * a.batch), dim3(256), lds, st>>>(a, scale_log2, inv_sqrt, hpw,
-                                                                                    nqt, n_ht, pass);
-        e = hipGetLastError();
+    if constexpr (FAST) {
+        if (G == 1) return run_jvp_fast<DT, DH, 4>(a, st);
+        return G == 2 ? run_jvp_fast<DT, DH, 2>(a, st) : run_jvp_fast<DT, DH, 1>(a, st);
+    } else {
+        const int hpw = G % 4 == 0 ? 4 : G;                // query heads per workgroup tile (1, 2 or 4)
+        const int QT = 4 * 32 / hpw;
+        const int nqt = (a.seq_len + QT - 1) / QT;
+        const int n_ht = a.n_heads / hpw;
+        const float scale_log2 = 1.4426950408889634f / sqrtf((float)DH);
+        const float inv_sqrt = 1.f / sqrtf((float)DH);
+        const size_t lds = (size_t)C::NS * C::STAGE;
+        hipError_t e = hipFuncSetAttribute((const void *)attn_jvp_kernel<DT, DH>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
+        for (int pass = 0; pass < C::NPASS; ++pass) {
+            attn_jvp_kernel<DT, DH><<<dim3(nqt * n_ht * a.batch), dim3(256), lds, st>>>(a, scale_log2, inv_sqrt, hpw,
+                                                                                        nqt, n_ht, pass);
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
     }
-    return hipSuccess;
 }
 
 template <int DT>

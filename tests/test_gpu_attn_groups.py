@@ -2,12 +2,14 @@
 same arithmetic whatever share of a workgroup its head group takes, so a block whose key/value weights
 are repeated per query head has bitwise the results of the grouped block.  The lengths are the edges
 of the 32-query tiles and of the groups of two and four such tiles."""
+import numpy as np
 import pytest
 import torch
 
+from oracle import reference as ref
 from paper_2609_34866_amd import inputs, jab
 
-from gpu_helpers import small
+from gpu_helpers import oracle_problem, small
 
 pytestmark = pytest.mark.gpu
 
@@ -66,3 +68,42 @@ def test_grouped_tiles_are_causal_for_any_value(hkv):
     y[0, 96:, 3] = float("inf")                        # the fourth 32-token block on
     b = jab.attn_ref(p, y, w)
     assert torch.equal(a[:, :96], b[:, :96])
+
+
+def _curvature(base, hkv, dh, w, x, boost):
+    """Forms of two probes with the key/value part of the block repeated hkv times."""
+    p = jab.problem_of(base.with_(n_kv_heads=hkv))
+    probes = inputs.make_probes(base, 2, seed=5)
+    rep = torch.stack([_repeat_kv(v, 4, dh, hkv) for v in probes])
+    return jab.curvature(p, x, _repeat_kv(w, 4, dh, hkv).cuda(), rep.cuda(), 0.5)
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("boost", [1.0, 12.0])
+def test_curvature_head_groups_agree_bitwise(dh, boost):
+    """The tangent kernel's groupings, in the first pass (boost 1) and the checked one (boost 12)."""
+    for T in LENGTHS:
+        base = small(batch=2, seq_len=T, d_model=128, n_heads=4, n_kv_heads=1, head_dim=dh, group_size=64, dtype="bf16")
+        x, w = inputs.make_x(base).cuda(), inputs.make_w(base)
+        w[:4 * dh] = (w[:4 * dh].float() * boost).to(w.dtype)
+        want = _curvature(base, 1, dh, w, x, boost)
+        assert bool(torch.isfinite(want).all())
+        for hkv in (2, 4):
+            assert torch.equal(_curvature(base, hkv, dh, w, x, boost), want), (T, hkv)
+
+
+@pytest.mark.parametrize("hq,hkv,dh", [(4, 1, 128), (2, 2, 64)])
+def test_curvature_checked_pass_matches_oracle(hq, hkv, dh):
+    """Small first tokens make every later query overshoot its first block's maximum by more than 2^64:
+    all such tiles take the checked pass.  Bar as test_gpu_curvature's for bf16, 3e-2 of the pooled form:
+    the rounding of P zQ (2^-9 of each term) against a nearly one-hot map."""
+    wl = small(batch=1, seq_len=130, d_model=128, n_heads=hq, n_kv_heads=hkv, head_dim=dh, group_size=64, dtype="bf16")
+    x, w = inputs.make_x(wl), inputs.make_w(wl)
+    x[:, :32] = (x[:, :32].float() * 2.0 ** -6).to(x.dtype)
+    w[:(hq + hkv) * dh] = (w[:(hq + hkv) * dh].float() * 4.0).to(w.dtype)
+    probes = inputs.make_probes(wl, 2, seed=5)
+    parts = ref.curvature_parts(inputs.to_f64(x), inputs.to_f64(w), oracle_problem(wl), probes.numpy(), wl.dtype)
+    want = ref.curvature_forms(parts, 0.0)
+    got = jab.curvature(jab.problem_of(wl), x.cuda(), w.cuda(), probes.cuda(), 0.0).cpu().numpy()
+    err = np.abs(got - want) / np.maximum(np.abs(want), 0.1 * np.abs(want[:, 3:4]))
+    assert err.max() < 3e-2, err
