@@ -186,6 +186,28 @@ FwdWs carve_fwd(const jab_problem &p, void *ws, size_t *bytes, int n_sets, int n
     return w;
 }
 
+// The reduction's counters (one int per set of partials, at most 7^3), set to 0 by the call's first
+// quantizer launch: they lie in the slack rows of the first projection, which the attention reads only
+// as keys that the mask removes (32 rows of at least 64 bytes)
+static_assert(QK_SLACK_ROWS * 2 * 16 * 2 >= 7 * 7 * 7 * (int)sizeof(int), "counters in the slack rows");
+int *tickets(const jab_problem &p, const FwdWs &w) {
+    const Dims D = dims_of(p);
+    return reinterpret_cast<int *>(static_cast<char *>(w.proj[0].qk) +
+                                   (size_t)(D.M * (D.Hq + D.Hkv) * D.dh) * esize(p.dtype));
+}
+
+// jab_loss_fwd's out, and behind it (set 1) the KL term's
+jab::ReduceOut loss_out(const jab_problem &p, double *out) {
+    const Dims D = dims_of(p);
+    jab::ReduceOut r;
+    r.out = out; r.out_stride = 3 + D.B;
+    r.stats = 1;
+    r.inv[0] = 1.0 / ((double)D.M * (double)(D.Hq * D.dh));
+    r.inv[1] = 1.0 / (double)D.B;
+    r.per_seq = out + 3; r.seq_stride = 3 + D.B;
+    return r;
+}
+
 // Curvature: the probe as a projection operand, the projection at the float point and its tangent,
 // the tangent sums per (pass, sequence, head, 32-query block) and their total
 struct CurvWs {
@@ -606,7 +628,8 @@ jab_status jab_loss_fwd(const jab_problem *p, const void *x, const void *w, cons
     hipStream_t st = static_cast<hipStream_t>(stream);
     const jab::QuantShape sh = quant_shape(*p, q->bits);
     JAB_RUN(JAB_KT_QUANT, st, "quantize",
-            jab::launch_quantize(sh, p->dtype, w, q->scale, q->zero, nullptr, nullptr, W.w_op, nullptr, st));
+            jab::launch_quantize(sh, p->dtype, w, q->scale, q->zero, nullptr, nullptr, W.w_op, nullptr, st,
+                                 tickets(*p, W), 2));
     if ((s = run_project_split(*p, x, W.w_op, W.proj[0], st))) return s;
     jab::AttnArgs a = attn_args(*p, W.proj[0], W.proj[0], W.proj[0]);
     a.mode = jab::ATT_LOSS;
@@ -614,10 +637,8 @@ jab_status jab_loss_fwd(const jab_problem *p, const void *x, const void *w, cons
     a.partials[0] = W.partials;
     JAB_RUN(JAB_KT_ATTN, st, "attention", jab::launch_attn_fwd(p->dtype, a, st));
     JAB_RUN(JAB_KT_REDUCE, st, "reduce",
-            jab::launch_reduce_seq(W.partials, 1, p->batch, per_seq_waves(*p), W.seq_sums, st));
-    const double inv_n = 1.0 / ((double)D.M * (double)(D.Hq * D.dh));
-    JAB_RUN(JAB_KT_REDUCE, st, "reduce",
-            jab::launch_reduce_final(W.seq_sums, 1, p->batch, inv_n, out, 0, 1, 1, st));
+            jab::launch_reduce(W.partials, 1, p->batch, per_seq_waves(*p), W.seq_sums, tickets(*p, W),
+                               loss_out(*p, out), st));
     return JAB_OK;
 }
 
@@ -670,7 +691,8 @@ jab_status jab_loss_fwd_kl(const jab_problem *p, const void *x, const void *w, c
     hipStream_t st = static_cast<hipStream_t>(stream);
     const jab::QuantShape sh = quant_shape(*p, q->bits);
     JAB_RUN(JAB_KT_QUANT, st, "quantize",
-            jab::launch_quantize(sh, p->dtype, w, q->scale, q->zero, nullptr, nullptr, W.w_op, nullptr, st));
+            jab::launch_quantize(sh, p->dtype, w, q->scale, q->zero, nullptr, nullptr, W.w_op, nullptr, st,
+                                 tickets(*p, W), 2));
     if ((s = run_project_split(*p, x, W.w_op, W.proj[0], st))) return s;
     jab::AttnArgs a = attn_args(*p, W.proj[0], W.proj[0], W.proj[0]);
     a.mode = jab::ATT_LOSS;
@@ -690,13 +712,7 @@ jab_status jab_loss_fwd_kl(const jab_problem *p, const void *x, const void *w, c
     k.partials = kl_partials;
     JAB_RUN(JAB_KT_KL, st, "KL attention-map term", jab::launch_attn_kl(p->dtype, k, st));
     JAB_RUN(JAB_KT_REDUCE, st, "reduce",
-            jab::launch_reduce_seq(W.partials, 2, p->batch, per_seq, W.seq_sums, st));
-    const double inv_n = 1.0 / ((double)D.M * (double)(D.Hq * D.dh));
-    JAB_RUN(JAB_KT_REDUCE, st, "reduce",
-            jab::launch_reduce_final(W.seq_sums, 1, p->batch, inv_n, out, 0, 1, 1, st));
-    JAB_RUN(JAB_KT_REDUCE, st, "reduce",
-            jab::launch_reduce_final(W.seq_sums + (size_t)D.B * 2, 1, p->batch, 1.0 / (double)D.B,
-                                     out + 3 + D.B, 0, 1, 1, st));
+            jab::launch_reduce(W.partials, 2, p->batch, per_seq, W.seq_sums, tickets(*p, W), loss_out(*p, out), st));
     return JAB_OK;
 }
 
@@ -974,7 +990,8 @@ jab_status jab_loss_sweep(const jab_problem *p, const void *x, const void *w, in
         const jab::QuantShape sh = quant_shape(*p, b3);
         const uint8_t *z = zero_by_bits ? zero_by_bits[i] : nullptr;
         JAB_RUN(JAB_KT_QUANT, st, "quantize",
-                jab::launch_quantize(sh, p->dtype, w, scale_by_bits[i], z, nullptr, nullptr, W.w_op, nullptr, st));
+                jab::launch_quantize(sh, p->dtype, w, scale_by_bits[i], z, nullptr, nullptr, W.w_op, nullptr, st,
+                                     i == 0 ? tickets(*p, W) : nullptr, n_triples));
         if ((s = run_project_split(*p, x, W.w_op, W.proj[i], st))) return s;
     }
     // 2. one score matrix per (b_Q, b_K), applied to the value tensors of up to two triples
@@ -1000,10 +1017,12 @@ jab_status jab_loss_sweep(const jab_problem *p, const void *x, const void *w, in
         }
     }
     // 3. deterministic reductions
+    jab::ReduceOut r;
+    std::memset(&r, 0, sizeof(r));
+    r.out = loss; r.out_stride = 1;
+    r.per_seq = loss_per_seq; r.seq_stride = D.B;
     JAB_RUN(JAB_KT_REDUCE, st, "reduce",
-            jab::launch_reduce_seq(W.partials, n_triples, p->batch, per_seq, W.seq_sums, st));
-    JAB_RUN(JAB_KT_REDUCE, st, "reduce",
-            jab::launch_reduce_sweep(W.seq_sums, n_triples, p->batch, loss, loss_per_seq, st));
+            jab::launch_reduce(W.partials, n_triples, p->batch, per_seq, W.seq_sums, tickets(*p, W), r, st));
     return JAB_OK;
 }
 
@@ -1040,7 +1059,8 @@ jab_status run_bwd(const jab_problem *p, const void *x, const void *w, const jab
     const jab::QuantShape sh = quant_shape(*p, q->bits);
     // forward: projection, attention storing the log-sum-exp and the backward seed (g, D), loss
     JAB_RUN(JAB_KT_QUANT, st, "quantize",
-            jab::launch_quantize(sh, p->dtype, w, q->scale, q->zero, nullptr, nullptr, W.f.w_op, nullptr, st));
+            jab::launch_quantize(sh, p->dtype, w, q->scale, q->zero, nullptr, nullptr, W.f.w_op, nullptr, st,
+                                 tickets(*p, W.f), 2));
     if ((s = run_project_split(*p, x, W.f.w_op, W.f.proj[0], st))) return s;
     jab::AttnArgs a = attn_args(*p, W.f.proj[0], W.f.proj[0], W.f.proj[0]);
     a.mode = jab::ATT_LOSS | jab::ATT_STORE_G | jab::ATT_STORE_LSE;
@@ -1064,14 +1084,9 @@ jab_status run_bwd(const jab_problem *p, const void *x, const void *w, const jab
         JAB_RUN(JAB_KT_KL, st, "KL attention-map term", jab::launch_attn_kl(p->dtype, k, st));
     }
     JAB_RUN(JAB_KT_REDUCE, st, "reduce",
-            jab::launch_reduce_seq(W.f.partials, kl ? 2 : 1, p->batch, per_seq, W.f.seq_sums, st));
+            jab::launch_reduce(W.f.partials, kl ? 2 : 1, p->batch, per_seq, W.f.seq_sums, tickets(*p, W.f),
+                               loss_out(*p, out), st));
     const double n_out = (double)D.M * (double)(D.Hq * D.dh);
-    JAB_RUN(JAB_KT_REDUCE, st, "reduce",
-            jab::launch_reduce_final(W.f.seq_sums, 1, p->batch, 1.0 / n_out, out, 0, 1, 1, st));
-    if (kl)
-        JAB_RUN(JAB_KT_REDUCE, st, "reduce",
-                jab::launch_reduce_final(W.f.seq_sums + (size_t)D.B * 2, 1, p->batch, 1.0 / (double)D.B,
-                                         out + 3 + D.B, 0, 1, 1, st));
     // backward through attention (recomputed from the log-sum-exp) into dY^T
     JAB_RUN(JAB_KT_MISC, st, "zero padding",
             jab::launch_zero_cols(p->dtype, W.dyt, (int)D.R, (int)Ms, (int)D.M, st));

@@ -20,8 +20,10 @@ hipError_t launch_quant_init(const QuantShape &sh, int dtype, const void *w, flo
                              uint8_t *zero, hipStream_t st);
 hipError_t launch_quantize(const QuantShape &sh, int dtype, const void *w, const float *scale,
                            const uint8_t *zero, uint8_t *codes, float *w_hat, void *w_op,
-                           double *werr_part, hipStream_t st);
-// scratch: werr_scratch_doubles(sh) doubles, the quantizer's per-block partials first
+                           double *werr_part, hipStream_t st, int *clear = nullptr, int n_clear = 0);
+// (clear: n_clear ints set to 0 by the way, for a later kernel of the stream to count in)
+// scratch: werr_scratch_doubles(sh) doubles, the quantizer's per-block partials first, written by
+// launch_quantize with werr_part = scratch
 size_t werr_scratch_doubles(const QuantShape &sh);
 hipError_t launch_werr_reduce(const QuantShape &sh, double *scratch, double *out, hipStream_t st);
 // The persistent GEMMs take their tiles from a per-(device, stream) queue of 4 KiB that the
@@ -170,16 +172,21 @@ hipError_t launch_curv_forms(const double *partials, int64_t n, double *parts, d
 // w_out = the int8 probe (+-1) in the storage dtype
 hipError_t launch_probe_to_dtype(int dtype, const int8_t *probe, int64_t n, void *w_out, hipStream_t st);
 
-// Deterministic reductions of the attention partials.
-//   partials [n_sets][B][per_seq][2] -> seq_sums [n_sets][B][2] -> per set: loss, per-seq.
-hipError_t launch_reduce_seq(const double *partials, int n_sets, int batch, int per_seq,
-                             double *seq_sums, hipStream_t st);
-// out layout per set s: out[s*stride + 0] = sse, +1 = sse * inv_n, +2 = sum a^2,
-// +3+b = sse of sequence b (when per_seq_out is nonzero).
-hipError_t launch_reduce_final(const double *seq_sums, int n_sets, int batch, double inv_n,
-                               double *out, int stride, int with_stats, int per_seq_out,
-                               hipStream_t st);
-// Sweep layout: loss[s] = sse of set s, loss_per_seq[s][b] (may be null).
+// Deterministic reduction of the attention partials [n_sets][B][per_seq][2], one launch: per set the
+// sums over its sequences, out[0] = first sum, with stats (at most two sets) out[1] = out[0] * inv[set]
+// and out[2] = second sum; per_seq[b] = first sum of sequence b (NULL to skip).  seq_sums: scratch
+// [n_sets][B][2]; tickets: n_sets ints that an earlier kernel of the stream has set to 0
+// (launch_quantize's clear).
+struct ReduceOut {
+    double *out;
+    int64_t out_stride;           // doubles between sets
+    int stats;
+    double inv[2];
+    double *per_seq;
+    int64_t seq_stride;
+};
+hipError_t launch_reduce(const double *partials, int n_sets, int batch, int per_seq, double *seq_sums, int *tickets,
+                         const ReduceOut &r, hipStream_t st);
 // sum of squares of a [R][d] fp32 matrix over the row ranges [r[u], r[u+1]), u < n_units (<= 3),
 // in a fixed order: part holds unit_sumsq_part_bytes(n_units), out[u] the sums (fp64)
 struct UnitRows {
@@ -220,7 +227,4 @@ hipError_t launch_rope_rows(int dtype, const float *src, int64_t lds, void *dst,
                             int heads, int dh, const float2 *tab, hipStream_t st);
 hipError_t launch_rope_cols(int dtype, void *yt, int64_t ldt, int64_t ncols, int T, int heads, int dh,
                             const float2 *tab, bool inverse, hipStream_t st);
-hipError_t launch_reduce_sweep(const double *seq_sums, int n_sets, int batch, double *loss,
-                               double *loss_per_seq, hipStream_t st);
-
 }  // namespace jab

@@ -206,7 +206,8 @@ __global__ __launch_bounds__(256) void quantize_kernel(QuantShape sh, const void
                                                        uint8_t *__restrict__ codes,
                                                        float *__restrict__ w_hat,
                                                        void *__restrict__ w_op,
-                                                       double *__restrict__ werr_part) {
+                                                       double *__restrict__ werr_part,
+                                                       int *__restrict__ clear, int n_clear) {
     const int64_t nchunks = (int64_t)sh.rows * sh.cols / 8;
     const int64_t c0 = (int64_t)blockIdx.x * (256 * QCPT) + threadIdx.x;
     double err[3] = {0, 0, 0}, nrm[3] = {0, 0, 0};
@@ -219,6 +220,8 @@ __global__ __launch_bounds__(256) void quantize_kernel(QuantShape sh, const void
         if (c0 + i * 256 < nchunks)
             quant_chunk<DT>(sh, (c0 + i * 256) * 8, v[i], scale, zero, codes, w_hat, w_op, werr_part != nullptr, err,
                             nrm);
+    if (clear && blockIdx.x == 0)
+        for (int i = threadIdx.x; i < n_clear; i += 256) clear[i] = 0;
     if (!werr_part)
         return;
     // block reduction in a fixed order: wave sums, then the waves in order
@@ -238,45 +241,52 @@ __global__ __launch_bounds__(256) void quantize_kernel(QuantShape sh, const void
     }
 }
 
-// Sum of the per-block [6] partials in a fixed order, in two stages: workgroup g of
-// kWerrGroups sums the blocks g L .. g L + L - 1 (thread t every 256th from t, then the waves
-// in order) into stage[g][6]; one wavefront then sums the groups (lane l every 64th from l).
+// Sum of the per-block [6] partials in a fixed order, in two stages: workgroup g of at most kWerrGroups - 1
+// sums the blocks g L .. g L + L - 1 (thread t every 256th from t, then the waves
+// in order) into stage[g][6]; one workgroup then sums the groups (thread t group t).
 constexpr int kWerrGroups = 256;
 
-__global__ __launch_bounds__(256) void werr_stage1_kernel(const double *__restrict__ part, int nblocks, int per,
-                                                         double *__restrict__ stage) {
+// Workgroup g sums its share of the quantizer's partials; the workgroup that finishes last sums all
+// workgroups' sums (whichever it is: the order is fixed).  The sums go past the XCDs' caches and have
+// arrived before the count is raised.  One launch instead of two of 5 us.
+__global__ __launch_bounds__(256) void werr_reduce_kernel(const double *__restrict__ part, int nblocks, int per,
+                                                          double *__restrict__ stage, int *__restrict__ ticket,
+                                                          double *__restrict__ out) {
     const int g = blockIdx.x, lane = lane_id(), wave = threadIdx.x >> 6;
+    __shared__ double red[4][6];
+    __shared__ int last;
+    auto block_sum = [&](const double (&acc)[6], auto put) {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            const double t = wave_sum_f64(acc[k]);
+            if (lane == 0) red[wave][k] = t;
+        }
+        __syncthreads();
+        if (threadIdx.x < 6) {
+            double t = 0;
+            for (int i = 0; i < 4; ++i) t += red[i][threadIdx.x];
+            put(t);
+        }
+    };
     const int b0 = g * per, b1 = min(nblocks, b0 + per);
     double acc[6] = {0, 0, 0, 0, 0, 0};
     for (int i = b0 + (int)threadIdx.x; i < b1; i += 256)
 #pragma unroll
         for (int k = 0; k < 6; ++k) acc[k] += part[(int64_t)i * 6 + k];
-    __shared__ double red[4][6];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-        const double t = wave_sum_f64(acc[k]);
-        if (lane == 0) red[wave][k] = t;
-    }
+    block_sum(acc, [&](double t) {
+        __hip_atomic_store(stage + g * 6 + threadIdx.x, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    });
     __syncthreads();
-    if (threadIdx.x < 6) {
-        double t = 0;
-        for (int i = 0; i < 4; ++i) t += red[i][threadIdx.x];
-        stage[g * 6 + threadIdx.x] = t;
-    }
-}
-
-__global__ __launch_bounds__(64) void werr_reduce_kernel(const double *__restrict__ stage, int ngroups,
-                                                         double *__restrict__ out) {
-    const int lane = lane_id();
-    double acc[6] = {0, 0, 0, 0, 0, 0};
-    for (int i = lane; i < ngroups; i += 64)
+    if (threadIdx.x == 0)
+        last = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+    __syncthreads();
+    if (!last) return;
+    const bool mine = threadIdx.x < gridDim.x;          // at most 256 workgroups
 #pragma unroll
-        for (int k = 0; k < 6; ++k) acc[k] += stage[i * 6 + k];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-        const double t = wave_sum_f64(acc[k]);
-        if (lane == 0) out[k] = t;
-    }
+    for (int k = 0; k < 6; ++k)
+        acc[k] = mine ? __hip_atomic_load(stage + threadIdx.x * 6 + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
+    block_sum(acc, [&](double t) { out[threadIdx.x] = t; });
 }
 
 }  // namespace
@@ -293,6 +303,11 @@ int quant_blocks(const QuantShape &sh) {
 
 size_t werr_scratch_doubles(const QuantShape &sh) { return (size_t)(quant_blocks(sh) + kWerrGroups) * 6; }
 
+// the reduction's workgroups leave kWerrGroups - 1 sums at most; the last slot holds their count
+static int *werr_ticket(const QuantShape &sh, double *scratch) {
+    return reinterpret_cast<int *>(scratch + (size_t)(quant_blocks(sh) + kWerrGroups - 1) * 6);
+}
+
 hipError_t launch_quant_init(const QuantShape &sh, int dtype, const void *w, float *scale,
                              uint8_t *zero, hipStream_t st) {
     const dim3 grid(blocks_for(sh)), block(256);
@@ -306,22 +321,26 @@ hipError_t launch_quant_init(const QuantShape &sh, int dtype, const void *w, flo
 
 hipError_t launch_quantize(const QuantShape &sh, int dtype, const void *w, const float *scale,
                            const uint8_t *zero, uint8_t *codes, float *w_hat, void *w_op,
-                           double *werr_part, hipStream_t st) {
+                           double *werr_part, hipStream_t st, int *clear, int n_clear) {
     const dim3 grid(quant_blocks(sh)), block(256);
+    if (werr_part) {                                   // launch_werr_reduce's count
+        clear = werr_ticket(sh, werr_part);
+        n_clear = 1;
+    }
     switch (dtype) {
-    case F32: quantize_kernel<F32><<<grid, block, 0, st>>>(sh, w, scale, zero, codes, w_hat, w_op, werr_part); break;
-    case F16: quantize_kernel<F16><<<grid, block, 0, st>>>(sh, w, scale, zero, codes, w_hat, w_op, werr_part); break;
-    default: quantize_kernel<BF16><<<grid, block, 0, st>>>(sh, w, scale, zero, codes, w_hat, w_op, werr_part); break;
+    case F32: quantize_kernel<F32><<<grid, block, 0, st>>>(sh, w, scale, zero, codes, w_hat, w_op, werr_part, clear, n_clear); break;
+    case F16: quantize_kernel<F16><<<grid, block, 0, st>>>(sh, w, scale, zero, codes, w_hat, w_op, werr_part, clear, n_clear); break;
+    default: quantize_kernel<BF16><<<grid, block, 0, st>>>(sh, w, scale, zero, codes, w_hat, w_op, werr_part, clear, n_clear); break;
     }
     return hipGetLastError();
 }
 
 hipError_t launch_werr_reduce(const QuantShape &sh, double *scratch, double *out, hipStream_t st) {
     const int nblocks = quant_blocks(sh);
-    const int per = (nblocks + kWerrGroups - 1) / kWerrGroups;
+    const int per = (nblocks + kWerrGroups - 2) / (kWerrGroups - 1);
     double *stage = scratch + (size_t)nblocks * 6;
-    werr_stage1_kernel<<<kWerrGroups, 256, 0, st>>>(scratch, nblocks, per, stage);
-    werr_reduce_kernel<<<1, 64, 0, st>>>(stage, kWerrGroups, out);
+    werr_reduce_kernel<<<(nblocks + per - 1) / per, 256, 0, st>>>(scratch, nblocks, per, stage, werr_ticket(sh, scratch),
+                                                                 out);
     return hipGetLastError();
 }
 

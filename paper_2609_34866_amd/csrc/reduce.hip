@@ -7,83 +7,84 @@
 //
 // Each attention wavefront leaves one (sse, sum a^2) pair in fp64.  One wavefront
 // per (set, sequence) sums its pairs with a lane-strided loop and a butterfly in a
-// fixed order, then one wavefront per set sums the sequences.  No atomics, so the
-// result is bitwise reproducible.
+// fixed order; the wavefront of a set that finishes last sums the set's sequences,
+// whichever it is, from what all of them stored, in a fixed order.  The only atomic
+// is that count of finished wavefronts, so the result is bitwise reproducible.
 #include "device_common.h"
 #include "kernels.h"
 
 namespace jab {
 namespace {
 
-__global__ __launch_bounds__(64) void reduce_seq_kernel(const double *__restrict__ part, int batch,
-                                                        int per_seq, double *__restrict__ seq_sums) {
-    const int b = blockIdx.x, set = blockIdx.y, lane = lane_id();
-    const double *p = part + ((int64_t)set * batch + b) * per_seq * 2;
-    double s0 = 0, s1 = 0;
-    for (int i = lane; i < per_seq; i += 64) {
-        s0 += p[2 * i];
-        s1 += p[2 * i + 1];
-    }
-    s0 = wave_sum_f64(s0);
-    s1 = wave_sum_f64(s1);
-    if (lane == 0) {
-        seq_sums[((int64_t)set * batch + b) * 2] = s0;
-        seq_sums[((int64_t)set * batch + b) * 2 + 1] = s1;
-    }
+// What the sequences of a set leave for its last wavefront goes past the XCDs' caches (agent scope)
+// and has arrived before the count is raised: the wait is on the wavefront's own stores.
+__device__ inline void store_agent(double *p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline double load_agent(const double *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__global__ __launch_bounds__(64) void reduce_final_kernel(const double *__restrict__ seq_sums, int batch,
-                                                          double inv_n, double *__restrict__ out,
-                                                          int stride, int with_stats, int per_seq_out) {
-    const int set = blockIdx.x, lane = lane_id();
-    const double *p = seq_sums + (int64_t)set * batch * 2;
+// Bound by latency: at 16 x 2048 tokens of 32 heads a wavefront sums 2048 pairs, eight loads in flight.
+// One launch instead of two or three (the smallest kernel takes 5 us of a call): 16 + 5 us before.
+__global__ __launch_bounds__(64) void reduce_kernel(const double *__restrict__ part, int batch, int per_seq,
+                                                    double *__restrict__ seq_sums, int *__restrict__ tickets,
+                                                    ReduceOut r) {
+    const int b = blockIdx.x, set = blockIdx.y, lane = lane_id();
+    const double2 *p = reinterpret_cast<const double2 *>(part) + ((int64_t)set * batch + b) * per_seq;
     double s0 = 0, s1 = 0;
-    for (int i = lane; i < batch; i += 64) {
-        s0 += p[2 * i];
-        s1 += p[2 * i + 1];
+    int i = lane;
+    for (; i + 7 * 64 < per_seq; i += 8 * 64) {
+        double2 v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = p[i + 64 * k];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            s0 += v[k].x;
+            s1 += v[k].y;
+        }
+    }
+    for (; i < per_seq; i += 64) {
+        const double2 v = p[i];
+        s0 += v.x;
+        s1 += v.y;
     }
     s0 = wave_sum_f64(s0);
     s1 = wave_sum_f64(s1);
-    double *o = out + (int64_t)set * stride;
+    double *q = seq_sums + (int64_t)set * batch * 2;
+    int last = 0;
+    if (lane == 0) {
+        store_agent(q + 2 * b, s0);
+        store_agent(q + 2 * b + 1, s1);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        last = __hip_atomic_fetch_add(tickets + set, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == batch - 1;
+    }
+    if (!__builtin_amdgcn_readfirstlane(last)) return;
+    asm volatile("" ::: "memory");
+    double *o = r.out + set * r.out_stride, *ps = r.per_seq ? r.per_seq + set * r.seq_stride : nullptr;
+    s0 = s1 = 0;
+    for (int k = lane; k < batch; k += 64) {
+        const double x = load_agent(q + 2 * k), y = load_agent(q + 2 * k + 1);
+        s0 += x;
+        s1 += y;
+        if (ps) ps[k] = x;
+    }
+    s0 = wave_sum_f64(s0);
+    s1 = wave_sum_f64(s1);
     if (lane == 0) {
         o[0] = s0;
-        if (with_stats) {
-            o[1] = s0 * inv_n;
+        if (r.stats) {
+            o[1] = s0 * r.inv[set];
             o[2] = s1;
         }
     }
-    if (per_seq_out) {
-        const int base = with_stats ? 3 : 1;
-        for (int i = lane; i < batch; i += 64) o[base + i] = p[2 * i];
-    }
-}
-
-__global__ __launch_bounds__(64) void reduce_sweep_kernel(const double *__restrict__ seq_sums, int batch,
-                                                          double *__restrict__ loss,
-                                                          double *__restrict__ loss_per_seq) {
-    const int set = blockIdx.x, lane = lane_id();
-    const double *p = seq_sums + (int64_t)set * batch * 2;
-    double s0 = 0;
-    for (int i = lane; i < batch; i += 64) s0 += p[2 * i];
-    s0 = wave_sum_f64(s0);
-    if (lane == 0) loss[set] = s0;
-    if (loss_per_seq)
-        for (int i = lane; i < batch; i += 64) loss_per_seq[(int64_t)set * batch + i] = p[2 * i];
 }
 
 }  // namespace
 
-hipError_t launch_reduce_seq(const double *partials, int n_sets, int batch, int per_seq,
-                             double *seq_sums, hipStream_t st) {
-    reduce_seq_kernel<<<dim3(batch, n_sets), dim3(64), 0, st>>>(partials, batch, per_seq, seq_sums);
-    return hipGetLastError();
-}
-
-hipError_t launch_reduce_final(const double *seq_sums, int n_sets, int batch, double inv_n,
-                               double *out, int stride, int with_stats, int per_seq_out,
-                               hipStream_t st) {
-    reduce_final_kernel<<<dim3(n_sets), dim3(64), 0, st>>>(seq_sums, batch, inv_n, out, stride,
-                                                           with_stats, per_seq_out);
+hipError_t launch_reduce(const double *partials, int n_sets, int batch, int per_seq, double *seq_sums, int *tickets,
+                         const ReduceOut &r, hipStream_t st) {
+    reduce_kernel<<<dim3(batch, n_sets), dim3(64), 0, st>>>(partials, batch, per_seq, seq_sums, tickets, r);
     return hipGetLastError();
 }
 
@@ -129,12 +130,6 @@ hipError_t launch_unit_sumsq(const float *a, int64_t d, const UnitRows &rows, in
     if (n_units < 1 || n_units > 3 || d % 4) return hipErrorInvalidValue;
     unit_sumsq_kernel<<<dim3(SUMSQ_BLOCKS, n_units), dim3(256), 0, st>>>(a, d, rows, part);
     unit_sumsq_final_kernel<<<dim3(n_units), dim3(64), 0, st>>>(part, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_reduce_sweep(const double *seq_sums, int n_sets, int batch, double *loss,
-                               double *loss_per_seq, hipStream_t st) {
-    reduce_sweep_kernel<<<dim3(n_sets), dim3(64), 0, st>>>(seq_sums, batch, loss, loss_per_seq);
     return hipGetLastError();
 }
 
