@@ -234,7 +234,8 @@ struct BwdWs {
     FwdWs f;
     float *lse2, *D;
     void *g, *dyt, *xt, *vrow;
-    float *dw2;                   // second half of a split weight-gradient product
+    float *dw2;                   // the parts of a split weight-gradient product after the first
+    int parts;
     void *ds;                     // dS of the attention backward for its dQ pass (null: recomputed)
 };
 
@@ -261,7 +262,9 @@ BwdWs carve_bwd(const jab_problem &p, void *ws, size_t *bytes) {
     w.dyt = c.take((size_t)(D.R * Ms) * es);
     w.xt = c.take((size_t)(D.d * Ms) * es);
     w.vrow = c.take((size_t)(D.M * D.Hkv * D.dh) * es);
-    w.dw2 = static_cast<float *>(c.take((size_t)(D.R * D.d) * sizeof(float)));
+    const int parts = jab::gemm_f32_parts(p.dtype, (int)D.R, (int)D.d, (int)jab::transpose_ld(D.M));
+    w.dw2 = parts > 1 ? static_cast<float *>(c.take((size_t)(parts - 1) * (size_t)(D.R * D.d) * sizeof(float))) : nullptr;
+    w.parts = parts;
     const size_t dsb = bwd_ds_bytes(p);
     w.ds = dsb ? c.take(dsb) : nullptr;
     *bytes = fwd_bytes + c.off;
@@ -417,8 +420,7 @@ jab_status run_project_split(const jab_problem &p, const void *x, const void *w_
     }
     float *y32 = reinterpret_cast<float *>(tail + rope_tab_bytes(p));
     JAB_RUN(JAB_KT_GEMM, st, "projection GEMM (Q, K), fp32",
-            jab::launch_gemm_nt_f32out(p.dtype, x, w_operand, y32, (int)D.M, nqk, d, d, d, nqk, 1.f, st, nullptr,
-                                       nullptr));
+            jab::launch_gemm_nt_f32out(p.dtype, x, w_operand, y32, (int)D.M, nqk, d, d, d, nqk, 1.f, st));
     JAB_RUN(JAB_KT_MISC, st, "rotary embedding",
             jab::launch_rope_rows(p.dtype, y32, nqk, pr.qk, nqk, D.M, p.seq_len, heads, p.head_dim, tab, st));
     JAB_RUN(JAB_KT_GEMM_VT, st, "projection GEMM (V transposed)",
@@ -1134,14 +1136,13 @@ jab_status run_bwd(const jab_problem *p, const void *x, const void *w, const jab
     }
     if (transpose_x)   // X^T stays in the workspace: a caller looping over one X transposes it once
         JAB_RUN(JAB_KT_MISC, st, "transpose", jab::launch_transpose(p->dtype, x, W.xt, (int)D.M, (int)D.d, Ms, st));
-    int ksplit = 1;
     JAB_RUN(JAB_KT_DW_GEMM, st, "weight-gradient GEMM",
             jab::launch_gemm_nt_f32out(p->dtype, W.dyt, W.xt, dw, (int)D.R, (int)D.d, (int)Mp, (int)Ms,
-                                       (int)Ms, (int)D.d, (float)(2.0 / n_out), st, W.dw2, &ksplit));
-    // LSQ scale gradient (and the sum of the two halves of a split product)
+                                       (int)Ms, (int)D.d, (float)(2.0 / n_out), st, W.dw2));
+    // LSQ scale gradient (and the sum of the parts of a split product)
     const float gamma[3] = {lsq_gscale[0], lsq_gscale[1], lsq_gscale[2]};
     JAB_RUN(JAB_KT_MISC, st, "scale gradient",
-            jab::launch_lsq_scale_grad(sh, p->dtype, w, q->scale, q->zero, dw, ksplit == 2 ? W.dw2 : nullptr,
+            jab::launch_lsq_scale_grad(sh, p->dtype, w, q->scale, q->zero, dw, W.dw2, W.parts,
                                        1.f / ba.grad_scale, gamma, dscale, st));
     return JAB_OK;
 }

@@ -510,7 +510,7 @@ template <int DT>
 __global__ __launch_bounds__(256) void lsq_kernel(QuantShape sh, const void *__restrict__ w,
                                                   const float *__restrict__ scale,
                                                   const uint8_t *__restrict__ zero,
-                                                  float *__restrict__ dw, const float *__restrict__ dw2,
+                                                  float *__restrict__ dw, const float *__restrict__ dw2, int parts,
                                                   float qk_unscale, float g0, float g1, float g2,
                                                   float *__restrict__ ds) {
     typedef typename Mma<DT>::elem elem;
@@ -529,8 +529,8 @@ __global__ __launch_bounds__(256) void lsq_kernel(QuantShape sh, const void *__r
         f32x4 *dp = reinterpret_cast<f32x4 *>(dw + e);
         d0 = dp[0];
         d1 = dp[1];
-        if (dw2 != nullptr) {                           // the second half of a split product
-            const f32x4 *dq = reinterpret_cast<const f32x4 *>(dw2 + e);
+        for (int p = 1; p < parts; ++p) {               // the other parts of a split product
+            const f32x4 *dq = reinterpret_cast<const f32x4 *>(dw2 + (int64_t)(p - 1) * sh.rows * sh.cols + e);
             d0 += dq[0];
             d1 += dq[1];
         }
@@ -541,7 +541,7 @@ __global__ __launch_bounds__(256) void lsq_kernel(QuantShape sh, const void *__r
             d0 *= qk_unscale;
             d1 *= qk_unscale;
         }
-        if (dw2 != nullptr || rescale) {
+        if (parts > 1 || rescale) {
             dp[0] = d0;
             dp[1] = d1;
         }
@@ -663,14 +663,14 @@ hipError_t launch_zero_cols(int dtype, void *p, int rows, int ld, int c0, hipStr
 }
 
 hipError_t launch_lsq_scale_grad(const QuantShape &sh, int dtype, const void *w, const float *scale,
-                                 const uint8_t *zero, float *dw, const float *dw2, float qk_unscale,
+                                 const uint8_t *zero, float *dw, const float *dw2, int parts, float qk_unscale,
                                  const float gamma[3], float *ds, hipStream_t st) {
     const int64_t nchunks = (int64_t)sh.rows * sh.cols / 8;
     const dim3 grid((unsigned)((nchunks + 255) / 256)), block(256);
     switch (dtype) {
-    case F32: lsq_kernel<F32><<<grid, block, 0, st>>>(sh, w, scale, zero, dw, dw2, qk_unscale, gamma[0], gamma[1], gamma[2], ds); break;
-    case F16: lsq_kernel<F16><<<grid, block, 0, st>>>(sh, w, scale, zero, dw, dw2, qk_unscale, gamma[0], gamma[1], gamma[2], ds); break;
-    default: lsq_kernel<BF16><<<grid, block, 0, st>>>(sh, w, scale, zero, dw, dw2, qk_unscale, gamma[0], gamma[1], gamma[2], ds); break;
+    case F32: lsq_kernel<F32><<<grid, block, 0, st>>>(sh, w, scale, zero, dw, dw2, parts, qk_unscale, gamma[0], gamma[1], gamma[2], ds); break;
+    case F16: lsq_kernel<F16><<<grid, block, 0, st>>>(sh, w, scale, zero, dw, dw2, parts, qk_unscale, gamma[0], gamma[1], gamma[2], ds); break;
+    default: lsq_kernel<BF16><<<grid, block, 0, st>>>(sh, w, scale, zero, dw, dw2, parts, qk_unscale, gamma[0], gamma[1], gamma[2], ds); break;
     }
     return hipGetLastError();
 }

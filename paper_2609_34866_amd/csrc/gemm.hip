@@ -25,6 +25,7 @@
 //    so that neither part leaves the chip half empty: at 4 x 2048 tokens of d 4096 640 + 128 tiles took
 //    3 + 1 rounds of the 256 CUs, together 3 (372 -> 308 us); at 1 x 1999 160 + 32 tiles 189 -> 92 us,
 //    of which 54 us went into 2-byte stores of the ragged value tiles.
+#include <algorithm>
 #include <map>
 #include <mutex>
 #include <utility>
@@ -967,22 +968,43 @@ hipError_t launch_gemm_nt(int dtype, const void *A, const void *B, void *C, int 
     return persistent_fits<OUT_DT>(g) && persistent_pays(g) ? persistent<OUT_DT>(g, st) : small<OUT_DT>(g, st);
 }
 
-hipError_t launch_gemm_nt_f32out(int dtype, const void *A, const void *B, float *C, int M, int N, int K,
-                                 int lda, int ldb, int ldc, float alpha, hipStream_t st, float *C2,
-                                 int *ksplit_used) {
-    if (ksplit_used) *ksplit_used = 1;
-    if (M <= 0 || N <= 0 || K <= 0) return hipSuccess;
-    Gemm g{dtype, A, B, C, M, N, K, lda, ldb, ldc, alpha};
-    g.C2 = C2;
-    g.part_stride = (int64_t)M * ldc;
-    // K in two parts when they fill the CUs' rounds better than the tiles alone
-    if (C2 != nullptr && K % 128 == 0) {
+namespace {
+// An fp32 product whose K may be split: 256-tiles in one part or two where they pay, else small tiles
+// in as many parts as fill the CUs (two 128-tiles each, three 64-tiles for fp32), each part keeping 512
+// (fp32: 256) of K and the parts' sums at most 6 M values more to write and read.  Measured at 2304 x 768 x
+// 8192 fp16, 27 256-tiles: two parts of them 82 us, four parts of 108 128-tiles
+Gemm f32_plan(int dtype, int M, int N, int K, int ldc, bool split) {
+    Gemm g{dtype, nullptr, nullptr, nullptr, M, N, K, K, K, ldc};
+    char some = 0;
+    g.C = &some;                                      // tiles count where there is an output
+    if (split && K % 128 == 0) {
         const int t = tiles_of(g, 256);
         const double e1 = (double)t / (((t + CUS - 1) / CUS) * CUS);
         const double e2 = (double)(2 * t) / (((2 * t + CUS - 1) / CUS) * CUS);
         if (e2 > e1 + 0.05) g.ksplit = 2;
+        if (persistent_fits<OUT_F32>(g) && persistent_pays(g)) return g;
+        g.ksplit = 1;
     }
-    if (ksplit_used) *ksplit_used = g.ksplit;
+    if (!split || (persistent_fits<OUT_F32>(g) && persistent_pays(g))) return g;
+    const int64_t t = tiles_of(g, dtype == F32 ? 64 : 128), slots = dtype == F32 ? 3 * CUS : 2 * CUS;
+    const int64_t most = std::min<int64_t>({slots / t, K / (dtype == F32 ? 256 : 512), 1 + 6000000 / ((int64_t)M * N), 16});
+    g.ksplit = (int)std::max<int64_t>(1, most);
+    return g;
+}
+}  // namespace
+
+int gemm_f32_parts(int dtype, int M, int N, int K) {
+    return M > 0 && N > 0 && K > 0 ? f32_plan(dtype, M, N, K, N, true).ksplit : 1;
+}
+
+hipError_t launch_gemm_nt_f32out(int dtype, const void *A, const void *B, float *C, int M, int N, int K,
+                                 int lda, int ldb, int ldc, float alpha, hipStream_t st, float *C2) {
+    if (M <= 0 || N <= 0 || K <= 0) return hipSuccess;
+    Gemm g = f32_plan(dtype, M, N, K, ldc, C2 != nullptr);
+    g.A = A; g.B = B; g.C = C; g.lda = lda; g.ldb = ldb;
+    g.alpha = alpha;
+    g.C2 = C2;
+    g.part_stride = (int64_t)M * ldc;
     return persistent_fits<OUT_F32>(g) && persistent_pays(g) ? persistent<OUT_F32>(g, st) : small<OUT_F32>(g, st);
 }
 

@@ -52,12 +52,11 @@ bool gemm_rope_fuses(int dtype, int head_dim);
 bool project_is_one_launch(int dtype, int batch, int seq_T, int nqk, int nv, int K, int ldv);
 hipError_t launch_project(int dtype, const void *x, const void *w, void *qk, void *vt, int batch, int seq_T, int nqk,
                           int nv, int K, int ldv, int head_dim, const float4 *rope_tab_t, hipStream_t st);
-// Same product with an fp32 C = alpha * (A B^T).  With C2 (same shape) the product may be split
-// in two halves of K: *ksplit_used = 2 means C holds the first half's product and C2 the
-// second's (their sum is the result), 1 means C holds all of it.
+// Same product with an fp32 C = alpha * (A B^T).  With C2 the product goes in gemm_f32_parts parts of K:
+// C holds the first part's product and C2 [parts - 1][M][ldc] the others', to be added by the caller.
+int gemm_f32_parts(int dtype, int M, int N, int K);
 hipError_t launch_gemm_nt_f32out(int dtype, const void *A, const void *B, float *C, int M, int N, int K,
-                                 int lda, int ldb, int ldc, float alpha, hipStream_t st, float *C2 = nullptr,
-                                 int *ksplit_used = nullptr);
+                                 int lda, int ldb, int ldc, float alpha, hipStream_t st, float *C2 = nullptr);
 
 // ---- backward
 // V [B*T][ldv] in natural token order from transposed values [rows][ldt]
@@ -101,10 +100,10 @@ hipError_t launch_transpose(int dtype, const void *in, void *out, int rows, int 
 // zero columns [c0, ld) of a rows x ld matrix of the storage dtype
 hipError_t launch_zero_cols(int dtype, void *p, int rows, int ld, int c0, hipStream_t st);
 // ds[r][j] = gamma_m * sum_{k in group j} dw[r][k] phi[r][k] (eq. lsq); rows with bits 0 get 0.
-// dw2 (nullable): a second partial of dw, added into dw first (dw = dw + dw2); then the rows of
-// W_Q and W_K are multiplied by qk_unscale (a power of two; 1 leaves them).
+// dw2: parts - 1 more partials of dw (each the size of dw), added into dw first, in order; then the rows
+// of W_Q and W_K are multiplied by qk_unscale (a power of two; 1 leaves them).
 hipError_t launch_lsq_scale_grad(const QuantShape &sh, int dtype, const void *w, const float *scale,
-                                 const uint8_t *zero, float *dw, const float *dw2, float qk_unscale,
+                                 const uint8_t *zero, float *dw, const float *dw2, int parts, float qk_unscale,
                                  const float gamma[3], float *ds, hipStream_t st);
 
 // Causal GQA flash attention over one batch of sequences.
