@@ -63,38 +63,52 @@ __device__ inline int matrix_of_row(int r, int row_k, int row_v) {
 }
 
 // ------------------------------------------------------------------ quant-init
+// A thread takes QCPT chunks of 8 weights, 256 chunks apart, all loads before the arithmetic, with 32-bit
+// row and column indexing (rows * cols is at most 2^31 - 1).  Bound by HBM: 50 MB of a Mistral layer in
+// 17 us with one chunk per thread, 64-bit divisions and a scale per chunk, 13 us so (16 layers at once 239 / 148, 5.4 TB/s).
+constexpr int QCPT = 4;
+
 template <int DT>
 __global__ __launch_bounds__(256) void quant_init_kernel(QuantShape sh, const void *__restrict__ w,
                                                          float *__restrict__ scale,
                                                          uint8_t *__restrict__ zero) {
-    const int64_t chunk = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;   // 8 weights each
-    const int64_t nchunks = (int64_t)sh.rows * sh.cols / 8;
+    const uint32_t nchunks = (uint32_t)((int64_t)sh.rows * sh.cols / 8);
+    const uint32_t c0 = blockIdx.x * (256u * QCPT) + threadIdx.x;
     const int lpg = sh.group / 8;                     // lanes per group (power of two)
     // Threads past the end still take part in the shuffles (their lanes hold
     // neutral values); chunks never straddle groups since g is a multiple of 8.
-    const bool live = chunk < nchunks;
-    const int64_t e = live ? chunk * 8 : 0;
-    const int r = (int)(e / sh.cols);
-    const int col = (int)(e % sh.cols);
-    const int m = matrix_of_row(r, sh.row_k, sh.row_v);
-    const int bits = sh.bits[m];
-    float v[8];
-    load8<DT>(w, e, v);
-    float lo = 0.f, hi = 0.f, amax = 0.f;
+    float v[QCPT][8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        lo = fminf(lo, v[i]);
-        hi = fmaxf(hi, v[i]);
-        amax = fmaxf(amax, fabsf(v[i]));
+    for (int i = 0; i < QCPT; ++i) {
+        const uint32_t c = c0 + 256u * i;             // a group is past the end as a whole
+        load8<DT>(w, (int64_t)(c < nchunks ? c : 0) * 8, v[i]);
     }
-    for (int off = lpg / 2; off >= 1; off >>= 1) {
-        lo = fminf(lo, __shfl_xor(lo, off, 64));
-        hi = fmaxf(hi, __shfl_xor(hi, off, 64));
-        amax = fmaxf(amax, __shfl_xor(amax, off, 64));
+    // every lane of a group gets the group's range; lane i of the group keeps chunk i's, so the divisions
+    // run once for all chunks
+    const int gl = threadIdx.x & (lpg - 1);
+    float lo = 0.f, hi = 0.f;                         // symmetric: hi = max |w|
+#pragma unroll
+    for (int i = 0; i < QCPT; ++i) {
+        float l = 0.f, h = 0.f;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            l = fminf(l, v[i][k]);
+            h = fmaxf(h, sh.scheme == 0 ? v[i][k] : fabsf(v[i][k]));
+        }
+        for (int off = lpg / 2; off >= 1; off >>= 1) {
+            l = fminf(l, __shfl_xor(l, off, 64));
+            h = fmaxf(h, __shfl_xor(h, off, 64));
+        }
+        if (gl == i) {
+            lo = l;
+            hi = h;
+        }
     }
-    if (!live || (threadIdx.x & (lpg - 1)) != 0)
-        return;
-    const int64_t gi = (int64_t)r * (sh.cols / sh.group) + col / sh.group;
+    const uint32_t c = c0 + 256u * gl;                // a chunk of lane gl's group (the group's first is below it)
+    if (gl >= QCPT || c - gl >= nchunks) return;
+    const uint32_t gi = c / lpg;                      // groups are contiguous in memory
+    const int r = (int)(gi / (uint32_t)(sh.cols / sh.group));
+    const int bits = sh.bits[matrix_of_row(r, sh.row_k, sh.row_v)];
     float s = 1.f;
     int z = 0;
     if (bits != 0) {
@@ -108,7 +122,7 @@ __global__ __launch_bounds__(256) void quant_init_kernel(QuantShape sh, const vo
             z = (int)zf;
         } else {
             const float qmax = (float)((1 << (bits - 1)) - 1);
-            s = amax / qmax;
+            s = hi / qmax;
             if (s == 0.f) s = 1.f;
         }
     }
@@ -120,8 +134,9 @@ __global__ __launch_bounds__(256) void quant_init_kernel(QuantShape sh, const vo
 // Writes any of: codes (u8), w_hat (fp32), w_op (dtype; the projection operand),
 // and per-block partial sums of (w_hat - w)^2 and w^2 for each matrix.  A thread takes
 // QCPT chunks of 8 weights, 256 chunks apart (each of the block's QCPT passes reads 4 KiB
-// (bf16) contiguously); all of its loads are issued before the arithmetic.
-constexpr int QCPT = 4;
+// (bf16) contiguously); all of its loads are issued before the arithmetic.  Bound by HBM with codes, fp32
+// weights and weight errors (175 MB of a Mistral layer: 40 us with the errors selected per weight, 35.4 us
+// = 4.95 TB/s per chunk, a copy's rate).
 
 template <int DT>
 __device__ inline void quant_chunk(const QuantShape &sh, int64_t e, const float v[8], const float *__restrict__ scale,
@@ -190,11 +205,17 @@ __device__ inline void quant_chunk(const QuantShape &sh, int64_t e, const float 
     if (w_hat) store8<F32>(w_hat, e, wh);
     if (w_op) store8<DT>(w_op, e, wh);
     if (want_err) {
+        double e2 = 0, n2 = 0;                         // the chunk's sums, then into the matrix's
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const double d = (double)wh[i] - (double)v[i];
-            err[m] += d * d;
-            nrm[m] += (double)v[i] * (double)v[i];
+            const double x = (double)v[i], d = (double)wh[i] - x;
+            e2 = __builtin_fma(d, d, e2);
+            n2 = __builtin_fma(x, x, n2);
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            err[k] += k == m ? e2 : 0.0;
+            nrm[k] += k == m ? n2 : 0.0;
         }
     }
 }
@@ -291,11 +312,6 @@ __global__ __launch_bounds__(256) void werr_reduce_kernel(const double *__restri
 
 }  // namespace
 
-static inline int blocks_for(const QuantShape &sh) {
-    const int64_t nchunks = (int64_t)sh.rows * sh.cols / 8;
-    return (int)((nchunks + 255) / 256);
-}
-
 int quant_blocks(const QuantShape &sh) {
     const int64_t nchunks = (int64_t)sh.rows * sh.cols / 8;
     return (int)((nchunks + 256 * QCPT - 1) / (256 * QCPT));
@@ -310,7 +326,7 @@ static int *werr_ticket(const QuantShape &sh, double *scratch) {
 
 hipError_t launch_quant_init(const QuantShape &sh, int dtype, const void *w, float *scale,
                              uint8_t *zero, hipStream_t st) {
-    const dim3 grid(blocks_for(sh)), block(256);
+    const dim3 grid(quant_blocks(sh)), block(256);
     switch (dtype) {
     case F32: quant_init_kernel<F32><<<grid, block, 0, st>>>(sh, w, scale, zero); break;
     case F16: quant_init_kernel<F16><<<grid, block, 0, st>>>(sh, w, scale, zero); break;
