@@ -21,14 +21,18 @@
 //    access patterns are then free of bank conflicts (16 rows reading one logical chunk;
 //    4 consecutive rows reading 4 consecutive chunks), and every fragment of a wave is its
 //    lane's base address plus a constant offset.
-//  * dK/dV: a workgroup of NW waves owns 32 NW consecutive keys of one kv head, each wave
-//    32 keys with K and V in registers as B operands.  It walks the 32-query tiles of the
-//    group's query heads from the last tile down to its diagonal (workgroups of one kv head
-//    that start together read the same tiles at the same time, through one L2), and takes
-//    two key blocks, p and nkb - 1 - p, so every workgroup gets the same number of tiles.
-//    S = Q K^T and dP = G V^T come out with one key per lane; P and dS go from registers
-//    into the B operand of dV^T += G^T P and dK^T += Q^T dS.  With room for it in the
-//    workspace, the dK pass also stores each 32 x 32 dS tile as that operand (2 KiB).
+//  * dK/dV: a wave owns 32 keys of one kv head with K and V in registers as B operands and walks
+//    32-query tiles of the group's query heads from the last tile down to its diagonal.  S = Q K^T
+//    and dP = G V^T come out with one key per lane; P and dS go from registers into the B operand of
+//    dV^T += G^T P and dK^T += Q^T dS.  With room for it in the workspace, each 32 x 32 dS tile is
+//    also stored as that operand (2 KiB).  Two forms (run_bwd_dma_kl says where each is taken):
+//    - attn_bwd_dkdv_pipe_kernel: one 128-, 64- or 32-key block per workgroup, the waves of a key
+//      slice taking turns at its tiles, and in a wave the scores of one tile beside the softmax of the
+//      one before; for grids that do not fill the chip twice, and the KL term at head_dim 128.
+//    - attn_bwd_dkdv_dma_kernel: a workgroup takes the 128-key blocks p and nkb - 1 - p (the same
+//      number of tiles for all), tile after tile, two workgroups per CU.
+//    What bounds both once the chip is full: LDS reads (a wave reads 32 KiB of fragments for the 32
+//    matrix instructions of a tile at head_dim 128; 1.2 us for the four waves' tile in either form).
 //  * dQ from the stored dS: a wave owns 32 queries of one query head; the workgroup's waves
 //    share a kv head and walk its 32-key tiles, each wave's dS tiles riding the same LDS ring
 //    and read transposed into the B operand of dQ^T += K^T dS^T (5 products in all).
@@ -53,9 +57,7 @@ namespace {
 // group per 64 bytes and one rotation: 16 distinct slots as well.
 __host__ __device__ constexpr int quad_slot(int r, int c) { return (c >> 2) * 128 + 4 * r + ((c & 3) ^ ((r >> 2) & 3)); }
 
-// MODE (the dK/dV kernel): 0 both products, 1 dV alone, 2 dK alone.  With the KL term the
-// split pair (1 then 2) keeps two workgroups per CU where the kernel with both cannot.
-template <int DT, int DH, int NW, bool KL = false, int MODE = 0>
+template <int DT, int DH, int NW, bool KL = false>
 struct BwdTiles {
     static constexpr int NKC = DH / 16;           // k-steps of 16 over the head dimension
     static constexpr int NDB = DH / 32;           // 32-row blocks of a transposed result
@@ -66,8 +68,8 @@ struct BwdTiles {
     // dK/dV stage: Q tile | G tile (| teacher Q tile) | lse[32] | D[32] (| teacher lse[32] twice).
     // With the KL term the wave also keeps its keys' teacher K in registers: one wave per SIMD.
     static constexpr int NT_KV = KL ? 3 : 2;
-    static constexpr int WPC_KV = (KL && MODE == 0) ? 1 : (NW == 4 ? 2 : 1);   // workgroups per CU
-    static constexpr int NS_KV = (KL && MODE == 2) ? 3 : 4;                    // ring stages
+    static constexpr int WPC_KV = KL && DH == 128 ? 1 : 2;          // workgroups per CU
+    static constexpr int NS_KV = 4;                                 // ring stages
     static constexpr int KV_STAGE = NT_KV * TILE + (KL ? 512 : 256);
     static constexpr int KV_PW = NT_KV * TI / NW + (KL ? 2 : 1);   // DMA instructions per wave and tile
     // dQ stage: K tile | V tile (| teacher K tile)
@@ -131,18 +133,346 @@ __device__ inline int xcd_remap(int lin, int nwg) {
 }
 
 // ------------------------------------------------------------------ dK / dV
+// A workgroup's four waves are KW key slices of 32 keys times QW = 4 / KW query ways: the QW waves of
+// a slice take every QW-th 32-query tile and add their sums in LDS at the end (in the order of the
+// ways, so the result does not depend on timing).
+template <int DT, int DH, int KW, bool KL>
+struct DkdvCfg {
+    typedef BwdTiles<DT, DH, KW, KL> B;
+    static constexpr int QW = 4 / KW;
+    // a way's part of a stage: Q tile | G tile (| teacher Q tile) | lse[32] | D[32] (| teacher lse twice)
+    static constexpr int NT = KL ? 3 : 2;
+    static constexpr int SUB = NT * B::TILE + (KL ? 512 : 256);
+    static constexpr int STAGE = QW * SUB;
+    static constexpr int PW = NT * B::TI / KW + (KL ? 2 : 1);       // DMA instructions per wave and stage
+    static constexpr int WPC = DH == 64 && KW > 1 && !KL ? 2 : 1;   // workgroups per CU
+    static constexpr int NS = WPC * 4 * STAGE <= 160 * 1024 ? 4 : 3;                // ring stages
+    static constexpr int LDS = NS * STAGE;
+    static constexpr int ACC = 2 * B::NDB * 16 * 256;               // bytes of one wave's sums
+    static_assert(WPC * LDS <= 160 * 1024 && (QW - 1) * KW * ACC <= LDS, "LDS ring and the exchange of the sums");
+    static_assert(B::TI % KW == 0, "each tile splits evenly over a way's waves");
+    static_assert(NS >= 3 && (NS - 2) * PW < 64, "the counted waits");
+};
+
 // KL: the gradient of the KL attention-map term rides along (kl_scale (P - P_t) added to each dS
 // entry, P_t the teacher's map rebuilt from its projection and log-sum-exp); dS is then multiplied
 // by grad_scale (a power of two that keeps fp16 in range; the scale-gradient kernel divides it out
 // of the W_Q and W_K rows of the weight gradient).
-// DS: the dK pass stores dS (AttnBwdArgs::ds) for the dQ pass.
-template <int DT, int DH, int NW, bool KL, int MODE = 0, bool DS = false>
-__global__ __launch_bounds__(64 * NW, (BwdTiles<DT, DH, NW, KL, MODE>::WPC_KV)) void attn_bwd_dkdv_dma_kernel(
+// With room for it (AttnBwdArgs::ds) dS is stored for the dQ pass.
+//
+// The score products of tile u + 1 and the softmax of tile u are issued alternately: a wave's matrix
+// instructions run while its vector instructions do, so one wave per SIMD keeps both busy, and the 512
+// registers it may then use hold both tiles' scores beside the two outputs.
+template <int DT, int DH, int KW, bool KL>
+__global__ __launch_bounds__(256, (DkdvCfg<DT, DH, KW, KL>::WPC)) void attn_bwd_dkdv_pipe_kernel(
+    AttnBwdArgs a, float scale_log2, float inv_sqrt, int nkb, uint32_t inv_g) {
+    typedef DkdvCfg<DT, DH, KW, KL> C;
+    typedef typename C::B B;
+    typedef Mma<DT> MM;
+    typedef typename MM::operand opnd;
+    typedef uint16_t elem;
+    constexpr int BK = 32 * KW;                        // keys per block
+    constexpr int NS = C::NS, QW = C::QW, NKC = B::NKC, NDB = B::NDB, TI = B::TI;
+    extern __shared__ __align__(16) unsigned char smem[];
+
+    const int T = a.seq_len, Hq = a.n_heads, Hkv = a.n_kv_heads;
+    const int G = Hq / Hkv;
+    // one key block per workgroup, the longest first, so that the short ones fill what the long ones
+    // leave idle; one kv head's workgroups on one XCD where the counts allow it
+    const int heads = gridDim.x / nkb, per = heads & 7 ? heads : heads >> 3;
+    const int xcd = heads & 7 ? 0 : blockIdx.x & 7, idx = heads & 7 ? blockIdx.x : blockIdx.x >> 3;
+    const int kb = idx / per, head = xcd * per + idx % per;
+    const int kvh = head % Hkv, b = head / Hkv;
+    const int nq = (T - kb * BK + 31) / 32, n = G * nq;        // its tiles, QW per step
+    const int U = (n + QW - 1) / QW;
+
+    const int lane = threadIdx.x & 63, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int kw = wave % KW, qw = wave / KW;
+    const int64_t row0 = (int64_t)b * T;
+    const elem *Qs = static_cast<const elem *>(a.q) + row0 * a.ldq;
+    const elem *Gs = static_cast<const elem *>(a.g) + row0 * Hq * DH;
+    const elem *Qts = KL ? static_cast<const elem *>(a.qt) + row0 * a.ldq : nullptr;
+    const int64_t ld_base = (int64_t)b * Hq * T;       // lse2 / D of (b, h, t): ld_base + h T + t
+
+    // step u, this wave's way -> query head, first query (the group's heads for the last query tile,
+    // then the tile below, down to the block's diagonal; past the last tile the last one again, which
+    // is then not used)
+    auto tile_of = [&](int u, int &h, int &q0) -> bool {
+        const int v0 = QW * u + qw;
+        const int v = min(v0, n - 1);
+        const int vq = G == 1 ? v : (int)__umulhi((uint32_t)v, inv_g);     // v / G
+        h = kvh * G + (v - vq * G);
+        q0 = kb * BK + 32 * (nq - 1 - vq);
+        return v0 < n;
+    };
+
+    // ---- DMA: instruction i of a wave loads 1 KiB piece kw + KW i of its way's tiles (pieces
+    // [0, TI): Q, [TI, 2 TI): G, [2 TI, 3 TI): the teacher's Q), then lse and D (one 4-byte load per
+    // lane: lanes below 32 lse, the others D) and with the KL term the teacher's lse (every lane; lanes
+    // 32..63 repeat lanes 0..31).  A piece's row inside the tile depends on its parity alone and its
+    // first column is wave-uniform, so a lane forms one offset per tensor and parity.  Steps past the
+    // last load the last tile again: the waits below count the same loads in every step.
+    constexpr int NP = C::NT * TI / KW, NPAR = KW == 1 ? 2 : 1;
+    auto stage_ptr = [&](int s) { return smem + s * C::STAGE + qw * C::SUB; };
+    const float *ldp = (lane < 32 ? a.lse2 : a.D) + ld_base;
+    const int dcol = ((lane & 3) ^ ((lane >> 4) & 3)) * 8;             // quad_source at the lane
+    struct Loads { uint32_t q[NPAR], g[NPAR]; int l; const elem *Q, *G, *Qt; unsigned char *st; int h; };
+    auto plan = [&](int u, Loads &x) {
+        int h, q0;
+        tile_of(min(u, U - 1), h, q0);
+#pragma unroll
+        for (int p = 0; p < NPAR; ++p) {
+            const int q = min(q0 + 16 * (KW == 1 ? p : kw & 1) + (lane >> 2), T - 1);
+            x.q[p] = 2u * (uint32_t)(q * a.ldq + dcol);
+            x.g[p] = 2u * (uint32_t)(q * Hq * DH + dcol);
+        }
+        x.l = min(q0 + (lane & 31), T - 1);
+        x.Q = Qs + h * DH;
+        x.G = Gs + h * DH;
+        if constexpr (KL) x.Qt = Qts + h * DH;
+        x.st = stage_ptr(u % NS);
+        x.h = h;
+    };
+    auto issue_part = [&](const Loads &x, int i) {
+        if (i < NP) {
+            const int tix = (KW * i) / TI, idx = kw + (KW * i) % TI, par = KW == 1 ? i & 1 : 0;
+            const elem *base = (tix == 0 ? x.Q : tix == 1 ? x.G : x.Qt) + 32 * (idx >> 1);
+            lds_dma16_raw(base, tix == 1 ? x.g[par] : x.q[par], x.st + tix * B::TILE + idx * 1024);
+        } else if (i == NP) {
+            lds_dma4_raw(ldp + (int64_t)x.h * T + x.l, x.st + C::NT * B::TILE);
+        } else if (KL && i == NP + 1) {
+            lds_dma4_raw(a.lse_t + ld_base + (int64_t)x.h * T + x.l, x.st + C::NT * B::TILE + 256);
+        }
+    };
+    auto sync = [&] {
+        if constexpr (KW > 1) raw_barrier();
+        else asm volatile("" ::: "memory");            // a way of one wave reads its own loads only
+    };
+
+    const int kw0 = kb * BK + 32 * kw;                 // first key of this wave
+    const TileLanes tl(lane);
+    opnd kf[NKC], vf[NKC], ktf[KL ? NKC : 1];
+    f32x16 dkt[NDB], dvt[NDB];
+    auto load_keys = [&] {
+        const int kr = min(kw0 + (lane & 31), T - 1);
+        const elem *kp = static_cast<const elem *>(a.k) + (row0 + kr) * a.ldq + kvh * DH + half * 8;
+        const elem *vp = static_cast<const elem *>(a.v) + (row0 + kr) * a.ldv + kvh * DH + half * 8;
+#pragma unroll
+        for (int kc = 0; kc < NKC; ++kc) {
+            kf[kc] = __builtin_bit_cast(opnd, *reinterpret_cast<const u32x4 *>(kp + kc * 16));
+            vf[kc] = __builtin_bit_cast(opnd, *reinterpret_cast<const u32x4 *>(vp + kc * 16));
+        }
+        if constexpr (KL) {
+            const elem *ktp = static_cast<const elem *>(a.kt) + (row0 + kr) * a.ldq + kvh * DH + half * 8;
+#pragma unroll
+            for (int kc = 0; kc < NKC; ++kc)
+                ktf[kc] = __builtin_bit_cast(opnd, *reinterpret_cast<const u32x4 *>(ktp + kc * 16));
+        }
+#pragma unroll
+        for (int d = 0; d < NDB; ++d)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) { dkt[d][e] = 0.f; dvt[d][e] = 0.f; }
+    };
+    // dK^T, dV^T: lane -> key (a token column of dY^T), registers -> head-dimension rows
+    auto store_sums = [&] {
+        if constexpr (QW > 1) {                        // the ways' sums, exchanged through the (drained) ring
+            typedef __attribute__((address_space(3))) float lds_f32;
+            lds_f32 *ex = (lds_f32 *)smem;
+            constexpr int WF = C::ACC / 4;
+            wait_lgkm0();
+            wait_vmcnt<0>();
+            raw_barrier();
+            if (qw > 0) {
+                lds_f32 *o = ex + ((qw - 1) * KW + kw) * WF + lane;
+#pragma unroll
+                for (int d = 0; d < NDB; ++d)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        o[(d * 16 + e) * 64] = dkt[d][e];
+                        o[((NDB + d) * 16 + e) * 64] = dvt[d][e];
+                    }
+            }
+            __syncthreads();
+            if (qw > 0) return;
+#pragma unroll 1
+            for (int w = 1; w < QW; ++w) {
+                const lds_f32 *o = ex + ((w - 1) * KW + kw) * WF + lane;
+#pragma unroll
+                for (int d = 0; d < NDB; ++d)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        dkt[d][e] += o[(d * 16 + e) * 64];
+                        dvt[d][e] += o[((NDB + d) * 16 + e) * 64];
+                    }
+            }
+        }
+        const int key = kw0 + (lane & 31);
+        if (key >= T) return;
+        elem *dyt = static_cast<elem *>(a.dyt) + row0 + key;
+        const int koff = Hq * DH + kvh * DH, voff = (Hq + Hkv) * DH + kvh * DH;
+#pragma unroll
+        for (int d = 0; d < NDB; ++d)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int c = d * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
+                dyt[(int64_t)(koff + c) * a.ldt] = from_f32<DT>(dkt[d][e] * inv_sqrt);
+                dyt[(int64_t)(voff + c) * a.ldt] = from_f32<DT>(dvt[d][e]);
+            }
+    };
+
+    // The scores of a tile: S = Q K^T, dP = G V^T and the teacher's S_t = Q_t K_t^T; lane -> key,
+    // registers -> queries 8 (e / 4) + 4 half + e % 4
+    struct Scores { f32x16 s, dp, st; };
+    auto clear = [&](Scores &x) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) { x.s[e] = 0.f; x.dp[e] = 0.f; if constexpr (KL) x.st[e] = 0.f; }
+    };
+    struct Frags { opnd q, g, t; };
+    auto score_frags = [&](Frags &f, const lds_u8 *stq, int kc) {
+        f.q = row_frag<DT>(stq, tl, kc);
+        f.g = row_frag<DT>(stq + B::TILE, tl, kc);
+        if constexpr (KL) f.t = row_frag<DT>(stq + 2 * B::TILE, tl, kc);
+    };
+    auto score_step = [&](Scores &x, const Frags &f, int kc) {
+        x.s = MM::mma(f.q, kf[kc], x.s);
+        x.dp = MM::mma(f.g, vf[kc], x.dp);
+        if constexpr (KL) x.st = MM::mma(f.t, ktf[kc], x.st);
+    };
+
+    // step u: P and dS of tile u from its scores x, beside the scores y of tile u + 1; then the products
+    auto step = [&](int u, Scores &x, Scores &y) {
+        // this wave's part of tile u + 1 has landed (tiles issued after it may be pending), then every
+        // wave's part; every wave is also done reading tile u - 1, whose stage is refilled.  The dS
+        // stores in between only make a wait longer.
+        wait_lgkm0();
+        wait_vmcnt<(NS - 3) * C::PW>();
+        sync();
+        const lds_u8 *stq = (const lds_u8 *)stage_ptr(u % NS);
+        const lds_u8 *stn = (const lds_u8 *)stage_ptr((u + 1) % NS);
+        const lds_u8 *stg = stq + B::TILE;
+        Frags fr[NKC];
+        score_frags(fr[0], stn, 0);
+        score_frags(fr[1], stn, 1);
+        const __attribute__((address_space(3))) float *lsd =
+            (const __attribute__((address_space(3))) float *)(stq + C::NT * B::TILE);
+        f32x4 ls[4], dd[4], lt[4];
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4) {
+            const int r0 = 8 * e4 + 4 * half;
+            ls[e4] = *reinterpret_cast<const __attribute__((address_space(3))) f32x4 *>(lsd + r0);
+            dd[e4] = *reinterpret_cast<const __attribute__((address_space(3))) f32x4 *>(lsd + 32 + r0);
+            if constexpr (KL) lt[e4] = *reinterpret_cast<const __attribute__((address_space(3))) f32x4 *>(lsd + 64 + r0);
+        }
+        Loads ld;
+        plan(u + NS - 1, ld);
+        int h, q0;
+        const bool valid = tile_of(u, h, q0);
+        clear(y);
+        constexpr int EPK = 16 / NKC, IPK = (C::PW + NKC - 1) / NKC;   // softmax entries, loads per k-step
+#pragma unroll
+        for (int kc = 0; kc < NKC; ++kc) {
+            if (kc + 2 < NKC) score_frags(fr[kc + 2], stn, kc + 2);
+            score_step(y, fr[kc], kc);
+#pragma unroll
+            for (int i = kc * IPK; i < (kc + 1) * IPK; ++i) issue_part(ld, i);
+#pragma unroll
+            for (int i = 0; i < EPK; ++i) {
+                const int e = kc * EPK + i;
+                const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(x.s[e], scale_log2, -ls[e >> 2][e & 3]));
+                float ds = p * (x.dp[e] - dd[e >> 2][e & 3]);
+                if constexpr (KL) {
+                    const float pt = __builtin_amdgcn_exp2f(__builtin_fmaf(x.st[e], scale_log2, -lt[e >> 2][e & 3]));
+                    ds = (ds + a.kl_scale * (p - pt)) * a.grad_scale;
+                }
+                // kept here: the compiler would sink the whole softmax behind the branch below
+                float pk = p, dk = ds;
+                asm volatile("" : "+v"(pk), "+v"(dk));
+                x.s[e] = pk;
+                x.dp[e] = dk;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // the first operands of the products below
+        opnd tg[2], tq[2];
+#pragma unroll
+        for (int d = 0; d < 2; ++d) {
+            tg[d] = tr_frag<DT>(stg, tl, 0, d);
+            tq[d] = tr_frag<DT>(stq, tl, 0, d);
+        }
+        if (!valid || q0 + 31 < kw0 || kw0 >= T) return;   // no query of the tile sees these keys
+        // the diagonal and sequence-tail tiles (wave-uniform): entries above the diagonal or past the
+        // sequence are zero; the other tiles take no compare and no select
+        if (q0 < kw0 + 31 || q0 + 31 >= T) {
+            const int key = kw0 + (lane & 31);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int q = q0 + 8 * (e >> 2) + 4 * half + (e & 3);
+                const bool off = q < key || q >= T;
+                x.s[e] = off ? 0.f : x.s[e];
+                x.dp[e] = off ? 0.f : x.dp[e];
+            }
+        }
+        // dV^T += G^T P, dK^T += Q^T dS (k = the tile's 32 queries in two steps); the operand of each
+        // step is the dS tile that the dQ pass reads (2 KiB per tile: step ks, lane at ks KiB + 16
+        // lane).  The tile's address is wave-uniform (a buffer resource in scalar registers); the store
+        // is non-temporal (read once, by the dQ pass), so it does not push the Q and G tiles out of L2.
+        const opnd sb[2] = {acc_operand<DT>(x.dp, 0), acc_operand<DT>(x.dp, 1)};
+        if (a.ds) {
+            const int qt = q0 / 32, kt = kw0 / 32, nt = (T + 31) / 32;
+            const i32x4 rds = buffer_rsrc(static_cast<char *>(a.ds) +
+                                          (((int64_t)b * Hq + h) * (nt * (nt + 1) / 2) + qt * (qt + 1) / 2 + kt) * 2048);
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+                buffer_store16_nt(rds, lane * 16, ks * 1024, __builtin_bit_cast(i32x4, sb[ks]));
+        }
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            const opnd pb = acc_operand<DT>(x.s, ks);
+#pragma unroll
+            for (int d = 0; d < NDB; ++d) {
+                const bool have = ks == 0 && d < 2;
+                dvt[d] = MM::mma(have ? tg[d & 1] : tr_frag<DT>(stg, tl, ks, d), pb, dvt[d]);
+                dkt[d] = MM::mma(have ? tq[d & 1] : tr_frag<DT>(stq, tl, ks, d), sb[ks], dkt[d]);
+            }
+        }
+    };
+
+#pragma unroll
+    for (int t = 0; t < NS - 1; ++t) {
+        Loads ld;
+        plan(t, ld);
+#pragma unroll
+        for (int i = 0; i < C::PW; ++i) issue_part(ld, i);
+    }
+    load_keys();
+    wait_vmcnt<0>();                                   // the keys and the first tiles
+    sync();
+    Scores x, y;
+    clear(x);
+    const lds_u8 *st0 = (const lds_u8 *)stage_ptr(0);
+#pragma unroll
+    for (int kc = 0; kc < NKC; ++kc) {
+        Frags f;
+        score_frags(f, st0, kc);
+        score_step(x, f, kc);
+    }
+    int u = 0;
+    for (; u + 1 < U; u += 2) {
+        step(u, x, y);
+        step(u + 1, y, x);
+    }
+    if (u < U) step(u, x, y);
+    store_sums();
+    wait_vmcnt<0>();                                   // no load into LDS outlives the workgroup
+}
+
+// The same tile after tile, two key blocks per workgroup and two workgroups per CU, for grids that
+// fill the chip twice.
+template <int DT, int DH, int NW, bool KL, bool DS>
+__global__ __launch_bounds__(64 * NW, (BwdTiles<DT, DH, NW, KL>::WPC_KV)) void attn_bwd_dkdv_dma_kernel(
     AttnBwdArgs a, float scale_log2, float inv_sqrt, int nkb, int npair) {
-    typedef BwdTiles<DT, DH, NW, KL, MODE> C;
-    static_assert(MODE == 0 || MODE == 2 || !KL, "dV alone has no KL part");
-    static_assert(!DS || MODE != 1, "dS comes from the dK pass");
-    constexpr bool DO_DV = MODE != 2, DO_DK = MODE != 1;
+    typedef BwdTiles<DT, DH, NW, KL> C;
     typedef Mma<DT> MM;
     typedef typename MM::operand opnd;
     typedef uint16_t elem;
@@ -222,7 +552,7 @@ __global__ __launch_bounds__(64 * NW, (BwdTiles<DT, DH, NW, KL, MODE>::WPC_KV)) 
 #pragma unroll
         for (int kc = 0; kc < C::NKC; ++kc) {
             kf[kc] = __builtin_bit_cast(opnd, *reinterpret_cast<const u32x4 *>(kp + kc * 16));
-            if constexpr (DO_DK) vf[kc] = __builtin_bit_cast(opnd, *reinterpret_cast<const u32x4 *>(vp + kc * 16));
+            vf[kc] = __builtin_bit_cast(opnd, *reinterpret_cast<const u32x4 *>(vp + kc * 16));
         }
         if constexpr (KL) {
             const elem *ktp = static_cast<const elem *>(a.kt) + (row0 + kr) * a.ldq + kvh * DH + half * 8;
@@ -246,8 +576,8 @@ __global__ __launch_bounds__(64 * NW, (BwdTiles<DT, DH, NW, KL, MODE>::WPC_KV)) 
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 const int c = d * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
-                if constexpr (DO_DK) dyt[(int64_t)(koff + c) * a.ldt] = from_f32<DT>(dkt[d][e] * inv_sqrt);
-                if constexpr (DO_DV) dyt[(int64_t)(voff + c) * a.ldt] = from_f32<DT>(dvt[d][e]);
+                dyt[(int64_t)(koff + c) * a.ldt] = from_f32<DT>(dkt[d][e] * inv_sqrt);
+                dyt[(int64_t)(voff + c) * a.ldt] = from_f32<DT>(dvt[d][e]);
             }
     };
 
@@ -278,7 +608,7 @@ __global__ __launch_bounds__(64 * NW, (BwdTiles<DT, DH, NW, KL, MODE>::WPC_KV)) 
 #pragma unroll
             for (int kc = 0; kc < C::NKC; ++kc) {
                 s = MM::mma(row_frag<DT>(stq, tl, kc), kf[kc], s);
-                if constexpr (DO_DK) dp = MM::mma(row_frag<DT>(stg, tl, kc), vf[kc], dp);
+                dp = MM::mma(row_frag<DT>(stg, tl, kc), vf[kc], dp);
                 if constexpr (KL) st = MM::mma(row_frag<DT>(stq + 2 * C::TILE, tl, kc), ktf[kc], st);
             }
             const int key = kw + (lane & 31);
@@ -331,8 +661,8 @@ __global__ __launch_bounds__(64 * NW, (BwdTiles<DT, DH, NW, KL, MODE>::WPC_KV)) 
                 if constexpr (DS) buffer_store16_nt(rds, lane * 16, ks * 1024, __builtin_bit_cast(i32x4, sb));
 #pragma unroll
                 for (int d = 0; d < C::NDB; ++d) {
-                    if constexpr (DO_DV) dvt[d] = MM::mma(tr_frag<DT>(stg, tl, ks, d), pb, dvt[d]);
-                    if constexpr (DO_DK) dkt[d] = MM::mma(tr_frag<DT>(stq, tl, ks, d), sb, dkt[d]);
+                    dvt[d] = MM::mma(tr_frag<DT>(stg, tl, ks, d), pb, dvt[d]);
+                    dkt[d] = MM::mma(tr_frag<DT>(stq, tl, ks, d), sb, dkt[d]);
                 }
             }
         }
@@ -639,38 +969,59 @@ hipError_t run_bwd_dma_kl(const AttnBwdArgs &a, hipStream_t st) {
     hipError_t e = hipFuncSetAttribute((const void *)attn_bwd_dq_dma_kernel<DT, DH, NW, KL>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)q_lds);
     if (e != hipSuccess) return e;
-    const int nkb = (T + 32 * NW - 1) / (32 * NW);
-    const int npair = (nkb + 1) / 2;
-    const dim3 kv_grid(npair * a.n_kv_heads * a.batch);
-    // dK and dV in one pass; with the KL term, dV alone (it does not see the map's KL part) and then
-    // dK with the KL part, each at two workgroups per CU
-    auto dkdv_ds = [&](auto kl_c, auto mode_c, auto ds_c) -> hipError_t {
-        constexpr bool K2 = decltype(kl_c)::value;
-        constexpr int MODE = decltype(mode_c)::value;
+    const int G = a.n_heads / a.n_kv_heads;
+    const uint32_t inv_g = (uint32_t)((1ull << 32) / (uint32_t)G + 1);
+    // KW key slices per workgroup, one key block each
+    auto dkdv = [&](auto kw_c) -> hipError_t {
+        constexpr int KW = decltype(kw_c)::value;
+        typedef DkdvCfg<DT, DH, KW, KL> CM;
+        hipError_t err = hipFuncSetAttribute((const void *)attn_bwd_dkdv_pipe_kernel<DT, DH, KW, KL>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, CM::LDS);
+        if (err != hipSuccess) return err;
+        const int nkb = (T + 32 * KW - 1) / (32 * KW);
+        attn_bwd_dkdv_pipe_kernel<DT, DH, KW, KL><<<dim3(nkb * a.n_kv_heads * a.batch), dim3(256), CM::LDS, st>>>(
+            a, scale_log2, inv_sqrt, nkb, inv_g);
+        return hipGetLastError();
+    };
+    auto dkdv_paired = [&](auto ds_c) -> hipError_t {
         constexpr bool DS = decltype(ds_c)::value;
-        typedef BwdTiles<DT, DH, NW, K2, MODE> CM;
-        const size_t lds = (size_t)CM::NS_KV * CM::KV_STAGE;
-        hipError_t err = hipFuncSetAttribute((const void *)attn_bwd_dkdv_dma_kernel<DT, DH, NW, K2, MODE, DS>,
+        const size_t lds = (size_t)C::NS_KV * C::KV_STAGE;
+        hipError_t err = hipFuncSetAttribute((const void *)attn_bwd_dkdv_dma_kernel<DT, DH, NW, KL, DS>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (err != hipSuccess) return err;
-        attn_bwd_dkdv_dma_kernel<DT, DH, NW, K2, MODE, DS><<<kv_grid, dim3(64 * NW), lds, st>>>(
+        const int nkb = (T + 32 * NW - 1) / (32 * NW), npair = (nkb + 1) / 2;
+        attn_bwd_dkdv_dma_kernel<DT, DH, NW, KL, DS><<<dim3(npair * a.n_kv_heads * a.batch), dim3(64 * NW), lds, st>>>(
             a, scale_log2, inv_sqrt, nkb, npair);
         return hipGetLastError();
     };
-    // the pass that computes dK stores dS when the caller gave it room
-    auto dkdv = [&](auto kl_c, auto mode_c) -> hipError_t {
-        if constexpr (decltype(mode_c)::value != 1)
-            if (a.ds) return dkdv_ds(kl_c, mode_c, std::true_type());
-        return dkdv_ds(kl_c, mode_c, std::false_type());
+    // Which form, by the number of pairs of 128-key blocks (the paired form's workgroups; it needs about
+    // two per CU).  us of the dK/dV pass, KW = 1 / 2 / 4 / paired, on 256 CUs, bf16 or fp16:
+    //   DH 128: 64 pairs - / 187 / 305 / 426, 128 - / 247 / 345 / 456, 192 - / 367 / 372 / 473,
+    //   256 - / 498 / 452 / 546, 384 - / - / 649 / 618, 512 - / 977 / 912 / 721
+    //   DH 128, KL term: 128 - / 124 / 137, 256 - / 709 / 570, 512 - / 1470 / 1174 (paired: one workgroup per
+    //   CU, 256 781, 512 1588)
+    //   DH 64: 32 16 / 20 / 33 / 57, 48 22 / 20 / 31 / 41, 128 105 / 75 / 120 / 150, 256 204 / 123 / 140 / 167,
+    //   384 145 / 61 / 57 / 67, 768 300 / 127 / 109 / 127, 1536 - / - / 230 / 226
+    //   DH 64, KL term: 64 41 / 50 / 83 / 97, 96 44 / 33 / 47 / 54, 192 - / 58 / - / -, 384 177 / 122 / 106 / 88,
+    //   768 361 / 257 / 212 / 155
+    // (the head grouping and length differ between the rows; KW = 1 runs one workgroup per CU)
+    const int64_t heads = (int64_t)a.n_kv_heads * a.batch;
+    const int64_t pairs = heads * (((T + 127) / 128 + 1) / 2);
+    auto run_dkdv = [&]() -> hipError_t {
+        if constexpr (DH == 64 || !KL) {
+            if (pairs >= (DH == 128 ? 384 : KL ? 256 : 1024))
+                return a.ds ? dkdv_paired(std::true_type()) : dkdv_paired(std::false_type());
+        }
+        if constexpr (DH == 128 || !KL) {
+            if (pairs >= (DH == 128 ? 192 : 257)) return dkdv(std::integral_constant<int, 4>());
+        }
+        if constexpr (DH == 64) {
+            if (heads * ((T + 31) / 32) <= (KL ? 512 : 256)) return dkdv(std::integral_constant<int, 1>());
+        }
+        return dkdv(std::integral_constant<int, 2>());
     };
-    if constexpr (KL) {
-        e = dkdv(std::false_type(), std::integral_constant<int, 1>());
-        if (e == hipSuccess) e = dkdv(std::true_type(), std::integral_constant<int, 2>());
-    } else {
-        e = dkdv(std::false_type(), std::integral_constant<int, 0>());
-    }
+    e = run_dkdv();
     if (e != hipSuccess) return e;
-    const int G = a.n_heads / a.n_kv_heads;
     const int hpw = G % NW == 0 ? NW : G;              // query heads per workgroup
     const int QT = 32 * NW / hpw;
     const int nqt = (T + QT - 1) / QT;
