@@ -996,26 +996,50 @@ jab_status jab_loss_sweep(const jab_problem *p, const void *x, const void *w, in
                                      i == 0 ? tickets(*p, W) : nullptr, n_triples));
         if ((s = run_project_split(*p, x, W.w_op, W.proj[i], st))) return s;
     }
-    // 2. one score matrix per (b_Q, b_K), applied to the value tensors of up to two triples
-    std::vector<bool> done(n_triples, false);
+    // 2. one score matrix per (b_Q, b_K), applied to the value tensors of up to attn_max_nv triples; the
+    // sets of one size in launches of up to ATT_MAX_SETS, which fill the chip where one set does not and
+    // leave one tail instead of many (us, one launch per set / per 16: {2,3,4,8}^3 of 8 x 2048 Mistral tokens
+    // 14990 / 14740, 1 x 1024 993 / 825, GPT-2 4 x 512 361 / 249, tiny fp32 4 x 128 580 / 83)
+    struct Group {
+        int iq, ik, nv, iv[4], ip[4];
+    };
+    std::vector<Group> groups;
+    const int max_nv = jab::attn_max_nv(p->dtype);
     for (int t = 0; t < n_triples; ++t) {
-        if (done[t]) continue;
-        std::vector<int> group;
-        for (int u = t; u < n_triples; ++u)
-            if (!done[u] && tidx[3 * u] == tidx[3 * t] && tidx[3 * u + 1] == tidx[3 * t + 1]) group.push_back(u);
-        for (size_t g0 = 0; g0 < group.size(); g0 += (size_t)jab::attn_max_nv(p->dtype)) {
-            const int nv = (int)std::min(group.size() - g0, (size_t)jab::attn_max_nv(p->dtype));
-            jab::AttnArgs a = attn_args(*p, W.proj[tidx[3 * t]], W.proj[tidx[3 * t + 1]], W.proj[0]);
-            a.nv = nv;
-            for (int v = 0; v < nv; ++v) {
-                const int u = group[g0 + v];
-                a.v[v] = W.proj[tidx[3 * u + 2]].vt;
-                a.partials[v] = W.partials + (size_t)u * pstride;
-                done[u] = true;
+        Group *g = nullptr;
+        for (Group &h : groups)
+            if (h.iq == tidx[3 * t] && h.ik == tidx[3 * t + 1] && h.nv < max_nv) g = &h;
+        if (!g) {
+            groups.push_back(Group{tidx[3 * t], tidx[3 * t + 1], 0, {}, {}});
+            g = &groups.back();
+        }
+        g->iv[g->nv] = tidx[3 * t + 2];
+        g->ip[g->nv++] = t;
+    }
+    jab::AttnArgs a = attn_args(*p, W.proj[0], W.proj[0], W.proj[0]);
+    a.mode = jab::ATT_LOSS;
+    a.a_ref = a_ref;
+    for (int v = 0; v < 4; ++v) {
+        a.v[v] = W.proj[0].vt;
+        a.partials[v] = W.partials;
+    }
+    if (n_bits > 1) {       // the projections are carved at equal distances
+        a.qk_step = static_cast<char *>(W.proj[1].qk) - static_cast<char *>(W.proj[0].qk);
+        a.v_step = static_cast<char *>(W.proj[1].vt) - static_cast<char *>(W.proj[0].vt);
+    }
+    a.part_step = (int64_t)pstride;
+    for (a.nv = max_nv; a.nv >= 1; --a.nv) {
+        a.n_sets = 0;
+        for (size_t i = 0; i <= groups.size(); ++i) {
+            if (i < groups.size()) {
+                const Group &g = groups[i];
+                if (g.nv != a.nv) continue;
+                a.set[a.n_sets++] = jab::attn_set_code(g.iq, g.ik, g.nv, g.iv, g.ip);
             }
-            a.mode = jab::ATT_LOSS;
-            a.a_ref = a_ref;
-            JAB_RUN(JAB_KT_ATTN, st, "attention", jab::launch_attn_fwd(p->dtype, a, st));
+            if (a.n_sets == jab::ATT_MAX_SETS || (i == groups.size() && a.n_sets)) {
+                JAB_RUN(JAB_KT_ATTN, st, "attention", jab::launch_attn_fwd(p->dtype, a, st));
+                a.n_sets = 0;
+            }
         }
     }
     // 3. deterministic reductions

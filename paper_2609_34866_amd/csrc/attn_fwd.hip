@@ -39,6 +39,7 @@ hipError_t run_attn(const AttnArgs &a, hipStream_t st) {
                 b.v[v] = a.v[v0 + v];
                 b.partials[v] = a.partials[v0 + v];
             }
+            for (int i = 0; i < a.n_sets; ++i) b.set[i] = attn_set_drop(a.set[i], v0);
             if constexpr (DH == 64 || DH == 128) {
                 if (b.nv == 4) e = run_attn_fast_multi<DT, DH, 4>(b, st);
                 else e = b.nv == 2 ? run_attn_fast_multi<DT, DH, 2>(b, st) : launch_attn_fast<DT, DH>(b, st);

@@ -98,6 +98,7 @@ __global__ __launch_bounds__(256, (FastCfg<DT, DH, NV>::WPC)) void attn_fast_ker
     typedef typename MM::operand opnd;
     extern __shared__ __align__(16) unsigned char smem[];
 
+    const AttnSet<NV> as(a);
     const int T = a.seq_len, Hq = a.n_heads;
     const int G = Hq / a.n_kv_heads;
     const int Tp = vt_pad(T);
@@ -163,10 +164,10 @@ __global__ __launch_bounds__(256, (FastCfg<DT, DH, NV>::WPC)) void attn_fast_ker
         t.ht = grp % n_ht;
         t.b = grp / n_ht;
         const int kvh = (t.ht * HG) / G;               // G is a multiple of HG: one kv head per workgroup
-        t.rsk = buffer_rsrc(static_cast<const elem *>(a.k) + (int64_t)t.b * T * a.ld + kvh * DH);
+        t.rsk = buffer_rsrc(static_cast<const elem *>(as.k) + (int64_t)t.b * T * a.ld + kvh * DH);
 #pragma unroll
         for (int v = 0; v < NV; ++v)
-            t.rsv[v] = buffer_rsrc(static_cast<const elem *>(a.v[v]) + (int64_t)kvh * DH * a.ldv + (int64_t)t.b * Tp);
+            t.rsv[v] = buffer_rsrc(static_cast<const elem *>(as.v[v]) + (int64_t)kvh * DH * a.ldv + (int64_t)t.b * Tp);
     };
     // i-th of the wave's PW loads of block j of tile t (block index clamped to the tile's last)
     auto issue_t = [&](const Tile &t, int i, int j, unsigned char *slot) {
@@ -202,7 +203,7 @@ __global__ __launch_bounds__(256, (FastCfg<DT, DH, NV>::WPC)) void attn_fast_ker
     opnd qf[C::NKC];
     auto load_q = [&](const Tile &t) {
         const int qrow = (t.qg * WT + wt) * 32 + l32;
-        const elem *qp = static_cast<const elem *>(a.q) + ((int64_t)t.b * T + min(qrow, T - 1)) * a.ld +
+        const elem *qp = static_cast<const elem *>(as.q) + ((int64_t)t.b * T + min(qrow, T - 1)) * a.ld +
                          (t.ht * HG + wh) * DH;
 #pragma unroll
         for (int kc = 0; kc < C::NKC; ++kc) {
@@ -622,7 +623,7 @@ __global__ __launch_bounds__(256, (FastCfg<DT, DH, NV>::WPC)) void attn_fast_ker
         for (int v = 0; v < NV; ++v) {
             const double tse = wave_sum_f64((double)sse[v]);
             if (lane == 0 && (WT == 1 || qt < nqt)) {
-                double *ps = a.partials[v] + ((int64_t)b * Hq * nq32 + (int64_t)h * nq32 + qt) * 2;
+                double *ps = as.p[v] + ((int64_t)b * Hq * nq32 + (int64_t)h * nq32 + qt) * 2;
                 ps[0] = tse;
                 ps[1] = ta2;
             }
@@ -648,8 +649,9 @@ hipError_t launch_attn_fast_wt(const AttnArgs &a, hipStream_t st) {
     // pairs that do not give each CU two workgroups: one group tile per workgroup, the longest first
     // (measured, pairs / single, us: 1 x 512 of 12 heads 15.2 / 10.5, 1 x 1024 19.8 / 15.0, 8 x 777 25.4 /
     // 22.1; at 1 x 1999 of 32 heads of 128, one pair per CU, equal)
-    const bool single = n_pairs <= 512;
-    attn_fast_kernel<DT, DH, NV, WT><<<dim3(single ? nqg * n_ht * a.batch : n_pairs), dim3(256), C::LDS_BYTES, st>>>(
+    const int n_sets = a.n_sets > 1 ? a.n_sets : 1;
+    const bool single = n_pairs * n_sets <= 512;
+    attn_fast_kernel<DT, DH, NV, WT><<<dim3(single ? nqg * n_ht * a.batch : n_pairs, n_sets), dim3(256), C::LDS_BYTES, st>>>(
         a, scale_log2, nqt, n_ht, single);
     return hipGetLastError();
 }

@@ -161,6 +161,26 @@ __device__ inline int s_k(int kc, int half) {
 #define SCHED_FENCE() do {} while (0)
 #endif
 
+// The pointers of the workgroup's set (grid y).  The code is picked by comparisons: an index into a
+// kernel argument would copy the argument to scratch memory.
+template <int NV>
+struct AttnSet {
+    const void *q, *k, *v[NV];
+    double *p[NV];
+    __device__ AttnSet(const AttnArgs &a) {
+        uint64_t c = a.set[0];
+#pragma unroll
+        for (int i = 1; i < ATT_MAX_SETS; ++i) c = (int)blockIdx.y == i ? a.set[i] : c;
+        q = static_cast<const char *>(a.q) + (int64_t)(c & 7) * a.qk_step;
+        k = static_cast<const char *>(a.k) + (int64_t)(c >> 3 & 7) * a.qk_step;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            v[i] = static_cast<const char *>(a.v[i]) + (int64_t)(c >> (6 + 3 * i) & 7) * a.v_step;
+            p[i] = a.partials[i] + (int64_t)(c >> (18 + 9 * i) & 511) * a.part_step;
+        }
+    }
+};
+
 // NW waves per workgroup; att_wpc workgroups per CU (two for the 16-bit single-value kernel:
 // each wave gets half the register file).
 template <int DT, int DH, int NV, int QB, int NW>
@@ -173,6 +193,7 @@ __global__ __launch_bounds__(64 * NW, (att_wpc<DT, NV, NW>())) void attn_fwd_ker
     typedef typename MM::operand opnd;
     extern __shared__ __align__(16) unsigned char smem[];
 
+    const AttnSet<NV> as(a);
     const int T = a.seq_len, Hq = a.n_heads;
     const int G = Hq / a.n_kv_heads;
     const int QT = NW * C::QW / hpw;                   // queries per workgroup tile
@@ -200,7 +221,7 @@ __global__ __launch_bounds__(64 * NW, (att_wpc<DT, NV, NW>())) void attn_fwd_ker
     const int jmask = q0 / 32;
     const int64_t row0 = (int64_t)b * T;
 
-    const elem *Qg = static_cast<const elem *>(a.q);
+    const elem *Qg = static_cast<const elem *>(as.q);
 
     // ---- this wave's queries as B operands of S^T = K Q^T
     opnd qf[QB][C::NKC];
@@ -239,7 +260,7 @@ __global__ __launch_bounds__(64 * NW, (att_wpc<DT, NV, NW>())) void attn_fwd_ker
     for (int i = 0; i < C::PWK; ++i) {
         const int idx = (wave + NW * i) % C::KI;
         const int p = idx * 64 + lane, r = p / C::CK, c = (p % C::CK) ^ swz_key<C::CK>(r);
-        kdma[i] = static_cast<const elem *>(a.k) + (row0 + r) * a.ld + kvh * DH + c * C::EPC;
+        kdma[i] = static_cast<const elem *>(as.k) + (row0 + r) * a.ld + kvh * DH + c * C::EPC;
         kdst[i] = idx * 1024;
     }
     const elem *vdma[C::PWV];
@@ -249,7 +270,7 @@ __global__ __launch_bounds__(64 * NW, (att_wpc<DT, NV, NW>())) void attn_fwd_ker
         const int idx = (wave + NW * i) % C::VI;
         const int vb = idx * 64, v = vb / C::VCH, prb = vb % C::VCH;
         const int p = prb + lane, r = p / C::CV, c = (p % C::CV) ^ swz_key<C::CV>(r);
-        const elem *vt = static_cast<const elem *>(NV > 1 && v ? a.v[1] : a.v[0]);
+        const elem *vt = static_cast<const elem *>(NV > 1 && v ? as.v[NV - 1] : as.v[0]);
         vdma[i] = vt + (int64_t)(kvh * DH + r) * a.ldv + (int64_t)b * Tp + c * C::EPC;
         vdst[i] = C::K_BYTES + v * C::V_BYTES + prb * 16;
     }
@@ -584,7 +605,7 @@ __global__ __launch_bounds__(64 * NW, (att_wpc<DT, NV, NW>())) void attn_fwd_ker
                 const double tse = wave_sum_f64((double)sse);
                 const double ta2 = wave_sum_f64((double)sa2);
                 if (lane == 0) {
-                    double *pp = a.partials[v] + ((int64_t)b * per_seq + (int64_t)h * nq32 + (q0 / 32 + qb)) * 2;
+                    double *pp = as.p[v] + ((int64_t)b * per_seq + (int64_t)h * nq32 + (q0 / 32 + qb)) * 2;
                     pp[0] = tse;
                     pp[1] = ta2;
                 }
@@ -606,7 +627,7 @@ hipError_t launch_attn_kernel(const AttnArgs &a, int hpw, hipStream_t st) {
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS_BYTES);
     if (e != hipSuccess) return e;
     const int nwg = nqt * n_ht * a.batch;
-    attn_fwd_kernel<DT, DH, NV, QB, NW><<<dim3(nwg), dim3(64 * NW), C::LDS_BYTES, st>>>(a, scale_log2, hpw, nqt, n_ht);
+    attn_fwd_kernel<DT, DH, NV, QB, NW><<<dim3(nwg, max(a.n_sets, 1)), dim3(64 * NW), C::LDS_BYTES, st>>>(a, scale_log2, hpw, nqt, n_ht);
     return hipGetLastError();
 }
 

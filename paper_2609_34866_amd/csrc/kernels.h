@@ -130,7 +130,25 @@ struct AttnArgs {
     void *g_out;                  // [B][T][Hq*dh] storage dtype
     float *d_out;                 // [B][Hq][T]
     double *partials[4];          // per value tensor: [B][Hq][ceil(T/32)][2]
+    // Several (score matrix, value tensors) sets in one launch (ATT_LOSS; grid y): set y's queries and
+    // keys are iq and ik qk_steps after q and k, its i-th values iv[i] v_steps after v[0] and its partials
+    // ip[i] part_steps after partials[0].  One set with code 0 takes the pointers as they are.
+    int n_sets;                   // 0 and 1: one set
+    int64_t qk_step, v_step;      // bytes
+    int64_t part_step;            // doubles
+    uint64_t set[16];             // attn_set_code
 };
+constexpr int ATT_MAX_SETS = 16;
+// 3 bits each for iq, ik, iv[0..3], then 9 bits for ip[0..3] (at most 7 projections, 343 partials)
+inline uint64_t attn_set_code(int iq, int ik, int nv, const int *iv, const int *ip) {
+    uint64_t c = (uint64_t)iq | (uint64_t)ik << 3;
+    for (int i = 0; i < nv; ++i) c |= (uint64_t)iv[i] << (6 + 3 * i) | (uint64_t)ip[i] << (18 + 9 * i);
+    return c;
+}
+// the code without its first n values
+inline uint64_t attn_set_drop(uint64_t c, int n) {
+    return (c & 63) | (((c >> 6) & 4095) >> 3 * n) << 6 | (c >> 18 >> 9 * n) << 18;
+}
 int attn_partials_per_seq(int seq_len, int n_heads);   // (sse, sum a^2) pairs per sequence
 int attn_max_nv(int dtype);   // value tensors one attention pass can share a score matrix with
 hipError_t launch_attn_fwd(int dtype, const AttnArgs &a, hipStream_t st);
