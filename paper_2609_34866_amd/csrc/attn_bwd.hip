@@ -14,6 +14,9 @@
 //   dP_ij = G_i . V_j,  dS_ij = P_ij (dP_ij - D_i)
 //   dQ_i = sum_j dS_ij K_j / sqrt(dh),  dK_j = sum_i dS_ij Q_i / sqrt(dh)
 //
+// The kernels here are the 16-bit dtypes' at head_dim 16 (attn_bwd_mfma.hip has head_dim 64 and 128,
+// attn_bwd_f32.hip fp32).
+//
 // gfx950 design (no atomics, fixed summation order => deterministic):
 //  * dK/dV kernel: a wave owns 32 keys of one kv head and keeps K and V for them in
 //    registers as matrix-core B operands.  The workgroup walks the query tiles
@@ -39,10 +42,7 @@ namespace {
 
 template <int DT>
 __device__ inline typename Mma<DT>::operand load_operand(const typename Mma<DT>::elem *p) {
-    if constexpr (DT == F32)
-        return *p;
-    else
-        return __builtin_bit_cast(typename Mma<DT>::operand, *reinterpret_cast<const u32x4 *>(p));
+    return __builtin_bit_cast(typename Mma<DT>::operand, *reinterpret_cast<const u32x4 *>(p));
 }
 
 // B/A operand of a 16-bit MFMA from two 4-element runs (k-slots 0..3 and 4..7).
@@ -57,14 +57,10 @@ __device__ inline typename Mma<DT>::operand load_operand_split(const typename Mm
 
 template <int DT>
 __device__ inline typename Mma<DT>::operand pack_operand(const f32x16 &v, int first) {
-    if constexpr (DT == F32) {
-        return v[first];
-    } else {
-        u16x8 b;
+    u16x8 b;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) b[i] = from_f32<DT>(v[first + i]);
-        return __builtin_bit_cast(typename Mma<DT>::operand, b);
-    }
+    for (int i = 0; i < 8; ++i) b[i] = from_f32<DT>(v[first + i]);
+    return __builtin_bit_cast(typename Mma<DT>::operand, b);
 }
 
 template <int DT, int DH>
@@ -231,29 +227,16 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkdv_kernel(AttnBwdArgs a, fl
                 }
             }
             // ---- dV^T += G^T P,  dK^T += Q^T dS  (k = the tile's 32 queries)
-            if constexpr (DT == F32) {
 #pragma unroll
-                for (int kc2 = 0; kc2 < 16; ++kc2) {
-                    const int q = 8 * (kc2 >> 2) + 4 * half + (kc2 & 3);
+            for (int kc2 = 0; kc2 < 2; ++kc2) {
+                const typename MM::operand pb = pack_operand<DT>(s, 8 * kc2);
+                const typename MM::operand sb = pack_operand<DT>(dp, 8 * kc2);
+                const int q0 = 16 * kc2 + 4 * half;
 #pragma unroll
-                    for (int d = 0; d < C::NDB; ++d) {
-                        const int c = d * 32 + (lane & 31);
-                        dvt[d] = MM::mma(Gt[c * QTS + q], s[kc2], dvt[d]);
-                        dkt[d] = MM::mma(Qt[c * QTS + q], dp[kc2], dkt[d]);
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int kc2 = 0; kc2 < 2; ++kc2) {
-                    const typename MM::operand pb = pack_operand<DT>(s, 8 * kc2);
-                    const typename MM::operand sb = pack_operand<DT>(dp, 8 * kc2);
-                    const int q0 = 16 * kc2 + 4 * half;
-#pragma unroll
-                    for (int d = 0; d < C::NDB; ++d) {
-                        const int c = d * 32 + (lane & 31);
-                        dvt[d] = MM::mma(load_operand_split<DT>(Gt + c * QTS + q0, Gt + c * QTS + q0 + 8), pb, dvt[d]);
-                        dkt[d] = MM::mma(load_operand_split<DT>(Qt + c * QTS + q0, Qt + c * QTS + q0 + 8), sb, dkt[d]);
-                    }
+                for (int d = 0; d < C::NDB; ++d) {
+                    const int c = d * 32 + (lane & 31);
+                    dvt[d] = MM::mma(load_operand_split<DT>(Gt + c * QTS + q0, Gt + c * QTS + q0 + 8), pb, dvt[d]);
+                    dkt[d] = MM::mma(load_operand_split<DT>(Qt + c * QTS + q0, Qt + c * QTS + q0 + 8), sb, dkt[d]);
                 }
             }
         }
@@ -410,26 +393,15 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_kernel(AttnBwdArgs a, floa
                 }
             }
         // ---- dQ^T += K^T dS^T (k = the tile's 64 keys)
-        if constexpr (DT == F32) {
 #pragma unroll
-            for (int kc2 = 0; kc2 < 32; ++kc2) {
-                const int sb = kc2 >> 4, e = kc2 & 15;
-                const int k = sb * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
+        for (int kc2 = 0; kc2 < 4; ++kc2) {
+            const int sb = kc2 >> 1, hf = kc2 & 1;
+            const typename MM::operand sbop = pack_operand<DT>(dp[sb], 8 * hf);
+            const int k0 = sb * 32 + hf * 16 + 4 * half;
 #pragma unroll
-                for (int d = 0; d < C::NDB; ++d)
-                    dqt[d] = MM::mma(Kt[(d * 32 + (lane & 31)) * KTS + k], dp[sb][e], dqt[d]);
-            }
-        } else {
-#pragma unroll
-            for (int kc2 = 0; kc2 < 4; ++kc2) {
-                const int sb = kc2 >> 1, hf = kc2 & 1;
-                const typename MM::operand sbop = pack_operand<DT>(dp[sb], 8 * hf);
-                const int k0 = sb * 32 + hf * 16 + 4 * half;
-#pragma unroll
-                for (int d = 0; d < C::NDB; ++d) {
-                    const elem *rowp = Kt + (d * 32 + (lane & 31)) * KTS;
-                    dqt[d] = MM::mma(load_operand_split<DT>(rowp + k0, rowp + k0 + 8), sbop, dqt[d]);
-                }
+            for (int d = 0; d < C::NDB; ++d) {
+                const elem *rowp = Kt + (d * 32 + (lane & 31)) * KTS;
+                dqt[d] = MM::mma(load_operand_split<DT>(rowp + k0, rowp + k0 + 8), sbop, dqt[d]);
             }
         }
     }
@@ -611,18 +583,14 @@ hipError_t run_bwd(const AttnBwdArgs &a, hipStream_t st) {
     return run_bwd_kl<DT, DH, false>(a, st);
 }
 
+// fp32: attn_bwd_f32.hip; the 16-bit dtypes at head_dim 64 and 128: attn_bwd_mfma.hip (each with or
+// without the KL term)
 template <int DT>
 hipError_t bwd_dh(const AttnBwdArgs &a, hipStream_t st) {
-    // the 16-bit dtypes at head_dim 64 / 128 take the DMA-pipelined kernels (with or without the
-    // KL term)
-    if constexpr (DT != F32) {
-        if (a.head_dim == 64) return run_bwd_dma<DT, 64>(a, st);
-        if (a.head_dim == 128) return run_bwd_dma<DT, 128>(a, st);
-    }
     switch (a.head_dim) {
     case 16: return run_bwd<DT, 16>(a, st);
-    case 64: return run_bwd<DT, 64>(a, st);
-    default: return run_bwd<DT, 128>(a, st);
+    case 64: return run_bwd_dma<DT, 64>(a, st);
+    default: return run_bwd_dma<DT, 128>(a, st);
     }
 }
 
@@ -630,7 +598,7 @@ hipError_t bwd_dh(const AttnBwdArgs &a, hipStream_t st) {
 
 hipError_t launch_attn_bwd(int dtype, const AttnBwdArgs &a, hipStream_t st) {
     switch (dtype) {
-    case F32: return bwd_dh<F32>(a, st);
+    case F32: return launch_attn_bwd_f32(a, st);
     case F16: return bwd_dh<F16>(a, st);
     default: return bwd_dh<BF16>(a, st);
     }

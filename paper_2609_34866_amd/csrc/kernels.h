@@ -89,6 +89,7 @@ inline size_t attn_bwd_ds_bytes(int batch, int n_heads, int seq_len) {
     return (size_t)batch * n_heads * (nq * (nq + 1) / 2) * 2048;
 }
 hipError_t launch_attn_bwd(int dtype, const AttnBwdArgs &a, hipStream_t st);
+hipError_t launch_attn_bwd_f32(const AttnBwdArgs &a, hipStream_t st);   // launch_attn_bwd for fp32
 // out[c][r] = in[r][c] for an rows x cols matrix of the storage dtype: transpose_ld(rows) columns
 // (rows rounded up to 64; the padding columns written as 0) at row stride out_ld >= that.
 // transpose_stride: the stride of the backward's transposed operands, one 128-byte line past the
