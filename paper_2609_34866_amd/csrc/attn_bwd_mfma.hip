@@ -1004,19 +1004,21 @@ hipError_t run_bwd_dma_kl(const AttnBwdArgs &a, hipStream_t st) {
     //   384 145 / 61 / 57 / 67, 768 300 / 127 / 109 / 127, 1536 - / - / 230 / 226
     //   DH 64, KL term: 64 41 / 50 / 83 / 97, 96 44 / 33 / 47 / 54, 192 - / 58 / - / -, 384 177 / 122 / 106 / 88,
     //   768 361 / 257 / 212 / 155
-    // (the head grouping and length differ between the rows; KW = 1 runs one workgroup per CU)
+    // (the head grouping and length differ between the rows; KW = 1 runs one workgroup per CU and is
+    // taken while its own blocks have a CU each).  The number of ways is the same with the KL term as
+    // without, so lambda = 0 gives the squared error's gradients bit for bit.
     const int64_t heads = (int64_t)a.n_kv_heads * a.batch;
     const int64_t pairs = heads * (((T + 127) / 128 + 1) / 2);
     auto run_dkdv = [&]() -> hipError_t {
         if constexpr (DH == 64 || !KL) {
-            if (pairs >= (DH == 128 ? 384 : KL ? 256 : 1024))
+            if (pairs >= (DH == 128 ? 384 : KL ? 257 : 1024))
                 return a.ds ? dkdv_paired(std::true_type()) : dkdv_paired(std::false_type());
         }
         if constexpr (DH == 128 || !KL) {
             if (pairs >= (DH == 128 ? 192 : 257)) return dkdv(std::integral_constant<int, 4>());
         }
         if constexpr (DH == 64) {
-            if (heads * ((T + 31) / 32) <= (KL ? 512 : 256)) return dkdv(std::integral_constant<int, 1>());
+            if (heads * ((T + 31) / 32) <= 256) return dkdv(std::integral_constant<int, 1>());
         }
         return dkdv(std::integral_constant<int, 2>());
     };

@@ -3,10 +3,12 @@ four key slices per workgroup, one workgroup per key block, and the paired form,
 key blocks; ragged query tiles, steps that a way has no tile for.  The bars are
 those of the backward tests (relative L2 per matrix against the fp64 oracle, 2e-2)."""
 import pytest
+import torch
 
 from paper_2609_34866_amd import jab
 
-from test_gpu_backward import _check_backward
+from gpu_helpers import device_inputs
+from test_gpu_backward import _check_backward, _wl
 from test_gpu_kl_bwd import _check_kl_backward
 
 pytestmark = pytest.mark.gpu
@@ -38,3 +40,16 @@ def test_dkdv_forms_match_oracle(shape, ds_limit):
 @pytest.mark.parametrize("shape", [(128, 33, 64, 2, 2, 64, 32, "bf16", 0.0, 0.1), (65, 129, 64, 4, 2, 64, 32, "f16", 0.0, 0.1)])
 def test_dkdv_forms_with_the_kl_term_match_oracle(shape):
     _check_kl_backward(shape)
+
+
+@pytest.mark.parametrize("shape", FORMS + [(2, 1000, 64, 4, 4, 64, 32, "bf16"), (128, 40, 64, 2, 2, 64, 32, "f16")])
+def test_lambda_zero_is_the_plain_backward_in_every_form(shape):
+    wl = _wl(*shape)
+    x, w = device_inputs(wl)
+    p, bits = jab.problem_of(wl), (3, 4, 2)
+    scale, zero = jab.quant_init(p, w, bits)
+    a, qk, lse = jab.attn_ref_kl(p, x, w)
+    gam = jab.lsq_gscale(bits, wl.group_size)
+    _, dw, ds = jab.loss_bwd(p, x, w, bits, scale, zero, a, gam)
+    _, dw0, ds0 = jab.loss_bwd_kl(p, x, w, bits, scale, zero, a, qk, lse, gam, 0.0)
+    assert torch.equal(dw, dw0) and torch.equal(ds, ds0)
