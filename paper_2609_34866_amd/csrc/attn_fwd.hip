@@ -25,23 +25,28 @@ namespace {
 // 16-bit, head_dim 64 or 128: attn_fast_kernel, with four value tensors per pass, two or one for the
 // rest of the set (measured at 32 x 1024, 12 heads of 64 with their own keys, us: the generic kernel 142,
 // attn_fast_kernel 79; at 8 x 1024 44 and 26); each query gets bitwise the same result whichever pass
-// takes its value tensor.  Elsewhere the generic kernel takes the value tensors in pairs.
+// takes its value tensor.  Past that kernel's 32-bit offsets the generic kernel takes them one at a
+// time, with the same result per query; at head_dim 16 it takes them in pairs.
 template <int DT, int DH, int NV>
 hipError_t run_attn(const AttnArgs &a, hipStream_t st) {
     if constexpr (NV == 2) {                           // a.nv = 2 .. 4 value tensors
         hipError_t e = hipSuccess;
         AttnArgs b = a;
+        const bool fast = (DH == 64 || DH == 128) && fast_offsets_fit(a);
         for (int v0 = 0; v0 < a.nv && e == hipSuccess; v0 += b.nv) {
             const int left = a.nv - v0;
-            if constexpr (DH == 64 || DH == 128) b.nv = left >= 4 && fast_max_nv<DH>(a) == 4 ? 4 : min(2, left);
-            else b.nv = min(2, left);
+            if constexpr (DH == 64 || DH == 128)
+                b.nv = !fast ? 1 : left >= 4 && fast_max_nv<DH>(a) == 4 ? 4 : min(2, left);
+            else
+                b.nv = min(2, left);
             for (int v = 0; v < b.nv; ++v) {
                 b.v[v] = a.v[v0 + v];
                 b.partials[v] = a.partials[v0 + v];
             }
             for (int i = 0; i < a.n_sets; ++i) b.set[i] = attn_set_drop(a.set[i], v0);
             if constexpr (DH == 64 || DH == 128) {
-                if (b.nv == 4) e = run_attn_fast_multi<DT, DH, 4>(b, st);
+                if (!fast) e = run_attn_cfg<DT, DH, 1, 1, ATT_NW>(b, st);
+                else if (b.nv == 4) e = run_attn_fast_multi<DT, DH, 4>(b, st);
                 else e = b.nv == 2 ? run_attn_fast_multi<DT, DH, 2>(b, st) : launch_attn_fast<DT, DH>(b, st);
             } else {
                 e = b.nv == 2 ? run_attn_nv2<DT, DH>(b, st) : run_attn_cfg<DT, DH, 1, 1, ATT_NW>(b, st);
@@ -49,8 +54,9 @@ hipError_t run_attn(const AttnArgs &a, hipStream_t st) {
         }
         return e;
     } else if constexpr (DT != F32) {
-        if constexpr (DH == 64 || DH == 128) return launch_attn_fast<DT, DH>(a, st);
-        else return run_attn_cfg<DT, DH, 1, 1, ATT_NW>(a, st);
+        if constexpr (DH == 64 || DH == 128)
+            if (fast_offsets_fit(a)) return launch_attn_fast<DT, DH>(a, st);
+        return run_attn_cfg<DT, DH, 1, 1, ATT_NW>(a, st);
     } else {
         return run_attn_cfg<DT, DH, 1, 1, 4>(a, st);
     }

@@ -137,19 +137,20 @@ __global__ __launch_bounds__(256, (FastCfg<DT, DH, NV>::WPC)) void attn_fast_ker
     // swz_key(row).  Load i >= PK fills transposed-value chunks the same way (DH rows of four
     // chunks).  Keys past the sequence read the rows that follow it (the next sequence, or the 32
     // rows of slack after the last): the causal mask removes them.  Blocks past the tile's range
-    // re-load its last block into a slot that is never read.
+    // re-load its last block into a slot that is never read.  Offsets are unsigned 32-bit bytes from a
+    // sequence's first key or a head's first value row (fast_offsets_fit).
     uint32_t dvoff[C::PK + C::PV];
 #pragma unroll
     for (int i = 0; i < C::PK; ++i) {
         const int p = (wave + 4 * i) * 64 + lane, r = p / C::CK, c = (p % C::CK) ^ swz_key<C::CK>(r);
-        dvoff[i] = (uint32_t)(r * a.ld * 2 + c * 16);
+        dvoff[i] = (uint32_t)r * (uint32_t)a.ld * 2u + c * 16u;
     }
 #pragma unroll
     for (int i = 0; i < C::PV; ++i) {
         const int p = (wave + 4 * i) * 64 + lane, r = p / 4, c = (p % 4) ^ swz_key<4>(r);
-        dvoff[C::PK + i] = (uint32_t)(r * (int)a.ldv * 2 + c * 16);
+        dvoff[C::PK + i] = (uint32_t)r * (uint32_t)a.ldv * 2u + c * 16u;
     }
-    const int kstride = a.ld * 2 * 32;                 // bytes between key blocks of K
+    const uint32_t kstride = (uint32_t)a.ld * 64u;     // bytes between key blocks of K
 
     // ---- a tile: its query tile, head group and sequence, and the buffer resources of its keys
     // and values (wave-uniform)
@@ -173,7 +174,7 @@ __global__ __launch_bounds__(256, (FastCfg<DT, DH, NV>::WPC)) void attn_fast_ker
     auto issue_t = [&](const Tile &t, int i, int j, unsigned char *slot) {
         const int jl = last_block(t), jb = j < jl ? j : jl;
         if (i < C::PK) {
-            buffer_dma16(t.rsk, dvoff[i], jb * kstride, slot + (wave + 4 * i) * 1024);
+            buffer_dma16(t.rsk, dvoff[i], (int)(jb * kstride), slot + (wave + 4 * i) * 1024);
         } else {                                       // value tensor v, piece pc of its tile
             const int v = (i - C::PK) / C::PV, pc = (i - C::PK) % C::PV;
             buffer_dma16(t.rsv[v], dvoff[C::PK + pc], jb * 64, slot + C::K_BYTES + v * C::V_BYTES + (wave + 4 * pc) * 1024);
@@ -245,7 +246,7 @@ __global__ __launch_bounds__(256, (FastCfg<DT, DH, NV>::WPC)) void attn_fast_ker
         if constexpr (NV == 1) {
             const int pch = (wave + 4 * i) * 64 + lane, r = pch / CR, c = (pch % CR) ^ (r & 15);
             const int row = min((wa / HG) * 32 + r, T - 1 - qb0);
-            buffer_dma16(rsa, (uint32_t)(row * ac * 4 + c * 16), (wa % HG) * DH * 4, slot + (wave + 4 * i) * 1024);
+            buffer_dma16(rsa, (uint32_t)row * (uint32_t)ac * 4u + c * 16u, (wa % HG) * DH * 4, slot + (wave + 4 * i) * 1024);
         }
     };
     static_assert(NV > 1 || 32 * DH * 4 == C::BLK, "a teacher tile fills one slot");
@@ -658,6 +659,16 @@ hipError_t launch_attn_fast_wt(const AttnArgs &a, hipStream_t st) {
 
 // Four value tensors at head_dim 128 fill the accumulation registers and fit only without WT's
 // per-wave tiles (WT 2 and 4 spilled 315 registers): such groups go two at a time
+// The kernel's offsets are 32-bit: a sequence's keys (T rows and the 31 after them), the rows of a head's
+// transposed values and the teacher rows of a group tile each have to end below 2^32 bytes.  The sizes
+// past that (values: 16.9 M padded tokens at head_dim 128, 34.1 M at 64) take attn_fwd_kernel, whose
+// addresses are 64-bit.
+inline bool fast_offsets_fit(const AttnArgs &a) {
+    const int64_t lim = ((int64_t)1 << 32) - 256;
+    return (int64_t)(a.seq_len + 32) * a.ld * 2 < lim && ((int64_t)(a.head_dim - 1) * a.ldv + vt_pad(a.seq_len)) * 2 < lim &&
+           (int64_t)129 * a.n_heads * a.head_dim * 4 < lim;
+}
+
 template <int DH>
 int fast_max_nv(const AttnArgs &a) { return DH == 64 || a.n_heads / a.n_kv_heads % 4 == 0 ? 4 : 2; }
 

@@ -232,9 +232,9 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_kl_ring_kernel(KlA
 #pragma unroll
     for (int i = 0; i < PK; ++i) {
         const int p = (wave + 4 * i) * 64 + lane, r = p / CK, c = (p % CK) ^ swz_key<CK>(r);
-        dvoff[i] = (uint32_t)(r * a.ld * 2 + c * 16);
+        dvoff[i] = (uint32_t)r * (uint32_t)a.ld * 2u + c * 16u;
     }
-    const int kstride = a.ld * 2 * 32;
+    const uint32_t kstride = (uint32_t)a.ld * 64u;     // 32-bit byte offsets: see run_kl
     auto issue = [&](int j, unsigned char *slot) {
         const int jb = min(j, jlast);
         const int rows = T - jb * 32;                  // keys of the block
@@ -243,10 +243,10 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void attn_kl_ring_kernel(KlA
             uint32_t v = dvoff[i];
             if (RAG && rows < 32) {                         // the sequence's ragged last block: its last key again
                 const int p = (wave + 4 * i) * 64 + lane, r = p / CK, c = (p % CK) ^ swz_key<CK>(r);
-                v = (uint32_t)(min(r, rows - 1) * a.ld * 2 + c * 16);
+                v = (uint32_t)min(r, rows - 1) * (uint32_t)a.ld * 2u + c * 16u;
             }
-            buffer_dma16(rss, v, jb * kstride, slot + (wave + 4 * i) * 1024);
-            buffer_dma16(rst, v, jb * kstride, slot + K_BYTES + (wave + 4 * i) * 1024);
+            buffer_dma16(rss, v, (int)(jb * kstride), slot + (wave + 4 * i) * 1024);
+            buffer_dma16(rst, v, (int)(jb * kstride), slot + K_BYTES + (wave + 4 * i) * 1024);
         }
     };
     uint32_t koff[NKC];
@@ -367,21 +367,22 @@ hipError_t run_kl_ring(const KlArgs &a, hipStream_t st) {
 template <int DT, int DH>
 hipError_t run_kl(const KlArgs &a, hipStream_t st) {
     if constexpr (DT != F32 && (DH == 64 || DH == 128)) {
-        const int G = a.n_heads / a.n_kv_heads;
-        if (a.seq_len % 32 != 0) {
-            if (G == 1) return run_kl_ring<DT, DH, 4, true>(a, st);
-            return G == 2 ? run_kl_ring<DT, DH, 2, true>(a, st) : run_kl_ring<DT, DH, 1, true>(a, st);
+        // the ring kernel's offsets inside a sequence's keys are 32-bit; longer ones take attn_kl_kernel
+        if ((int64_t)(a.seq_len + 32) * a.ld * 2 < ((int64_t)1 << 32) - 256) {
+            const int G = a.n_heads / a.n_kv_heads;
+            if (a.seq_len % 32 != 0) {
+                if (G == 1) return run_kl_ring<DT, DH, 4, true>(a, st);
+                return G == 2 ? run_kl_ring<DT, DH, 2, true>(a, st) : run_kl_ring<DT, DH, 1, true>(a, st);
+            }
+            if (G == 1) return run_kl_ring<DT, DH, 4, false>(a, st);
+            return G == 2 ? run_kl_ring<DT, DH, 2, false>(a, st) : run_kl_ring<DT, DH, 1, false>(a, st);
         }
-        if (G == 1) return run_kl_ring<DT, DH, 4, false>(a, st);
-        return G == 2 ? run_kl_ring<DT, DH, 2, false>(a, st) : run_kl_ring<DT, DH, 1, false>(a, st);
-    } else {
-        const int nqt = (a.seq_len + 31) / 32;
-        const int64_t n_waves = (int64_t)a.batch * a.n_heads * nqt;
-        const float scale_log2 = 1.4426950408889634f / sqrtf((float)DH);
-        attn_kl_kernel<DT, DH><<<dim3((unsigned)((n_waves + 3) / 4)), dim3(256), 0, st>>>(a, scale_log2, nqt,
-                                                                                     (int)n_waves);
-        return hipGetLastError();
     }
+    const int nqt = (a.seq_len + 31) / 32;
+    const int64_t n_waves = (int64_t)a.batch * a.n_heads * nqt;
+    const float scale_log2 = 1.4426950408889634f / sqrtf((float)DH);
+    attn_kl_kernel<DT, DH><<<dim3((unsigned)((n_waves + 3) / 4)), dim3(256), 0, st>>>(a, scale_log2, nqt, (int)n_waves);
+    return hipGetLastError();
 }
 
 template <int DT>
