@@ -28,6 +28,7 @@
 #include <algorithm>
 #include <map>
 #include <mutex>
+#include <type_traits>
 #include <utility>
 
 #include "device_common.h"
@@ -123,7 +124,8 @@ __device__ inline f32x16 mma_chunk(u32x4 a, u32x4 b, f32x16 c) {
 // RDH > 0 (128-tile, 16-bit, OUT_DT): the rotary embedding on the [Q|K] tiles, heads of RDH columns, as
 // in gemm_w4p_kernel's epilogue.  A pair (c, c + RDH / 2) has to sit in one wave: at RDH 128 wave
 // column wc takes the 32-column blocks wc and wc + 2 of the tile instead of 2 wc and 2 wc + 1.
-template <int DT, int BT, int CPR, int OUT, int RDH>
+// WIDE: rows of a panel more than 2^32 bytes apart (offsets_fit), so the loads take 64-bit addresses per lane.
+template <int DT, int BT, int CPR, int OUT, int RDH, bool WIDE>
 __global__ __launch_bounds__(256, 2) void gemm_small_kernel(SmallArgs g) {
     typedef SmallCfg<DT, BT, CPR> S;
     static_assert(RDH == 0 || (OUT == OUT_DT && BT == 128 && DT != F32 && (RDH == 64 || RDH == 128)), "rotary epilogue");
@@ -168,24 +170,30 @@ __global__ __launch_bounds__(256, 2) void gemm_small_kernel(SmallArgs g) {
         return s * g.seq_T + min(n - s * g.seq_Tp, g.seq_T - 1);
     };
     const int rb0 = val ? token(min(bn0, g.n_tok - 1)) : bn0;
-    const i32x4 rsA = buffer_rsrc(Ap + (int64_t)bm0 * lda + (int64_t)kt0 * S::BK);
-    const i32x4 rsB = buffer_rsrc(Bp + (int64_t)rb0 * ldb + (int64_t)kt0 * S::BK);
-    uint32_t voffA[S::DPP], voffB[S::DPP];
+    const elem *Ab = Ap + (int64_t)bm0 * lda + (int64_t)kt0 * S::BK, *Bb = Bp + (int64_t)rb0 * ldb + (int64_t)kt0 * S::BK;
+    const i32x4 rsA = buffer_rsrc(Ab), rsB = buffer_rsrc(Bb);
+    typedef typename std::conditional<WIDE, uint64_t, uint32_t>::type off_t;
+    off_t voffA[S::DPP], voffB[S::DPP];
 #pragma unroll
     for (int i = 0; i < S::DPP; ++i) {
         const int r = S::RPI * (wave + 4 * i) + lane / CPR, c = (lane % CPR) ^ w4_key<CPR>(r);
         const int ra = min(bm0 + r, rows_a - 1) - bm0;
         const int rb = (val ? token(min(bn0 + r, g.n_tok - 1)) : min(bn0 + r, g.N - 1)) - rb0;
-        voffA[i] = (uint32_t)(ra * lda * S::ES + c * 16);
-        voffB[i] = (uint32_t)(rb * ldb * S::ES + c * 16);
+        voffA[i] = (off_t)ra * (off_t)lda * (off_t)S::ES + (off_t)(c * 16);
+        voffB[i] = (off_t)rb * (off_t)ldb * (off_t)S::ES + (off_t)(c * 16);
     }
     auto issue = [&](int kt, int slot) {      // k-tile kt (past the end: the last again, never read)
-        const int kk = min(kt, nk - 1) * S::BK * S::ES;
+        const off_t kk = (off_t)min(kt, nk - 1) * (off_t)(S::BK * S::ES);
         unsigned char *st = smem + slot * S::STAGE;
 #pragma unroll
         for (int i = 0; i < S::DPP; ++i) {
-            buffer_dma16(rsA, voffA[i], kk, st + (wave + 4 * i) * 1024);
-            buffer_dma16(rsB, voffB[i], kk, st + S::PANEL + (wave + 4 * i) * 1024);
+            if constexpr (WIDE) {
+                lds_dma16(reinterpret_cast<const char *>(Ab) + voffA[i] + kk, st + (wave + 4 * i) * 1024);
+                lds_dma16(reinterpret_cast<const char *>(Bb) + voffB[i] + kk, st + S::PANEL + (wave + 4 * i) * 1024);
+            } else {
+                buffer_dma16(rsA, voffA[i], (int)kk, st + (wave + 4 * i) * 1024);
+                buffer_dma16(rsB, voffB[i], (int)kk, st + S::PANEL + (wave + 4 * i) * 1024);
+            }
         }
     };
 
@@ -432,8 +440,8 @@ __global__ __launch_bounds__(256, 1) void gemm_w4p_kernel(const void *__restrict
     for (int i = 0; i < DPA; ++i) {
         const int r = RPI * (wave + 4 * i) + lane / CPR, pc = lane % CPR;
         const int c = pc ^ w4_key<CPR>(r);
-        voffA[i] = (uint32_t)(r * lda * 2 + c * 16);
-        voffB[i] = (uint32_t)(r * ldb * 2 + c * 16);
+        voffA[i] = (uint32_t)r * (uint32_t)lda * 2u + c * 16u;
+        voffB[i] = (uint32_t)r * (uint32_t)ldb * 2u + c * 16u;
     }
     // OUT_QKV (lda == ldb) with sequences that are not whole blocks of 32 tokens: a value tile's rows
     // of X skip at the sequence ends, so its per-lane offsets are its own; they are set for the first
@@ -451,7 +459,7 @@ __global__ __launch_bounds__(256, 1) void gemm_w4p_kernel(const void *__restrict
 #pragma unroll
             for (int i = 0; i < DPA; ++i) {
                 const int rr = t.val ? token(t.bn0 + r0 + 32 * i) - base : r0 + 32 * i;
-                voffB[i] = (uint32_t)(rr * ldb * 2 + c16);
+                voffB[i] = (uint32_t)rr * (uint32_t)ldb * 2u + c16;
             }
         }
     };
@@ -459,7 +467,7 @@ __global__ __launch_bounds__(256, 1) void gemm_w4p_kernel(const void *__restrict
     auto issue = [&](const Tile &t, int d, int ktile, int slot) {
         int kx = ktile + t.ks;
         if (kx >= nk) kx -= nk;
-        const int kk = (t.k0 + kx) * BK * 2;
+        const int kk = (int)((uint32_t)(t.k0 + kx) * (BK * 2u));
         if (d < DPA) buffer_dma16(t.rsA, voffA[d], kk, smem + ABASE + slot * HALF + (wave + 4 * d) * 1024);
         else buffer_dma16(t.rsB, voffB[d - DPA], kk, smem + BBASE + slot * HALF + (wave + 4 * (d - DPA)) * 1024);
     };
@@ -873,13 +881,22 @@ hipError_t run_gemm_w4p(const Gemm &g, hipStream_t st) {
     return hipGetLastError();
 }
 
+// A tile's loads take 32-bit byte offsets from its panels' first rows: bt rows of A and of B, and the k
+// range behind the last one, end below 2^32 bytes (the weight gradient's rows are as long as the batch has
+// tokens: 8.4 M of 16 bits with the 256-tile).  The row strides of a split plan are its K, at most a line less
+// than the launch's: a plan for the persistent kernel that then does not fit runs its parts in small tiles.
+bool offsets_fit(const Gemm &g, int bt) {
+    return (int64_t)bt * std::max(g.lda, g.ldb) * (g.dtype == F32 ? 4 : 2) < ((int64_t)1 << 32) - 256;
+}
+
 // The persistent kernel takes whole 256 x 256 tiles, 16-byte aligned output rows and at least three
 // k-tiles; a split K (fp32 output) only in two and where the tiles are whole in both directions (no
 // tile moved back over its neighbour: the two parts are summed by the caller); for the transposed
 // value output, 32-token blocks inside one sequence (OUT_QKV works on padded positions instead).
 template <int OUT>
 bool persistent_fits(const Gemm &g) {
-    if (g.dtype == F32 || g.M < 256 || g.N < 256 || g.K % 64 != 0 || g.K / 64 / g.ksplit < 3) return false;
+    if (g.dtype == F32 || g.M < 256 || g.N < 256 || g.K % 64 != 0 || g.K / 64 / g.ksplit < 3 || !offsets_fit(g, 256))
+        return false;
     if (g.ksplit > 1 && (OUT != OUT_F32 || g.ksplit > 2 || g.K % 128 != 0 || g.M % 256 != 0 || g.N % 256 != 0))
         return false;
     if (OUT == OUT_F32) return g.ldc % 4 == 0 && g.N % 4 == 0;
@@ -889,7 +906,7 @@ bool persistent_fits(const Gemm &g) {
     return OUT != OUT_QKV || (g.nv >= 256 && g.n_tok >= 256 && g.lda == g.ldb && g.ldv % 8 == 0);
 }
 
-template <int DT, int BT, int CPR, int OUT, int RDH = 0>
+template <int DT, int BT, int CPR, int OUT, int RDH = 0, bool WIDE = false>
 hipError_t run_gemm_small_cfg(const Gemm &g, hipStream_t st) {
     typedef SmallCfg<DT, BT, CPR> S;
     SmallArgs a;
@@ -902,12 +919,12 @@ hipError_t run_gemm_small_cfg(const Gemm &g, hipStream_t st) {
     a.tiles_vm = (g.nv + BT - 1) / BT;
     a.tiles_vn = (g.n_tok + BT - 1) / BT;
     a.rtab = g.rtab;
-    hipError_t e = hipFuncSetAttribute((const void *)gemm_small_kernel<DT, BT, CPR, OUT, RDH>,
+    hipError_t e = hipFuncSetAttribute((const void *)gemm_small_kernel<DT, BT, CPR, OUT, RDH, WIDE>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::LDS_BYTES);
     if (e != hipSuccess) return e;
     const int n = a.tiles_m * a.tiles_n * g.ksplit + (OUT == OUT_DT ? a.tiles_vm * a.tiles_vn : 0);
     if (n == 0) return hipSuccess;
-    gemm_small_kernel<DT, BT, CPR, OUT, RDH><<<dim3(n), dim3(256), S::LDS_BYTES, st>>>(a);
+    gemm_small_kernel<DT, BT, CPR, OUT, RDH, WIDE><<<dim3(n), dim3(256), S::LDS_BYTES, st>>>(a);
     return hipGetLastError();
 }
 
@@ -923,11 +940,12 @@ int tiles_of(const Gemm &g, int bt) {
 template <int DT, int OUT, int RDH>
 hipError_t run_gemm_small(const Gemm &g, hipStream_t st) {
     if (g.K % 32 != 0) return hipErrorInvalidValue;
-    if constexpr (RDH > 0) {
+    if constexpr (RDH > 0) {                          // at least 192 rows of weights: K is below 11.2 M
         return g.K % 64 == 0 ? run_gemm_small_cfg<DT, 128, 8, OUT, RDH>(g, st)
                              : run_gemm_small_cfg<DT, 128, 4, OUT, RDH>(g, st);
     } else {
-        const bool big = tiles_of(g, 128) >= (DT == F32 ? 8 : 1) * CUS;
+        if (!offsets_fit(g, 64)) return run_gemm_small_cfg<DT, 64, 4, OUT, 0, true>(g, st);
+        const bool big = tiles_of(g, 128) >= (DT == F32 ? 8 : 1) * CUS && offsets_fit(g, 128);
         if constexpr (DT != F32)
             if (g.K % 64 != 0)
                 return big ? run_gemm_small_cfg<DT, 128, 4, OUT>(g, st) : run_gemm_small_cfg<DT, 64, 4, OUT>(g, st);

@@ -72,3 +72,52 @@ def test_keys_past_4_gib():
     out = jab.loss_fwd_kl(p, x, w, (0, 0, 0), None, None, a, qk, lse)
     assert float(out[0]) == 0.0 and float(out[4]) == 0.0
     assert abs(float(out[6])) <= 1e-4 * heads * T
+
+
+# the weight gradient contracts over the tokens, so its operands' rows are as long as the batch has tokens:
+# 64 rows of them pass 2^32 bytes
+@pytest.mark.parametrize("dtype,hq,dh,B,bar", [(torch.float32, 2, 16, 533300, 1e-3), (torch.bfloat16, 1, 64, 1065300, 2e-2)])
+def test_weight_gradient_of_many_tokens(dtype, hq, dh, B, bar):
+    """bar: the running fp32 sums of a part's million tokens (2^-24 per step, as its square root: 6e-5); in
+    16 bits the backward tests' 2e-2 for gradients."""
+    T, d = 32, 32
+    p = jab.problem(B, T, d, hq, 1, dh, 32, dtype)
+    x, w = _inputs(p.rows, B, T, d, dtype)
+    bits = (3, 3, 3)
+    scale, zero = jab.quant_init(p, w, bits)
+    a = jab.attn_ref(p, x, w)
+    _, dw, _ = jab.loss_bwd(p, x, w, bits, scale, zero, a, jab.lsq_gscale(bits, 32))
+    w_hat = jab.quantize(p, w, bits, scale, zero)["w_hat"].to(dtype).double()
+    want = torch.zeros_like(w_hat)
+    mask = torch.ones(T, T, dtype=torch.bool, device="cuda").triu(1)
+    for b0 in range(0, B, 32768):
+        xb = x[b0:b0 + 32768].double()
+        *qs, k, v = ((xb @ m.t().contiguous()) for m in w_hat.split(dh))
+        kt, vt = k.transpose(1, 2).contiguous(), v.transpose(1, 2).contiguous()
+        dq, dk, dv = [], 0.0, 0.0
+        for h, q in enumerate(qs):
+            z = torch.bmm(q, kt) / math.sqrt(dh)
+            prob = torch.softmax(z.masked_fill_(mask, -math.inf), -1)
+            g = (torch.bmm(prob, v) - a[b0:b0 + 32768, :, h * dh:(h + 1) * dh]) * (2.0 / (B * T * hq * dh))
+            dp = torch.bmm(g, vt)
+            dz = prob * (dp - (dp * prob).sum(-1, keepdim=True)) / math.sqrt(dh)
+            dq.append(torch.bmm(dz, k))
+            dk = dk + torch.bmm(dz.transpose(1, 2).contiguous(), q)
+            dv = dv + torch.bmm(prob.transpose(1, 2).contiguous(), g)
+        dy = torch.cat(dq + [dk, dv], -1)
+        want += dy.reshape(-1, p.rows).t().contiguous() @ xb.reshape(-1, d)
+    for m, (got, ref) in enumerate(zip(dw.double().split(dh), want.split(dh))):
+        assert float((got - ref).norm()) <= bar * float(ref.norm()), m
+
+
+def test_projection_of_wide_rows():
+    """17.1 M input channels: the 64 rows of the activations pass 2^32 bytes."""
+    d, T, dtype = 17_100_000 // 32 * 32, 64, torch.float32
+    p = jab.problem(1, T, d, 1, 1, 16, 32, dtype)
+    x, w = _inputs(p.rows, 1, T, d, dtype)
+    y = jab.project(p, x, w)[0].double()
+    want = torch.zeros_like(y)
+    for k in range(0, d, 1 << 20):
+        want += x[0, :, k:k + (1 << 20)].double() @ w[:, k:k + (1 << 20)].double().t().contiguous()
+    # 17 M running fp32 sums: 2^-24 per step as its square root, 2.5e-4
+    assert float((y - want).norm()) <= 2e-3 * float(want.norm())
