@@ -11,6 +11,8 @@
 // MI355X, us, dK/dV and dQ, with 128-row workgroups whose waves shared staged tiles / here: 3 x 333 tokens
 // of 12 heads of 64 76 and 55 / 39 and 24, 8 x 512 191 and 149 / 125 and 71; with the KL term 2 x 512 124 and
 // 99 / 43 and 35.
+#include <algorithm>
+
 #include "device_common.h"
 #include "kernels.h"
 
@@ -300,6 +302,28 @@ __global__ __launch_bounds__((64 * F32Cfg<DH, KL>::NW), 1) void attn_bwd_dq_f32_
         }
 }
 
+// the arguments of sequences b0 .. b0 + n - 1
+template <bool KL>
+AttnBwdArgs sequences(const AttnBwdArgs &a, int b0, int n) {
+    AttnBwdArgs s = a;
+    const int64_t row = (int64_t)b0 * a.seq_len, map = (int64_t)b0 * a.n_heads * a.seq_len;
+    auto rows = [row](const void *p, int64_t ld) { return static_cast<const float *>(p) + row * ld; };
+    s.batch = n;
+    s.q = rows(a.q, a.ldq);
+    s.k = rows(a.k, a.ldq);
+    s.v = rows(a.v, a.ldv);
+    s.g = rows(a.g, (int64_t)a.n_heads * a.head_dim);
+    s.lse2 = a.lse2 + map;
+    s.D = a.D + map;
+    s.dyt = static_cast<float *>(a.dyt) + row;
+    if (KL) {
+        s.qt = rows(a.qt, a.ldq);
+        s.kt = rows(a.kt, a.ldq);
+        s.lse_t = a.lse_t + map;
+    }
+    return s;
+}
+
 template <int DH, bool KL>
 hipError_t run(const AttnBwdArgs &a, hipStream_t st) {
     constexpr size_t kv_lds = f32_lds_bytes<DH, KL>(2), q_lds = f32_lds_bytes<DH, KL>(1);
@@ -314,11 +338,20 @@ hipError_t run(const AttnBwdArgs &a, hipStream_t st) {
     e = hipFuncSetAttribute((const void *)attn_bwd_dq_f32_kernel<DH, KL>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)q_lds);
     if (e != hipSuccess) return e;
-    attn_bwd_dkdv_f32_kernel<DH, KL><<<dim3(nb * a.n_kv_heads * a.batch), block, kv_lds, st>>>(a, scale_log2, inv_sqrt, nb);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    attn_bwd_dq_f32_kernel<DH, KL><<<dim3(nb * a.n_heads * a.batch), block, q_lds, st>>>(a, scale_log2, inv_sqrt, nb);
-    return hipGetLastError();
+    // a grid holds below 2^32 threads, so many heads of many sequences go in several launches
+    const int64_t most = (((int64_t)1 << 32) - 1) / (int64_t)block.x;
+    auto launch = [&](auto kernel, int heads, size_t lds) -> hipError_t {
+        const int step = (int)std::max<int64_t>(1, most / ((int64_t)nb * heads));
+        for (int b0 = 0; b0 < a.batch; b0 += std::min(step, a.batch - b0)) {
+            const int n = std::min(step, a.batch - b0);
+            kernel<<<dim3(nb * heads * n), block, lds, st>>>(sequences<KL>(a, b0, n), scale_log2, inv_sqrt, nb);
+            const hipError_t err = hipGetLastError();
+            if (err != hipSuccess) return err;
+        }
+        return hipSuccess;
+    };
+    e = launch(attn_bwd_dkdv_f32_kernel<DH, KL>, a.n_kv_heads, kv_lds);
+    return e == hipSuccess ? launch(attn_bwd_dq_f32_kernel<DH, KL>, a.n_heads, q_lds) : e;
 }
 
 }  // namespace

@@ -3,6 +3,9 @@
 tiles, groups of query heads.  The bars are those of the backward tests (1e-4 relative L2 per matrix
 against the fp64 oracle)."""
 import pytest
+import torch
+
+from paper_2609_34866_amd import jab
 
 from test_gpu_backward import _check_backward
 from test_gpu_kl_bwd import _check_kl_backward
@@ -16,3 +19,29 @@ def test_fp32_backward_matches_oracle(B, T, hq, hkv, dh):
     shape = (B, T, 64, hq, hkv, dh, 32, "f32")
     _check_backward(shape)
     _check_kl_backward(shape + (0.0, 0.1))
+
+
+def test_more_workgroups_than_one_launch_takes():
+    """64 heads of 262144 one-token sequences: 2^24 workgroups of 256 threads, one more than a grid dimension
+    holds.  With one token P = 1, so dV is the output gradient summed over the group and dS = 0 up to the
+    rounding of the two sums whose difference it is."""
+    B, d, hq, hkv, dh = 262144, 32, 64, 16, 16
+    p = jab.problem(B, 1, d, hq, hkv, dh, 32, torch.float32)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    x = torch.randn((B, 1, d), generator=gen, device="cuda")
+    w = torch.randn((p.rows, d), generator=gen, device="cuda") * 0.1
+    bits = (3, 3, 3)
+    scale, zero = jab.quant_init(p, w, bits)
+    a, qk, lse = jab.attn_ref_kl(p, x, w)
+    gam = jab.lsq_gscale(bits, 32)
+    w_hat = jab.quantize(p, w, bits, scale, zero)["w_hat"]
+    xs = x.reshape(B, d).double()
+    diff = xs @ (w_hat - w)[-hkv * dh:].double().t().contiguous()        # [B][hkv dh], the same for a group's heads
+    want = (diff.t().contiguous() @ xs) * ((hq // hkv) * 2.0 / (B * hq * dh))
+    for dw in (jab.loss_bwd(p, x, w, bits, scale, zero, a, gam)[1],
+               jab.loss_bwd_kl(p, x, w, bits, scale, zero, a, qk, lse, gam, 0.1)[1]):
+        dv = dw[-hkv * dh:].double()
+        # 2^-24 per addition, 262144 of them in up to sixteen parts
+        assert float((dv - want).norm()) <= 1e-4 * float(want.norm())
+        assert float(dw[:-hkv * dh].double().norm()) <= 1e-4 * float(want.norm())
