@@ -8,6 +8,9 @@
 // at the end, in wave order.  A wave stages its own tiles, row-major, with the next tile's global loads
 // in registers while it computes: no barrier in the loop.  The products that contract over tokens read
 // the same tiles column by column (one float per lane, 32 consecutive addresses), so no transposed copy is kept.
+// The teacher's tile of the KL term enters one score product alone, so it stays in registers as that product's
+// operand: with it in LDS, head_dim 128 had room for two waves per CU (8 x 2048 tokens of 32 / 8 heads of 128,
+// dK/dV and dQ 14.8 and 11.2 ms against 9.0 and 6.2 with four).
 // MI355X, us, dK/dV and dQ, with 128-row workgroups whose waves shared staged tiles / here: 3 x 333 tokens
 // of 12 heads of 64 76 and 55 / 39 and 24, 8 x 512 191 and 149 / 125 and 71; with the KL term 2 x 512 124 and
 // 99 / 43 and 35.
@@ -23,13 +26,12 @@ template <int DH, bool KL>
 struct F32Cfg {
     static constexpr int RST = DH + 4;                 // floats per tile row
     static constexpr int NDB = DH < 32 ? 1 : DH / 32;  // 32-row blocks of a transposed result
-    static constexpr int NT = KL ? 3 : 2;              // tiles per step: Q, G (K, V) and the teacher's
-    static constexpr int NW = DH == 128 && KL ? 2 : 4; // waves
+    static constexpr int NW = 4;                       // waves
     // head_dim 16 reads 32 columns (the upper 16 rows of the result are not used): 16 floats of slack
     static constexpr int TILE = 32 * RST + (DH < 32 ? 16 : 0);
-    static constexpr int WAVE = NT * TILE + 96;        // lse, D and the teacher's lse of the 32 queries
+    static constexpr int WAVE = 2 * TILE + 96;         // Q, G (K, V); lse, D and the teacher's lse of the 32 queries
     static constexpr int LD = DH / 8;                  // 16-byte loads per lane and tile
-    static constexpr bool AHEAD = NW == 4;             // the next tile's loads in registers (else they spill)
+    static constexpr bool AHEAD = !(DH == 128 && KL);  // the next tile's loads in registers (else they spill)
 };
 
 typedef __attribute__((address_space(3))) float lds_f32;
@@ -88,6 +90,19 @@ __device__ inline f32x16 scores(const lds_f32 *t, const f32x4 (&b)[DH / 8], int 
 #pragma unroll
         for (int k = 0; k < 4; ++k) c = mma32(x[k], b[i][k], c);
     }
+    return c;
+}
+// the same from the tile's rows in registers (row_operand of row lane % 32), with the same products in the same
+// order: equal maps give equal scores
+template <int DH>
+__device__ inline f32x16 scores(const f32x4 (&t)[DH / 8], const f32x4 (&b)[DH / 8]) {
+    f32x16 c;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) c[e] = 0.f;
+#pragma unroll
+    for (int i = 0; i < DH / 8; ++i)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) c = mma32(t[i][k], b[i][k], c);
     return c;
 }
 // acc (transposed: registers -> head dimension) += tile^T x s, contracted over the tile's 32 rows
@@ -151,7 +166,7 @@ __global__ __launch_bounds__((64 * F32Cfg<DH, KL>::NW), 1) void attn_bwd_dkdv_f3
     const float *Q = static_cast<const float *>(a.q) + row0 * a.ldq;
     const float *Gr = static_cast<const float *>(a.g) + row0 * Hq * DH;
     const float *Qt = KL ? static_cast<const float *>(a.qt) + row0 * a.ldq : nullptr;
-    lds_f32 *tq = (lds_f32 *)smem + wave * C::WAVE, *tg = tq + C::TILE, *tt = tg + C::TILE, *st = tq + C::NT * C::TILE;
+    lds_f32 *tq = (lds_f32 *)smem + wave * C::WAVE, *tg = tq + C::TILE, *st = tq + 2 * C::TILE;
 
     f32x4 kf[C::LD], vf[C::LD], ktf[KL ? C::LD : 1];
     const bool live = key < T;
@@ -171,26 +186,36 @@ __global__ __launch_bounds__((64 * F32Cfg<DH, KL>::NW), 1) void attn_bwd_dkdv_f3
         const int h = kvh * G + v / nq, i0 = k0 + 32 * (v % nq);
         load_rows<DH>(rq, Q + h * DH, a.ldq, i0, T, lane);
         load_rows<DH>(rg, Gr + h * DH, (int64_t)Hq * DH, i0, T, lane);
-        if constexpr (KL) load_rows<DH>(rt, Qt + h * DH, a.ldq, i0, T, lane);
         const int q = i0 + (lane & 31);
         const int64_t li = ((int64_t)b * Hq + h) * T + q;
         rs = q < T ? (half ? a.D[li] : a.lse2[li]) : (half ? 0.f : INFINITY);
         if constexpr (KL) rl = q < T ? a.lse_t[li] : INFINITY;
     };
-    if (C::AHEAD && wave < n) load(wave);
+    auto load_teacher = [&](int v) {
+        const int h = kvh * G + v / nq, q = k0 + 32 * (v % nq) + (lane & 31);
+        if constexpr (KL) row_operand<DH>(rt, q < T ? Qt + (int64_t)q * a.ldq + h * DH : nullptr, half);
+    };
+    if (C::AHEAD && wave < n) {
+        load(wave);
+        load_teacher(wave);
+    }
     for (int v = wave; v < n; v += C::NW) {
-        if (!C::AHEAD) load(v);
+        if (!C::AHEAD) {
+            load(v);
+            load_teacher(v);
+        }
         wave_lds_fence();                              // the last tile's reads are done
         store_rows<DH>(tq, rq, lane);
         store_rows<DH>(tg, rg, lane);
-        if constexpr (KL) store_rows<DH>(tt, rt, lane);
         st[lane] = rs;
         if (KL && half == 0) st[64 + lane] = rl;
         wave_lds_fence();
         const int i0 = k0 + 32 * (v % nq);
         if (C::AHEAD && v + C::NW < n) load(v + C::NW);
-        f32x16 s = scores<DH>(tq, kf, lane), dp = scores<DH>(tg, vf, lane), sc;
-        if constexpr (KL) sc = scores<DH>(tt, ktf, lane);
+        f32x16 sc;
+        if constexpr (KL) sc = scores<DH>(rt, ktf);
+        if (C::AHEAD && v + C::NW < n) load_teacher(v + C::NW);
+        f32x16 s = scores<DH>(tq, kf, lane), dp = scores<DH>(tg, vf, lane);
         const bool diag = i0 == k0;
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
@@ -243,7 +268,7 @@ __global__ __launch_bounds__((64 * F32Cfg<DH, KL>::NW), 1) void attn_bwd_dq_f32_
     const float *K = static_cast<const float *>(a.k) + row0 * a.ldq + kvh * DH;
     const float *V = static_cast<const float *>(a.v) + row0 * a.ldv + kvh * DH;
     const float *Kt = KL ? static_cast<const float *>(a.kt) + row0 * a.ldq + kvh * DH : nullptr;
-    lds_f32 *tk = (lds_f32 *)smem + wave * C::WAVE, *tv = tk + C::TILE, *tt = tv + C::TILE;
+    lds_f32 *tk = (lds_f32 *)smem + wave * C::WAVE, *tv = tk + C::TILE;
 
     f32x4 qf[C::LD], gf[C::LD], qtf[KL ? C::LD : 1];
     const bool live = qrow < T;
@@ -261,19 +286,29 @@ __global__ __launch_bounds__((64 * F32Cfg<DH, KL>::NW), 1) void attn_bwd_dq_f32_
     auto load = [&](int j) {
         load_rows<DH>(rk, K, a.ldq, 32 * j, T, lane);
         load_rows<DH>(rv, V, a.ldv, 32 * j, T, lane);
-        if constexpr (KL) load_rows<DH>(rt, Kt, a.ldq, 32 * j, T, lane);
     };
-    if (C::AHEAD && wave <= qb) load(wave);
+    auto load_teacher = [&](int j) {
+        const int k = 32 * j + (lane & 31);
+        if constexpr (KL) row_operand<DH>(rt, k < T ? Kt + (int64_t)k * a.ldq : nullptr, half);
+    };
+    if (C::AHEAD && wave <= qb) {
+        load(wave);
+        load_teacher(wave);
+    }
     for (int j = wave; j <= qb; j += C::NW) {
-        if (!C::AHEAD) load(j);
+        if (!C::AHEAD) {
+            load(j);
+            load_teacher(j);
+        }
         wave_lds_fence();                              // the last tile's reads are done
         store_rows<DH>(tk, rk, lane);
         store_rows<DH>(tv, rv, lane);
-        if constexpr (KL) store_rows<DH>(tt, rt, lane);
         wave_lds_fence();
         if (C::AHEAD && j + C::NW <= qb) load(j + C::NW);
-        f32x16 s = scores<DH>(tk, qf, lane), dp = scores<DH>(tv, gf, lane), sc;
-        if constexpr (KL) sc = scores<DH>(tt, qtf, lane);
+        f32x16 sc;
+        if constexpr (KL) sc = scores<DH>(rt, qtf);
+        if (C::AHEAD && j + C::NW <= qb) load_teacher(j + C::NW);
+        f32x16 s = scores<DH>(tk, qf, lane), dp = scores<DH>(tv, gf, lane);
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
             const bool off = j == qb && 32 * j + 8 * (e >> 2) + 4 * half + (e & 3) > qrow;

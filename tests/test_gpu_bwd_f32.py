@@ -1,5 +1,5 @@
-"""GPU parity of the fp32 attention backward, whose waves take every fourth (with the KL term at head_dim
-128 every second) tile of a 32-row block: fewer tiles than waves, one more than a multiple, ragged last
+"""GPU parity of the fp32 attention backward, whose waves take every fourth tile of a
+32-row block: fewer tiles than waves, one more than a multiple, ragged last
 tiles, groups of query heads.  The bars are those of the backward tests (1e-4 relative L2 per matrix
 against the fp64 oracle)."""
 import pytest
