@@ -385,11 +385,15 @@ __global__ __launch_bounds__(256, 1) void attn_jvp_kernel(JvpArgs a, float scale
 // every wave has read block j - 1's values, whose slot takes block j + 3; the first key fragments of
 // block j + 1 are read under those products.
 // As in attn_fast_kernel, a query's reference is the maximum of its first block and stays there (no
-// maximum, compare or branch per block); a query whose row sum then exceeds 2^R, R = 64, or whose sums are
-// not finite repeats the tile with a reference that moves on an overshoot beyond 2^R (infinite for the
-// queries that are not flagged, so their arithmetic is the same in both passes).  The products of
-// probabilities up to 2^64 and logit tangents stay far below the end of the fp32 and bf16 range; fp16,
-// which ends at 2^16, keeps attn_jvp_kernel and its reference that is never exceeded.
+// maximum, compare or branch per block).  A query whose row sum then exceeds 2^R, R = 64, or whose results are not
+// finite takes the maximum over all its blocks instead: its tile reads the keys once more for that maximum (one
+// product per block) and repeats the pass with it, so the probabilities are at most 1, as attn_jvp_kernel's.
+// (The repeat moved a reference on an overshoot beyond 2^R before: probabilities up to 2^64 times the square of a
+// logit tangent left the fp32 range from tangents of 2^31 on, and with the rescale of 256 accumulators in its
+// loop it took three times the first pass: one probe of 4 x 2048 Mistral tokens with every tile repeated 4.65 ms,
+// so 1.64; attn_jvp_kernel 2.30.)
+// Queries that are not flagged keep their reference, so their arithmetic is the same in both passes.  fp16, whose
+// packed operands end at 2^16, keeps attn_jvp_kernel.
 // Measured, attn_jvp_kernel (two passes at head_dim 128, nothing overlapped) / this, us per probe: 4 x 2048
 // with 32 / 8 heads of 128 1457 / 519 (41 % matrix-core busy), 1 x 999 174 / 56, 8 x 1024 with 12 heads of
 // 64 185 / 98.  About 1.4 us per block (56 products, 0.9 us, and 215 + 16 vector operations that share
@@ -501,9 +505,9 @@ __global__ __launch_bounds__(256, 1) void attn_jvp_fast_kernel(JvpArgs a, float 
 
     f32x16 o[C::NDB], uq[C::NDB], uk[C::NDB], wv[C::NDB];
     float m_run, l_run, mq_run, mk_run, cqq, ckk, cqk;
-    float thr = INFINITY;                              // checked pass: the overshoot that moves the reference
+    float ref = -INFINITY;                             // a flagged query's maximum
     f32x16 s, sq, sk;                                  // scores of the next softmax block
-    float mx = 0.f;                                    // ... and their maximum (log2 units)
+    float mx = 0.f;                                    // block 0's maximum (log2 units)
     uint32_t pp[8], pq[8], pk[8];                      // the last softmax block's P, P zQ, P zK, packed
     // the key fragments stream through four registers sets: read f < NKC is K's k-step f, the others Kd's
     constexpr int LA = 3;                              // reads ahead of their products
@@ -557,24 +561,9 @@ __global__ __launch_bounds__(256, 1) void attn_jvp_fast_kernel(JvpArgs a, float 
     typedef std::integral_constant<bool, true> yes;
     typedef std::integral_constant<bool, false> no;
     // phase 1 of block j (VAL: block j - 1's value products; NEXT: block j + 1 is the wave's too)
-    auto phase1 = [&](int j, auto val_c, auto next_c, auto checked_c) {
+    auto phase1 = [&](int j, auto val_c, auto next_c) {
         constexpr bool VAL = decltype(val_c)::value, NEXT = decltype(next_c)::value;
-        constexpr bool CHECKED = decltype(checked_c)::value;
-        // the reference of block j
-        bool moved = false;
-        float alpha = 1.f;
-        if constexpr (!VAL) {
-            m_run = mx;                                // block 0's maximum
-        } else if constexpr (CHECKED) {
-            const bool move = mx > m_run + thr;
-            moved = __any(move);
-            if (moved) {
-                const float m_new = move ? mx : m_run;
-                alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-                l_run *= alpha; mq_run *= alpha; mk_run *= alpha; cqq *= alpha; ckk *= alpha; cqk *= alpha;
-                m_run = m_new;
-            }
-        }
+        if constexpr (!VAL) m_run = fmaxf(mx, ref);    // block 0
         const unsigned char *sv = slot(j - 1);
         opnd vf[2], vdf[2];
         opnd bp[2], bq[2], bk[2];
@@ -638,25 +627,9 @@ __global__ __launch_bounds__(256, 1) void attn_jvp_fast_kernel(JvpArgs a, float 
                 SCHED_FENCE();
             }
         }
-        if (CHECKED && VAL && moved) {
-            // the accumulators still held block j - 1's reference.  In place in the accumulation registers (the compiler's own form would stage
-            // all of them through the architectural ones), in a basic block of its own
-#pragma unroll
-            for (int d = 0; d < C::NDB; ++d)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    auto mul = [&](f32x16 &acc) {
-                        float x = acc[e], y;
-                        asm volatile("v_accvgpr_read_b32 %1, %0\n\tv_mul_f32 %1, %1, %2\n\tv_accvgpr_write_b32 %0, %1"
-                                     : "+a"(x), "=&v"(y) : "v"(alpha));
-                        acc[e] = x;
-                    };
-                    mul(o[d]); mul(uq[d]); mul(uk[d]); mul(wv[d]);
-                }
-        }
     };
 
-    auto tile_pass = [&](auto checked) {
+    auto tile_pass = [&] {
 #pragma unroll
         for (int d = 0; d < C::NDB; ++d)
 #pragma unroll
@@ -672,16 +645,16 @@ __global__ __launch_bounds__(256, 1) void attn_jvp_fast_kernel(JvpArgs a, float 
         for (int f = 0; f < LA; ++f) rd_key(smem, f);
         if (jw == 0) {
             scores(0, yes(), yes());
-            phase1(0, no(), no(), checked);
+            phase1(0, no(), no());
         } else {
             scores(0, no(), yes());
-            phase1(0, no(), yes(), checked);
+            phase1(0, no(), yes());
             for (int j = 1; j < jw; ++j) {
-                scores(j, no(), checked);
-                phase1(j, yes(), yes(), checked);
+                scores(j, no(), no());
+                phase1(j, yes(), yes());
             }
-            scores(jw, yes(), checked);
-            phase1(jw, yes(), no(), checked);
+            scores(jw, yes(), no());
+            phase1(jw, yes(), no());
         }
         {   // the value products of the diagonal block
             const unsigned char *sv = slot(jw);
@@ -702,12 +675,52 @@ __global__ __launch_bounds__(256, 1) void attn_jvp_fast_kernel(JvpArgs a, float 
         }
         wait_vmcnt<0>();                               // no load into LDS outlives the pass
     };
-    tile_pass(no());
+    // the queries' maxima over all their blocks: the keys alone through the ring, as in tile_pass
+    auto max_pass = [&]() -> float {
+        auto issue_keys = [&](int j) {
+#pragma unroll
+            for (int i = 0; i < C::PK; ++i) issue_one(i, j);
+        };
+        float m = -INFINITY;
+        issue_keys(0);
+        issue_keys(1);
+        issue_keys(2);
+        for (int j = 0; j <= jlast; ++j) {
+            wait_lgkm0();                              // block j - 1 is read, block j has landed
+            wait_vmcnt<2 * C::PK>();
+            raw_barrier();
+            issue_keys(j + 3);
+            if (j > jw) continue;
+#pragma unroll
+            for (int f = 0; f < LA; ++f) rd_key(slot(j), f);
+#pragma unroll
+            for (int kc = 0; kc < C::NKC; ++kc) {
+                if (kc + LA < C::NKC) rd_key(slot(j), kc + LA);
+                s = mma_v<DT>(kf[kc % (LA + 1)], qf[kc], s, kc == 0, kc == C::NKC - 1);
+            }
+            const int lim = j == jw ? qrow - 32 * j - 4 * half : 32;
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                if (8 * (e >> 2) + (e & 3) <= lim) m = fmaxf(m, s[e]);
+        }
+        wait_vmcnt<0>();
+        wait_lgkm0();
+        raw_barrier();                                 // every wave is done with the ring
+        return halves_max(m) * scale_log2;
+    };
+    tile_pass();
     {
-        // flagged queries (NaN sums too): the four waves decide together, they share the ring
+        // flagged queries (0 * x is 0 for every finite x and NaN otherwise; NaN sums too): the four waves decide
+        // together, they share the ring.  The tangents' accumulators need no check: past the fp32 range with a
+        // row sum of at most 2^64, their squares are past it too.
         const float l = halves_sum(l_run);
-        const float fin = (mq_run + mk_run) * 0.f + (cqq + ckk + cqk) * 0.f;   // 0, or NaN
-        const bool bad = !(l <= __builtin_exp2f(C::R) && halves_sum(fin) == 0.f) && qrow < T;
+        float nonfin = (halves_sum(mq_run) + halves_sum(mk_run)) * 0.f;
+        nonfin = __builtin_fmaf(halves_sum(cqq) + halves_sum(ckk) + halves_sum(cqk), 0.f, nonfin);
+#pragma unroll
+        for (int d = 0; d < C::NDB; ++d)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) nonfin = __builtin_fmaf(o[d][e], 0.f, nonfin);
+        const bool bad = !(l <= __builtin_exp2f(C::R) && halves_sum(nonfin) == 0.f) && qrow < T;
         int *flags = reinterpret_cast<int *>(smem + C::NS * C::STAGE);
         const int any_bad = __any(bad) ? 1 : 0;
         wait_lgkm0();
@@ -716,8 +729,9 @@ __global__ __launch_bounds__(256, 1) void attn_jvp_fast_kernel(JvpArgs a, float 
         wait_lgkm0();
         raw_barrier();
         if (flags[0] | flags[1] | flags[2] | flags[3]) {
-            thr = bad ? C::R : INFINITY;
-            tile_pass(yes());
+            const float m = max_pass();
+            if (bad) ref = m;
+            tile_pass();
         }
     }
 

@@ -81,7 +81,7 @@ def _curvature(base, hkv, dh, w, x, boost):
 @pytest.mark.parametrize("dh", [64, 128])
 @pytest.mark.parametrize("boost", [1.0, 12.0])
 def test_curvature_head_groups_agree_bitwise(dh, boost):
-    """The tangent kernel's groupings, in the first pass (boost 1) and the checked one (boost 12)."""
+    """The tangent kernel's groupings, in the first pass (boost 1) and the repeated one (boost 12)."""
     for T in LENGTHS:
         base = small(batch=2, seq_len=T, d_model=128, n_heads=4, n_kv_heads=1, head_dim=dh, group_size=64, dtype="bf16")
         x, w = inputs.make_x(base).cuda(), inputs.make_w(base)
@@ -95,7 +95,7 @@ def test_curvature_head_groups_agree_bitwise(dh, boost):
 @pytest.mark.parametrize("hq,hkv,dh", [(4, 1, 128), (2, 2, 64)])
 def test_curvature_checked_pass_matches_oracle(hq, hkv, dh):
     """Small first tokens make every later query overshoot its first block's maximum by more than 2^64:
-    all such tiles take the checked pass.  Bar as test_gpu_curvature's for bf16, 3e-2 of the pooled form:
+    all such tiles are repeated with their maxima.  Bar as test_gpu_curvature's for bf16, 3e-2 of the pooled form:
     the rounding of P zQ (2^-9 of each term) against a nearly one-hot map."""
     wl = small(batch=1, seq_len=130, d_model=128, n_heads=hq, n_kv_heads=hkv, head_dim=dh, group_size=64, dtype="bf16")
     x, w = inputs.make_x(wl), inputs.make_w(wl)

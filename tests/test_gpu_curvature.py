@@ -165,3 +165,22 @@ def test_curvature_to_omega_to_allocation_matches_oracle():
                     assert got == al.allocate(tg, widths, params, budget, floor, method)
                     want = al.allocate(to, widths, params, budget, floor, method)
                     assert got[0] == want[0], (trace, crit, method, budget, got, want)
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+def test_large_tangents_stay_finite(dh):
+    """Logit tangents of 2^40 beside logits within 2^5 (tiny W_Q, huge W_K): a query's squares, times a
+    probability of 2^60 against a reference that stays at the first block's maximum, would leave the fp32
+    range; the forms themselves are far inside it."""
+    wl = small(batch=1, seq_len=160, d_model=128, n_heads=4, n_kv_heads=1, head_dim=dh, group_size=64, dtype="bf16")
+    x, w = inputs.make_x(wl), inputs.make_w(wl)
+    x[:, :32] = (x[:, :32].float() * 2.0 ** -6).to(x.dtype)       # the first block's logits are near 0
+    w[:4 * dh] = (w[:4 * dh].float() * 2.0 ** -34).to(w.dtype)
+    w[4 * dh:5 * dh] = (w[4 * dh:5 * dh].float() * 2.0 ** 36).to(w.dtype)
+    probes = inputs.make_probes(wl, 2, seed=5)
+    parts = ref.curvature_parts(inputs.to_f64(x), inputs.to_f64(w), oracle_problem(wl), probes.numpy(), wl.dtype)
+    got = jab.curvature(jab.problem_of(wl), x.cuda(), w.cuda(), probes.cuda(), 0.0).cpu().numpy()
+    want = ref.curvature_forms(parts, 0.0)
+    assert np.isfinite(got).all(), got
+    err = np.abs(got - want) / np.maximum(np.abs(want), 0.1 * np.abs(want[:, 3:4]))
+    assert err.max() < 3e-2, err
