@@ -190,7 +190,7 @@ hipError_t launch_curv_forms(const double *partials, int64_t n, double *parts, d
 // w_out = the int8 probe (+-1) in the storage dtype
 hipError_t launch_probe_to_dtype(int dtype, const int8_t *probe, int64_t n, void *w_out, hipStream_t st);
 
-// Deterministic reduction of the attention partials [n_sets][B][per_seq][2], one launch: per set the
+// Deterministic reduction of the attention partials [n_sets][B][per_seq][2], one launch or two: per set the
 // sums over its sequences, out[0] = first sum, with stats (at most two sets) out[1] = out[0] * inv[set]
 // and out[2] = second sum; per_seq[b] = first sum of sequence b (NULL to skip).  seq_sums: scratch
 // [n_sets][B][2]; tickets: n_sets ints that an earlier kernel of the stream has set to 0

@@ -7,9 +7,10 @@
 //
 // Each attention wavefront leaves one (sse, sum a^2) pair in fp64.  One wavefront
 // per (set, sequence) sums its pairs with a lane-strided loop and a butterfly in a
-// fixed order; the wavefront of a set that finishes last sums the set's sequences,
-// whichever it is, from what all of them stored, in a fixed order.  The only atomic
-// is that count of finished wavefronts, so the result is bitwise reproducible.
+// fixed order; then one wavefront per set sums the set's sequences in a fixed order:
+// the one that finishes last, whichever it is, from what all of them stored, or for
+// many sequences a second launch's.  The only atomic is the count of finished
+// wavefronts, so the result is bitwise reproducible.
 #include "device_common.h"
 #include "kernels.h"
 
@@ -25,8 +26,49 @@ __device__ inline double load_agent(const double *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// the sequences' sums q [batch][2] of one set (every lane of a wavefront)
+__device__ inline void finish_set(const double *q, int batch, int set, int lane, const ReduceOut &r) {
+    double *o = r.out + set * r.out_stride, *ps = r.per_seq ? r.per_seq + set * r.seq_stride : nullptr;
+    double s0 = 0, s1 = 0;
+    int k = lane;
+    for (; k + 7 * 64 < batch; k += 8 * 64) {
+        double x[8], y[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            x[i] = load_agent(q + 2 * (k + 64 * i));
+            y[i] = load_agent(q + 2 * (k + 64 * i) + 1);
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            s0 += x[i];
+            s1 += y[i];
+            if (ps) ps[k + 64 * i] = x[i];
+        }
+    }
+    for (; k < batch; k += 64) {
+        const double x = load_agent(q + 2 * k), y = load_agent(q + 2 * k + 1);
+        s0 += x;
+        s1 += y;
+        if (ps) ps[k] = x;
+    }
+    s0 = wave_sum_f64(s0);
+    s1 = wave_sum_f64(s1);
+    if (lane == 0) {
+        o[0] = s0;
+        if (r.stats) {
+            o[1] = s0 * r.inv[set];
+            o[2] = s1;
+        }
+    }
+}
+
 // Bound by latency: at 16 x 2048 tokens of 32 heads a wavefront sums 2048 pairs, eight loads in flight.
-// One launch instead of two or three (the smallest kernel takes 5 us of a call): 16 + 5 us before.
+// One launch (tickets) instead of two of 5 us while the wavefronts are few: their counts go one after the
+// other, 11 ns each, whichever set they belong to.  us, one launch / two: 16 sequences of 2048 tokens 6 / 20 (the second
+// launch with its loads one by one), 300 of 97 8.0 / 8.5, 1024 of 33 20.7 / 8.7, 2730 of 24
+// 51 / 11, 8192 of 1 143 / 16, 64 sets of 4096 2770 / 64.
+constexpr int kOneLaunchWaves = 512;
+
 __global__ __launch_bounds__(64) void reduce_kernel(const double *__restrict__ part, int batch, int per_seq,
                                                     double *__restrict__ seq_sums, int *__restrict__ tickets,
                                                     ReduceOut r) {
@@ -56,35 +98,29 @@ __global__ __launch_bounds__(64) void reduce_kernel(const double *__restrict__ p
     if (lane == 0) {
         store_agent(q + 2 * b, s0);
         store_agent(q + 2 * b + 1, s1);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        last = __hip_atomic_fetch_add(tickets + set, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == batch - 1;
+        if (tickets) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            last = __hip_atomic_fetch_add(tickets + set, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == batch - 1;
+        }
     }
     if (!__builtin_amdgcn_readfirstlane(last)) return;
     asm volatile("" ::: "memory");
-    double *o = r.out + set * r.out_stride, *ps = r.per_seq ? r.per_seq + set * r.seq_stride : nullptr;
-    s0 = s1 = 0;
-    for (int k = lane; k < batch; k += 64) {
-        const double x = load_agent(q + 2 * k), y = load_agent(q + 2 * k + 1);
-        s0 += x;
-        s1 += y;
-        if (ps) ps[k] = x;
-    }
-    s0 = wave_sum_f64(s0);
-    s1 = wave_sum_f64(s1);
-    if (lane == 0) {
-        o[0] = s0;
-        if (r.stats) {
-            o[1] = s0 * r.inv[set];
-            o[2] = s1;
-        }
-    }
+    finish_set(q, batch, set, lane, r);
+}
+
+__global__ __launch_bounds__(64) void reduce_sets_kernel(const double *__restrict__ seq_sums, int batch, ReduceOut r) {
+    finish_set(seq_sums + (int64_t)blockIdx.x * batch * 2, batch, blockIdx.x, lane_id(), r);
 }
 
 }  // namespace
 
 hipError_t launch_reduce(const double *partials, int n_sets, int batch, int per_seq, double *seq_sums, int *tickets,
                          const ReduceOut &r, hipStream_t st) {
-    reduce_kernel<<<dim3(batch, n_sets), dim3(64), 0, st>>>(partials, batch, per_seq, seq_sums, tickets, r);
+    const bool one = (int64_t)batch * n_sets <= kOneLaunchWaves;
+    reduce_kernel<<<dim3(batch, n_sets), dim3(64), 0, st>>>(partials, batch, per_seq, seq_sums, one ? tickets : nullptr, r);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || one) return e;
+    reduce_sets_kernel<<<dim3(n_sets), dim3(64), 0, st>>>(seq_sums, batch, r);
     return hipGetLastError();
 }
 

@@ -28,10 +28,12 @@ def test_weight_gradient_parts_match_oracle(shape):
     _check_backward(shape)
 
 
-@pytest.mark.parametrize("B,T", [(1, 1), (1, 33), (63, 8), (64, 8), (65, 8), (3, 1100), (200, 40)])
+@pytest.mark.parametrize("B,T", [(1, 1), (1, 33), (63, 8), (64, 8), (65, 8), (3, 1100), (200, 40), (256, 2), (257, 2),
+                                 (513, 1), (1100, 1)])
 def test_loss_reduction_is_the_sum_of_its_sequences(B, T):
     """out against the per-sequence sums it returns, and those against single-sequence calls, for batches
-    around a wavefront and partial counts around the unrolled loop; the same bits on every call."""
+    around a wavefront and partial counts around the unrolled loops; the same bits on every call.  From 257
+    sequences on the two sets of the KL call take two launches, the loss alone one up to 512: equal bits."""
     wl = small(batch=B, seq_len=T, d_model=64, n_heads=4, n_kv_heads=4, head_dim=16, group_size=32, dtype="bf16")
     x, w = device_inputs(wl)
     p, bits = jab.problem_of(wl), (3, 4, 2)
@@ -43,7 +45,7 @@ def test_loss_reduction_is_the_sum_of_its_sequences(B, T):
     assert torch.equal(jab.loss_fwd(p, x, w, bits, scale, zero, a), out[:3 + B])
     o = out.cpu().numpy()
     n = B * T * 64
-    np.testing.assert_allclose(o[0], o[3:3 + B].sum(), rtol=1e-13)         # fp64 sums of up to 200 terms
+    np.testing.assert_allclose(o[0], o[3:3 + B].sum(), rtol=1e-13)         # fp64 sums of up to 1100 terms
     np.testing.assert_allclose(o[1], o[0] / n, rtol=1e-14)
     np.testing.assert_allclose(o[2], float((a.double() ** 2).sum()), rtol=1e-6)   # fp32 squares per tile
     np.testing.assert_allclose(o[3 + B], o[6 + B:].sum(), rtol=1e-12, atol=1e-12)
