@@ -21,7 +21,7 @@
 //  * Workgroup ids are remapped so that each XCD (ids congruent mod 8 land on the same XCD) walks a
 //    contiguous range of tiles, grouped 8 M-tiles at a time so that concurrently running tiles share A
 //    and B panels in that XCD's L2.
-//  * A projection's [Q|K] and value tiles go in one launch (the value tiles with the operands swapped),
+//  * A projection's [Q|K] and value tiles go in one launch where that pays (the value tiles with the operands swapped),
 //    so that neither part leaves the chip half empty: at 4 x 2048 tokens of d 4096 640 + 128 tiles took
 //    3 + 1 rounds of the 256 CUs, together 3 (372 -> 308 us); at 1 x 1999 160 + 32 tiles 189 -> 92 us,
 //    of which 54 us went into 2-byte stores of the ragged value tiles.
@@ -69,6 +69,7 @@ struct SmallArgs {
     int M, N, K, lda, ldb, ldc;
     int nv, ldv, seq_T, seq_Tp, n_tok;   // values: rows, row stride, sequence length, padded, batch * padded
     float alpha;
+    int pack;                            // OUT_VT: sequences per tile
     int ksplit;                          // OUT_F32: parts of K, part p > 0 at C2 + (p - 1) part_stride
     int64_t part_stride;
     int tiles_m, tiles_n, tiles_vm, tiles_vn;
@@ -124,6 +125,9 @@ __device__ inline f32x16 mma_chunk(u32x4 a, u32x4 b, f32x16 c) {
 // RDH > 0 (128-tile, 16-bit, OUT_DT): the rotary embedding on the [Q|K] tiles, heads of RDH columns, as
 // in gemm_w4p_kernel's epilogue.  A pair (c, c + RDH / 2) has to sit in one wave: at RDH 128 wave
 // column wc takes the 32-column blocks wc and wc + 2 of the tile instead of 2 wc and 2 wc + 1.
+// OUT_VT: the values alone, of sequences of at most 32 tokens: a tile's columns are the tokens of `pack` whole
+// sequences (as many as fit) instead of padded positions, and its outputs are spread to the padded
+// positions, zeros between, through LDS.
 // WIDE: rows of a panel more than 2^32 bytes apart (offsets_fit), so the loads take 64-bit addresses per lane.
 template <int DT, int BT, int CPR, int OUT, int RDH, bool WIDE>
 __global__ __launch_bounds__(256, 2) void gemm_small_kernel(SmallArgs g) {
@@ -141,10 +145,10 @@ __global__ __launch_bounds__(256, 2) void gemm_small_kernel(SmallArgs g) {
     const int n_items = gridDim.x, x = blockIdx.x & 7;
     int pid = x * (n_items >> 3) + min(x, n_items & 7) + (blockIdx.x >> 3);
     const int tiles = g.tiles_m * g.tiles_n;
-    const bool val = OUT == OUT_DT && pid >= tiles;
+    const bool val = OUT == OUT_VT || (OUT == OUT_DT && pid >= tiles);
     int part = 0, tm = g.tiles_m, tn = g.tiles_n;
     if (val) {
-        pid -= tiles;
+        pid -= OUT == OUT_VT ? 0 : tiles;
         tm = g.tiles_vm;
         tn = g.tiles_vn;
     } else if (OUT == OUT_F32) {
@@ -154,7 +158,8 @@ __global__ __launch_bounds__(256, 2) void gemm_small_kernel(SmallArgs g) {
     const int group_tiles = 8 * tn;
     const int first_m = (pid / group_tiles) * 8;
     const int gsz = min(tm - first_m, 8);
-    const int bm0 = (first_m + (pid % group_tiles) % gsz) * BT, bn0 = (pid % group_tiles) / gsz * BT;
+    const int bm0 = (first_m + (pid % group_tiles) % gsz) * BT;
+    const int bn0 = (pid % group_tiles) / gsz * (OUT == OUT_VT ? g.pack * g.seq_T : BT);   // OUT_VT: a token
     const int nkt = g.K / S::BK;
     const int kt0 = part * nkt / g.ksplit, nk = (part + 1) * nkt / g.ksplit - kt0;
 
@@ -165,11 +170,13 @@ __global__ __launch_bounds__(256, 2) void gemm_small_kernel(SmallArgs g) {
     const elem *Ap = static_cast<const elem *>(val ? g.B : g.A) + (val ? (int64_t)g.N * lda : 0);
     const elem *Bp = static_cast<const elem *>(val ? g.A : g.B);
     const int rows_a = val ? g.nv : g.M;
+    const int n_pos = OUT == OUT_VT ? g.M : g.n_tok;
     auto token = [&](int n) -> int {          // source row of padded position n
+        if constexpr (OUT == OUT_VT) return n;
         const int s = n / g.seq_Tp;
         return s * g.seq_T + min(n - s * g.seq_Tp, g.seq_T - 1);
     };
-    const int rb0 = val ? token(min(bn0, g.n_tok - 1)) : bn0;
+    const int rb0 = val ? token(min(bn0, n_pos - 1)) : bn0;
     const elem *Ab = Ap + (int64_t)bm0 * lda + (int64_t)kt0 * S::BK, *Bb = Bp + (int64_t)rb0 * ldb + (int64_t)kt0 * S::BK;
     const i32x4 rsA = buffer_rsrc(Ab), rsB = buffer_rsrc(Bb);
     typedef typename std::conditional<WIDE, uint64_t, uint32_t>::type off_t;
@@ -178,7 +185,7 @@ __global__ __launch_bounds__(256, 2) void gemm_small_kernel(SmallArgs g) {
     for (int i = 0; i < S::DPP; ++i) {
         const int r = S::RPI * (wave + 4 * i) + lane / CPR, c = (lane % CPR) ^ w4_key<CPR>(r);
         const int ra = min(bm0 + r, rows_a - 1) - bm0;
-        const int rb = (val ? token(min(bn0 + r, g.n_tok - 1)) : min(bn0 + r, g.N - 1)) - rb0;
+        const int rb = (val ? token(min(bn0 + r, n_pos - 1)) : min(bn0 + r, g.N - 1)) - rb0;
         voffA[i] = (off_t)ra * (off_t)lda * (off_t)S::ES + (off_t)(c * 16);
         voffB[i] = (off_t)rb * (off_t)ldb * (off_t)S::ES + (off_t)(c * 16);
     }
@@ -242,6 +249,45 @@ __global__ __launch_bounds__(256, 2) void gemm_small_kernel(SmallArgs g) {
         slot = slot == S::NS - 1 ? 0 : slot + 1;
     }
     wait_vmcnt<0>();
+
+    if constexpr (OUT == OUT_VT) {
+        // the tile as [BT value rows][BT tokens] in LDS (16-byte chunks XOR-swizzled per row), then whole rows of
+        // padded positions: positions 16 p + 8 h + 4 b + 0..3 of a sequence hold tokens 16 p + 8 b + 4 h + 0..3
+        static_assert((size_t)BT * BT * S::ES <= S::LDS_BYTES, "the tile in the ring's LDS");
+        constexpr int CB = BT / S::EPC;                    // chunks per row
+        raw_barrier();                                     // every wave has left the ring
+        auto at = [&](int row, int col) -> elem * {
+            const int ch = (col / S::EPC) ^ (row & (CB < 16 ? CB - 1 : 15));
+            return reinterpret_cast<elem *>(smem) + row * BT + ch * S::EPC + col % S::EPC;
+        };
+#pragma unroll
+        for (int i = 0; i < S::FB; ++i)
+#pragma unroll
+            for (int j = 0; j < S::FB; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    *at(wr * (BT / 2) + 32 * i + l32, 32 * (S::FB * wc + j) + 8 * (e >> 2) + 4 * half + (e & 3)) =
+                        from_f32<DT>(acc[i][j][e]);
+        __syncthreads();
+        const int T = g.seq_T, seq0 = bn0 / T, ns = min(g.pack, g.M / T - seq0);
+        constexpr int CPS = 32 / S::EPC;                   // chunks of a sequence's 32 positions
+        for (int r = wave; r < min(BT, rows_a - bm0); r += 4) {
+            elem *crow = static_cast<elem *>(g.C2) + (int64_t)(bm0 + r) * g.ldv + (int64_t)seq0 * 32;
+            for (int c = lane; c < ns * CPS; c += 64) {
+                const int sq = c / CPS, p0 = (c % CPS) * S::EPC;
+                elem v[S::EPC];
+#pragma unroll
+                for (int k = 0; k < S::EPC; ++k) {
+                    const int t = vt_perm(p0 + k);
+                    v[k] = t < T ? *at(r, sq * T + t) : elem(0);
+                }
+                u32x4 o;
+                __builtin_memcpy(&o, v, 16);
+                *reinterpret_cast<u32x4 *>(crow + (int64_t)c * S::EPC) = o;
+            }
+        }
+        return;
+    }
 
     // ---- epilogue from registers: acc[i][j][4 q + t] = C[row][col + t], row = 32 i + l32, col =
     // 32 (CB0 wc + CBJ j) + 8 q + 4 half (tile coordinates); 16 bytes per lane and store
@@ -856,6 +902,12 @@ struct Gemm {
     const float4 *rtab = nullptr;
 };
 
+// sequences whose tokens fit in a tile's columns (OUT_VT of the small-tile kernel)
+int packed(const Gemm &g, int bt) { return bt / g.seq_T; }
+int packed_tiles(const Gemm &g, int bt) {
+    return (g.nv + bt - 1) / bt * ((g.M / g.seq_T + packed(g, bt) - 1) / packed(g, bt));
+}
+
 template <int DT, int OUT, int RDH = 0>
 hipError_t run_gemm_w4p(const Gemm &g, hipStream_t st) {
     constexpr int CPR = 8;
@@ -918,11 +970,15 @@ hipError_t run_gemm_small_cfg(const Gemm &g, hipStream_t st) {
     a.tiles_n = g.C ? (g.N + BT - 1) / BT : 0;
     a.tiles_vm = (g.nv + BT - 1) / BT;
     a.tiles_vn = (g.n_tok + BT - 1) / BT;
+    if (OUT == OUT_VT) {
+        a.pack = packed(g, BT);
+        a.tiles_vn = (g.M / g.seq_T + a.pack - 1) / a.pack;
+    }
     a.rtab = g.rtab;
     hipError_t e = hipFuncSetAttribute((const void *)gemm_small_kernel<DT, BT, CPR, OUT, RDH, WIDE>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::LDS_BYTES);
     if (e != hipSuccess) return e;
-    const int n = a.tiles_m * a.tiles_n * g.ksplit + (OUT == OUT_DT ? a.tiles_vm * a.tiles_vn : 0);
+    const int n = a.tiles_m * a.tiles_n * g.ksplit + (OUT == OUT_F32 ? 0 : a.tiles_vm * a.tiles_vn);
     if (n == 0) return hipSuccess;
     gemm_small_kernel<DT, BT, CPR, OUT, RDH, WIDE><<<dim3(n), dim3(256), S::LDS_BYTES, st>>>(a);
     return hipGetLastError();
@@ -944,8 +1000,10 @@ hipError_t run_gemm_small(const Gemm &g, hipStream_t st) {
         return g.K % 64 == 0 ? run_gemm_small_cfg<DT, 128, 8, OUT, RDH>(g, st)
                              : run_gemm_small_cfg<DT, 128, 4, OUT, RDH>(g, st);
     } else {
-        if (!offsets_fit(g, 64)) return run_gemm_small_cfg<DT, 64, 4, OUT, 0, true>(g, st);
-        const bool big = tiles_of(g, 128) >= (DT == F32 ? 8 : 1) * CUS && offsets_fit(g, 128);
+        if constexpr (OUT != OUT_VT)
+            if (!offsets_fit(g, 64)) return run_gemm_small_cfg<DT, 64, 4, OUT, 0, true>(g, st);
+        const int tiles = OUT == OUT_VT ? packed_tiles(g, 128) : tiles_of(g, 128);
+        const bool big = tiles >= (DT == F32 ? 8 : 1) * CUS && offsets_fit(g, 128);
         if constexpr (DT != F32)
             if (g.K % 64 != 0)
                 return big ? run_gemm_small_cfg<DT, 128, 4, OUT>(g, st) : run_gemm_small_cfg<DT, 64, 4, OUT>(g, st);
@@ -1043,16 +1101,33 @@ bool qk_persistent(const Gemm &g) { return persistent_fits<OUT_DT>(g) && persist
 // launch of its own keeps the values' k-tile rotation and the [Q|K] tile queue (from 32 rounds on).
 // Measured, one launch / two, us, at d 4096, 5120 + 1024 columns: 8 K tokens 307 / 371, 16 K 611 / 612,
 // 32 K 1203 / 1212, 64 K (24 rounds) 2450 / 2510.  Sequences that are not whole blocks of 32 tokens
-// always go together: only this form takes them
+// go together where this form takes them (256 value rows); else their values go to the small tiles
 bool qkv_persistent(const Gemm &g) {
     return qk_persistent(g) && persistent_fits<OUT_QKV>(g) &&
            (g.seq_Tp != g.seq_T || tiles_of(g, 256) <= 24 * CUS);
 }
 }  // namespace
 
+namespace {
+// Values of very short sequences over their tokens, several sequences per tile, instead of over padded positions:
+// in a launch of their own, whose tiles run at a little over half of the 256-tile's rate (fp32: four fifths of
+// the 128-tile's).  Where the products left out (with that factor) are worth 20 us: 24 GFLOP at 1.2 PFLOP/s, fp32 a tenth.  Measured,
+// us of the projection, padded / packed (and the 256-tiles over tokens, single stores and a zeroing pass that padded
+// positions replaced): d 4096, 1024 value rows, 8192 x 1 token 1912 / 430 (1109), 4096 x 8 1814 / 1402 (1529),
+// 2048 x 16 1445 / 1395 (1364), 2048 x 20 1728 / 1806, 256 x 1 97 / 62, 64 x 1 42 / 55; d 768, 4096 x 8 229 / 166,
+// 2048 x 16 158 / 176; in fp32 4096 x 1 1347 / 180 (412), 1024 x 16 597 / 486 (537), 64 x 1 31 / 56.
+bool pack_pays(const Gemm &g) {
+    if (g.seq_T > 32 || g.nv == 0 || !offsets_fit(g, 128)) return false;
+    const int64_t tiles = (g.M / g.seq_T + packed(g, 128) - 1) / packed(g, 128);
+    const double saved = ((double)g.n_tok - (g.dtype == F32 ? 1.25 : 1.75) * 128 * (double)tiles) * 2.0 * g.nv * g.K;
+    return saved >= (g.dtype == F32 ? 2.4e9 : 2.4e10);
+}
+}  // namespace
+
 bool project_is_one_launch(int dtype, int batch, int seq_T, int nqk, int nv, int K, int ldv) {
     char some = 0;                                    // tiles count where there is an output
     const Gemm g = projection(dtype, nullptr, nullptr, &some, &some, batch, seq_T, nqk, nv, K, ldv, nullptr);
+    if (pack_pays(g)) return false;
     return qk_persistent(g) ? qkv_persistent(g) : true;
 }
 
@@ -1064,7 +1139,8 @@ hipError_t launch_project(int dtype, const void *x, const void *w, void *qk, voi
         Gemm t{dtype, static_cast<const char *>(w) + (size_t)nqk * K * (dtype == F32 ? 4 : 2), x, vt, nv, M, K, K, K, ldv};
         t.seq_T = seq_T; t.seq_Tp = (seq_T + 31) / 32 * 32;
         if (persistent_fits<OUT_VT>(t) && persistent_pays(t)) return persistent<OUT_VT>(t, st);
-        return small<OUT_DT>(projection(dtype, x, w, nullptr, vt, batch, seq_T, nqk, nv, K, ldv, nullptr), st);
+        const Gemm g = projection(dtype, x, w, nullptr, vt, batch, seq_T, nqk, nv, K, ldv, nullptr);
+        return pack_pays(g) ? small<OUT_VT>(g, st) : small<OUT_DT>(g, st);
     }
     const bool rope = rope_tab_t != nullptr;
     if (rope && (!gemm_rope_fuses(dtype, head_dim) || nqk % head_dim != 0)) return hipErrorInvalidValue;

@@ -1,5 +1,5 @@
 """GPU projection on every route of the GEMM dispatch (64-, 128- and 256-tiles, one launch or two, whole
-and ragged sequences, with and without the rotary embedding) against an fp32 product.
+and ragged sequences, values of very short ones packed, with and without the rotary embedding) against an fp32 product.
 
 [Q|K] comes back from ``attn_ref_kl``: one rounding of the fp32 sum to the dtype (half an ulp, at most
 2^-8 or 2^-11 of the value) plus the sum's own error (d terms, the two products summed in other orders).  V^T is
@@ -31,6 +31,11 @@ ROUTES = [
     (1, 4096, 512, 32, 8, 64, "bf16", 0.0),       # 256-tiles, one launch, whole sequences
     (5, 777, 512, 32, 8, 64, "bf16", 0.0),        # 256-tiles, one launch, ragged: tiles span sequences
     (70, 45, 576, 40, 5, 64, "f16", 0.0),         # ... short sequences, ragged last tiles both ways
+    (3001, 7, 512, 8, 8, 64, "bf16", 0.0),        # values over packed sequences, 18 per tile, a last tile of 13
+    (3000, 3, 544, 10, 5, 64, "f16", 1e4),        # ... ragged value rows, k-tiles of 32, rotary queries and keys
+    (4001, 16, 2048, 16, 16, 64, "bf16", 0.0),    # ... 8 per tile, the longest that pays
+    (1001, 5, 256, 16, 16, 16, "f32", 0.0),       # ... fp32
+    (2500, 1, 512, 4, 4, 64, "f32", 0.0),         # ... one token
     (1, 65, 128, 4, 1, 128, "bf16", 1e4),         # rotary 128-tile, head_dim 128
     (2, 77, 96, 8, 4, 64, "f16", 1e4),            # rotary 128-tile, head_dim 64, k-tiles of 32
     (5, 777, 512, 32, 8, 64, "bf16", 1e4),        # rotary 256-tiles, ragged, head_dim 64
