@@ -4,8 +4,8 @@
 // What bounds it: the fp32 matrix instructions (32x32x2, 64 cycles for 2 k-steps): a 32 x 32 tile at
 // head_dim 64 takes 128 of them for dK/dV, 3.5 us in one wave, so the length of a wave's chain of tiles
 // decides at the sizes fp32 is used at.  A workgroup therefore owns one 32-row block (keys of a kv head, or
-// queries of a head) and its waves take every NW-th tile that block meets; the sums are added in LDS
-// at the end, in wave order.  A wave stages its own tiles, row-major, with the next tile's global loads
+// queries of a head) and its NW waves (four, or one: one_wave) take every NW-th tile that block meets; the sums
+// are added in LDS at the end, in wave order.  A wave stages its own tiles, row-major, with the next tile's global loads
 // in registers while it computes: no barrier in the loop.  The products that contract over tokens read
 // the same tiles column by column (one float per lane, 32 consecutive addresses), so no transposed copy is kept.
 // The teacher's tile of the KL term enters one score product alone, so it stays in registers as that product's
@@ -26,7 +26,6 @@ template <int DH, bool KL>
 struct F32Cfg {
     static constexpr int RST = DH + 4;                 // floats per tile row
     static constexpr int NDB = DH < 32 ? 1 : DH / 32;  // 32-row blocks of a transposed result
-    static constexpr int NW = 4;                       // waves
     // head_dim 16 reads 32 columns (the upper 16 rows of the result are not used): 16 floats of slack
     static constexpr int TILE = 32 * RST + (DH < 32 ? 16 : 0);
     static constexpr int WAVE = 2 * TILE + 96;         // Q, G (K, V); lse, D and the teacher's lse of the 32 queries
@@ -142,17 +141,17 @@ __device__ inline void block_and_head(int nblocks, int &blk, int &head) {
     head = x * per + i % per;
 }
 
-template <int DH, bool KL>
+template <int DH, bool KL, int NW>
 constexpr size_t f32_lds_bytes(int sums) {
     typedef F32Cfg<DH, KL> C;
-    const size_t tiles = (size_t)C::NW * C::WAVE, ex = (size_t)(C::NW - 1) * sums * C::NDB * 1024;
+    const size_t tiles = (size_t)NW * C::WAVE, ex = (size_t)(NW - 1) * sums * C::NDB * 1024;
     return (tiles > ex ? tiles : ex) * sizeof(float);
 }
 
 // dK^T and dV^T of the 32 keys of block kb of one kv head
-template <int DH, bool KL>
-__global__ __launch_bounds__((64 * F32Cfg<DH, KL>::NW), 1) void attn_bwd_dkdv_f32_kernel(AttnBwdArgs a, float scale_log2,
-                                                                                     float inv_sqrt, int nkb) {
+template <int DH, bool KL, int NW>
+__global__ __launch_bounds__(64 * NW, 1) void attn_bwd_dkdv_f32_kernel(AttnBwdArgs a, float scale_log2, float inv_sqrt,
+                                                                      int nkb) {
     typedef F32Cfg<DH, KL> C;
     extern __shared__ __align__(16) unsigned char smem[];
     const int T = a.seq_len, Hq = a.n_heads, Hkv = a.n_kv_heads, G = Hq / Hkv;
@@ -199,7 +198,7 @@ __global__ __launch_bounds__((64 * F32Cfg<DH, KL>::NW), 1) void attn_bwd_dkdv_f3
         load(wave);
         load_teacher(wave);
     }
-    for (int v = wave; v < n; v += C::NW) {
+    for (int v = wave; v < n; v += NW) {
         if (!C::AHEAD) {
             load(v);
             load_teacher(v);
@@ -211,10 +210,10 @@ __global__ __launch_bounds__((64 * F32Cfg<DH, KL>::NW), 1) void attn_bwd_dkdv_f3
         if (KL && half == 0) st[64 + lane] = rl;
         wave_lds_fence();
         const int i0 = k0 + 32 * (v % nq);
-        if (C::AHEAD && v + C::NW < n) load(v + C::NW);
+        if (C::AHEAD && v + NW < n) load(v + NW);
         f32x16 sc;
         if constexpr (KL) sc = scores<DH>(rt, ktf);
-        if (C::AHEAD && v + C::NW < n) load_teacher(v + C::NW);
+        if (C::AHEAD && v + NW < n) load_teacher(v + NW);
         f32x16 s = scores<DH>(tq, kf, lane), dp = scores<DH>(tg, vf, lane);
         const bool diag = i0 == k0;
 #pragma unroll
@@ -235,7 +234,7 @@ __global__ __launch_bounds__((64 * F32Cfg<DH, KL>::NW), 1) void attn_bwd_dkdv_f3
         accumulate<DH>(dvt, tg, s, lane);
         accumulate<DH>(dkt, tq, dp, lane);
     }
-    add_waves<C::NW>(acc, (lds_f32 *)smem, wave, lane);
+    add_waves<NW>(acc, (lds_f32 *)smem, wave, lane);
     if (wave > 0 || !live) return;
     float *dyt = static_cast<float *>(a.dyt) + row0 + key;
     const int koff = Hq * DH + kvh * DH, voff = (Hq + Hkv) * DH + kvh * DH;
@@ -251,9 +250,9 @@ __global__ __launch_bounds__((64 * F32Cfg<DH, KL>::NW), 1) void attn_bwd_dkdv_f3
 }
 
 // dQ^T of the 32 queries of one block of one head
-template <int DH, bool KL>
-__global__ __launch_bounds__((64 * F32Cfg<DH, KL>::NW), 1) void attn_bwd_dq_f32_kernel(AttnBwdArgs a, float scale_log2,
-                                                                                   float inv_sqrt, int nqb) {
+template <int DH, bool KL, int NW>
+__global__ __launch_bounds__(64 * NW, 1) void attn_bwd_dq_f32_kernel(AttnBwdArgs a, float scale_log2, float inv_sqrt,
+                                                                    int nqb) {
     typedef F32Cfg<DH, KL> C;
     extern __shared__ __align__(16) unsigned char smem[];
     const int T = a.seq_len, Hq = a.n_heads, Hkv = a.n_kv_heads, G = Hq / Hkv;
@@ -295,7 +294,7 @@ __global__ __launch_bounds__((64 * F32Cfg<DH, KL>::NW), 1) void attn_bwd_dq_f32_
         load(wave);
         load_teacher(wave);
     }
-    for (int j = wave; j <= qb; j += C::NW) {
+    for (int j = wave; j <= qb; j += NW) {
         if (!C::AHEAD) {
             load(j);
             load_teacher(j);
@@ -304,10 +303,10 @@ __global__ __launch_bounds__((64 * F32Cfg<DH, KL>::NW), 1) void attn_bwd_dq_f32_
         store_rows<DH>(tk, rk, lane);
         store_rows<DH>(tv, rv, lane);
         wave_lds_fence();
-        if (C::AHEAD && j + C::NW <= qb) load(j + C::NW);
+        if (C::AHEAD && j + NW <= qb) load(j + NW);
         f32x16 sc;
         if constexpr (KL) sc = scores<DH>(rt, qtf);
-        if (C::AHEAD && j + C::NW <= qb) load_teacher(j + C::NW);
+        if (C::AHEAD && j + NW <= qb) load_teacher(j + NW);
         f32x16 s = scores<DH>(tk, qf, lane), dp = scores<DH>(tv, gf, lane);
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
@@ -324,7 +323,7 @@ __global__ __launch_bounds__((64 * F32Cfg<DH, KL>::NW), 1) void attn_bwd_dq_f32_
         }
         accumulate<DH>(dqt, tk, dp, lane);
     }
-    add_waves<C::NW>(dqt, (lds_f32 *)smem, wave, lane);
+    add_waves<NW>(dqt, (lds_f32 *)smem, wave, lane);
     if (wave > 0 || !live) return;
     float *dyt = static_cast<float *>(a.dyt) + row0 + qrow;
 #pragma unroll
@@ -359,34 +358,49 @@ AttnBwdArgs sequences(const AttnBwdArgs &a, int b0, int n) {
     return s;
 }
 
+// Whether a block's tiles go to one wave, in a workgroup of its own, or to four: one where the blocks fill the
+// chip's waves (one per SIMD) anyway, since four leave waves without a tile at each block's end and in every block
+// of few tiles, and add their sums.  In times of a tile: the longest block, or all tiles over 4 x 256 waves
+// (0.8 of a tile per block for its start and end); four waves' steps over 256 workgroups (1.3 per block).  shared:
+// the kernel's registers let two such workgroups share a CU, which hides more of theirs.
+// us, four waves / one (and 128-row workgroups before): dK/dV GPT-2 1000 x 33 tokens 1207 / 319 (707), 100 x 100
+// 244 / 100 (156), 8 x 512 132 / 99 (196), 3 x 333 39 / 62 (76); 32 / 8 heads of 128 64 x 33 117 / 89 (173),
+// 16 x 100 83 / 159 (181), 8 x 512 403 / 637 (695).  dQ GPT-2 1000 x 33 480 / 225 (536), 20 x 333 103 / 83
+// (152), 8 x 512 76 / 94 (152); heads of 128 64 x 33 222 / 80 (128), 16 x 100 122 / 56 (97)
+bool one_wave(int nb, int G, int64_t heads, bool shared) {
+    const double n = nb, tiles = G * n * (n + 1) / 2, part = G % 4 == 0 ? 0.0 : G == 2 ? 0.25 : 0.375;
+    const double one = std::max(G * n + 0.8, heads * (tiles + 0.8 * n) / (shared ? 1.25 * 1024 : 1024));
+    const double four = std::max(G * n / 4 + 1.3, heads * (tiles / 4 + (part + 1.3) * n) / (shared ? 1.9 * 256 : 256));
+    return one < 0.9 * four;
+}
+
 template <int DH, bool KL>
 hipError_t run(const AttnBwdArgs &a, hipStream_t st) {
-    constexpr size_t kv_lds = f32_lds_bytes<DH, KL>(2), q_lds = f32_lds_bytes<DH, KL>(1);
-    static_assert(kv_lds <= 160 * 1024 && q_lds <= 160 * 1024, "LDS");
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)DH);
     const float inv_sqrt = 1.f / sqrtf((float)DH);
     const int nb = (a.seq_len + 31) / 32;
-    const dim3 block(64 * F32Cfg<DH, KL>::NW);
-    hipError_t e = hipFuncSetAttribute((const void *)attn_bwd_dkdv_f32_kernel<DH, KL>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kv_lds);
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute((const void *)attn_bwd_dq_f32_kernel<DH, KL>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)q_lds);
-    if (e != hipSuccess) return e;
-    // a grid holds below 2^32 threads, so many heads of many sequences go in several launches
-    const int64_t most = (((int64_t)1 << 32) - 1) / (int64_t)block.x;
-    auto launch = [&](auto kernel, int heads, size_t lds) -> hipError_t {
+    // (a grid holds below 2^32 threads, so many heads of many sequences go in several launches)
+    auto launch = [&](auto kernel, int waves, int heads, size_t lds) -> hipError_t {
+        hipError_t err = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        const int64_t most = (((int64_t)1 << 32) - 1) / (64 * waves);
         const int step = (int)std::max<int64_t>(1, most / ((int64_t)nb * heads));
-        for (int b0 = 0; b0 < a.batch; b0 += std::min(step, a.batch - b0)) {
+        for (int b0 = 0; err == hipSuccess && b0 < a.batch; b0 += std::min(step, a.batch - b0)) {
             const int n = std::min(step, a.batch - b0);
-            kernel<<<dim3(nb * heads * n), block, lds, st>>>(sequences<KL>(a, b0, n), scale_log2, inv_sqrt, nb);
-            const hipError_t err = hipGetLastError();
-            if (err != hipSuccess) return err;
+            kernel<<<dim3(nb * heads * n), dim3(64 * waves), lds, st>>>(sequences<KL>(a, b0, n), scale_log2, inv_sqrt, nb);
+            err = hipGetLastError();
         }
-        return hipSuccess;
+        return err;
     };
-    e = launch(attn_bwd_dkdv_f32_kernel<DH, KL>, a.n_kv_heads, kv_lds);
-    return e == hipSuccess ? launch(attn_bwd_dq_f32_kernel<DH, KL>, a.n_heads, q_lds) : e;
+    static_assert(f32_lds_bytes<DH, KL, 4>(2) <= 160 * 1024, "LDS");
+    const int G = a.n_heads / a.n_kv_heads;
+    const hipError_t e =
+        one_wave(nb, G, (int64_t)a.n_kv_heads * a.batch, false)
+            ? launch(attn_bwd_dkdv_f32_kernel<DH, KL, 1>, 1, a.n_kv_heads, f32_lds_bytes<DH, KL, 1>(2))
+            : launch(attn_bwd_dkdv_f32_kernel<DH, KL, 4>, 4, a.n_kv_heads, f32_lds_bytes<DH, KL, 4>(2));
+    if (e != hipSuccess) return e;
+    return one_wave(nb, 1, (int64_t)a.n_heads * a.batch, DH == 16 || (DH == 64 && !KL))
+               ? launch(attn_bwd_dq_f32_kernel<DH, KL, 1>, 1, a.n_heads, f32_lds_bytes<DH, KL, 1>(1))
+               : launch(attn_bwd_dq_f32_kernel<DH, KL, 4>, 4, a.n_heads, f32_lds_bytes<DH, KL, 4>(1));
 }
 
 }  // namespace

@@ -1,6 +1,6 @@
-"""GPU parity of the fp32 attention backward, whose waves take every fourth tile of a
-32-row block: fewer tiles than waves, one more than a multiple, ragged last
-tiles, groups of query heads.  The bars are those of the backward tests (1e-4 relative L2 per matrix
+"""GPU parity of the fp32 attention backward, whose waves take every fourth tile of a 32-row block, or all of them
+where many blocks of few tiles fill the chip: fewer tiles than waves, one more than a multiple, ragged last tiles,
+groups of query heads.  The bars are those of the backward tests (1e-4 relative L2 per matrix
 against the fp64 oracle)."""
 import pytest
 import torch
@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dh", [16, 64, 128])
-@pytest.mark.parametrize("B,T,hq,hkv", [(1, 20, 2, 2), (2, 33, 4, 2), (1, 161, 2, 2), (1, 130, 4, 1), (8, 64, 2, 1)])
+@pytest.mark.parametrize("B,T,hq,hkv", [(1, 20, 2, 2), (2, 33, 4, 2), (1, 161, 2, 2), (1, 130, 4, 1), (8, 64, 2, 1),
+                                        (150, 40, 4, 4), (130, 70, 8, 2)])
 def test_fp32_backward_matches_oracle(B, T, hq, hkv, dh):
     shape = (B, T, 64, hq, hkv, dh, 32, "f32")
     _check_backward(shape)
