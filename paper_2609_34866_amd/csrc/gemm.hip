@@ -125,7 +125,7 @@ __device__ inline f32x16 mma_chunk(u32x4 a, u32x4 b, f32x16 c) {
 // RDH > 0 (128-tile, 16-bit, OUT_DT): the rotary embedding on the [Q|K] tiles, heads of RDH columns, as
 // in gemm_w4p_kernel's epilogue.  A pair (c, c + RDH / 2) has to sit in one wave: at RDH 128 wave
 // column wc takes the 32-column blocks wc and wc + 2 of the tile instead of 2 wc and 2 wc + 1.
-// OUT_VT: the values alone, of sequences of at most 32 tokens: a tile's columns are the tokens of `pack` whole
+// OUT_VT: the values alone, of sequences that fit in a tile's columns: a tile's columns are the tokens of `pack` whole
 // sequences (as many as fit) instead of padded positions, and its outputs are spread to the padded
 // positions, zeros between, through LDS.
 // WIDE: rows of a panel more than 2^32 bytes apart (offsets_fit), so the loads take 64-bit addresses per lane.
@@ -270,11 +270,11 @@ __global__ __launch_bounds__(256, 2) void gemm_small_kernel(SmallArgs g) {
                         from_f32<DT>(acc[i][j][e]);
         __syncthreads();
         const int T = g.seq_T, seq0 = bn0 / T, ns = min(g.pack, g.M / T - seq0);
-        constexpr int CPS = 32 / S::EPC;                   // chunks of a sequence's 32 positions
+        const uint32_t cps = (uint32_t)g.seq_Tp / S::EPC;  // chunks of a sequence's positions
         for (int r = wave; r < min(BT, rows_a - bm0); r += 4) {
-            elem *crow = static_cast<elem *>(g.C2) + (int64_t)(bm0 + r) * g.ldv + (int64_t)seq0 * 32;
-            for (int c = lane; c < ns * CPS; c += 64) {
-                const int sq = c / CPS, p0 = (c % CPS) * S::EPC;
+            elem *crow = static_cast<elem *>(g.C2) + (int64_t)(bm0 + r) * g.ldv + (int64_t)seq0 * g.seq_Tp;
+            for (uint32_t c = lane; c < ns * cps; c += 64) {
+                const int sq = (int)(c / cps), p0 = (int)(c % cps) * S::EPC;
                 elem v[S::EPC];
 #pragma unroll
                 for (int k = 0; k < S::EPC; ++k) {
@@ -992,7 +992,8 @@ int tiles_of(const Gemm &g, int bt) {
 // The 128-tile from one tile per CU on for the 16-bit dtypes (measured, 64-tile against 128-tile, us:
 // K 768, 144 tiles 13.0 / 13.0, 288 18.6 / 18.6, 342 21.4 / 19.1; K 4096, 192 41.5 / 42.0, 384 76 / 61;
 // at 48 tiles of K 4096 20 / 39) and from eight per CU for fp32 (whose 64-tile fills the matrix cores
-// too: 576 tiles 128 / 155, 2304 442 / 433)
+// too: 576 tiles 128 / 155, 2304 442 / 433); packed sequences of more than 32 tokens fit the 64-tile once, the
+// 128-tile up to three times
 template <int DT, int OUT, int RDH>
 hipError_t run_gemm_small(const Gemm &g, hipStream_t st) {
     if (g.K % 32 != 0) return hipErrorInvalidValue;
@@ -1003,7 +1004,7 @@ hipError_t run_gemm_small(const Gemm &g, hipStream_t st) {
         if constexpr (OUT != OUT_VT)
             if (!offsets_fit(g, 64)) return run_gemm_small_cfg<DT, 64, 4, OUT, 0, true>(g, st);
         const int tiles = OUT == OUT_VT ? packed_tiles(g, 128) : tiles_of(g, 128);
-        const bool big = tiles >= (DT == F32 ? 8 : 1) * CUS && offsets_fit(g, 128);
+        const bool big = (tiles >= (DT == F32 ? 8 : 1) * CUS || (OUT == OUT_VT && g.seq_T > 32)) && offsets_fit(g, 128);
         if constexpr (DT != F32)
             if (g.K % 64 != 0)
                 return big ? run_gemm_small_cfg<DT, 128, 4, OUT>(g, st) : run_gemm_small_cfg<DT, 64, 4, OUT>(g, st);
@@ -1115,9 +1116,10 @@ namespace {
 // us of the projection, padded / packed (and the 256-tiles over tokens, single stores and a zeroing pass that padded
 // positions replaced): d 4096, 1024 value rows, 8192 x 1 token 1912 / 430 (1109), 4096 x 8 1814 / 1402 (1529),
 // 2048 x 16 1445 / 1395 (1364), 2048 x 20 1728 / 1806, 256 x 1 97 / 62, 64 x 1 42 / 55; d 768, 4096 x 8 229 / 166,
-// 2048 x 16 158 / 176; in fp32 4096 x 1 1347 / 180 (412), 1024 x 16 597 / 486 (537), 64 x 1 31 / 56.
+// 2048 x 16 158 / 176; in fp32 4096 x 1 1347 / 180 (412), 1024 x 16 597 / 486 (537), 1000 x 33 1285 / 1151 (1190),
+// 64 x 1 31 / 56.
 bool pack_pays(const Gemm &g) {
-    if (g.seq_T > 32 || g.nv == 0 || !offsets_fit(g, 128)) return false;
+    if (g.seq_T > 64 || g.nv == 0 || !offsets_fit(g, 128)) return false;
     const int64_t tiles = (g.M / g.seq_T + packed(g, 128) - 1) / packed(g, 128);
     const double saved = ((double)g.n_tok - (g.dtype == F32 ? 1.25 : 1.75) * 128 * (double)tiles) * 2.0 * g.nv * g.K;
     return saved >= (g.dtype == F32 ? 2.4e9 : 2.4e10);

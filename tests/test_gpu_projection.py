@@ -36,6 +36,7 @@ ROUTES = [
     (4001, 16, 2048, 16, 16, 64, "bf16", 0.0),    # ... 8 per tile, the longest that pays
     (1001, 5, 256, 16, 16, 16, "f32", 0.0),       # ... fp32
     (2500, 1, 512, 4, 4, 64, "f32", 0.0),         # ... one token
+    (500, 41, 256, 10, 10, 64, "f32", 0.0),       # ... two blocks of positions per sequence
     (1, 65, 128, 4, 1, 128, "bf16", 1e4),         # rotary 128-tile, head_dim 128
     (2, 77, 96, 8, 4, 64, "f16", 1e4),            # rotary 128-tile, head_dim 64, k-tiles of 32
     (5, 777, 512, 32, 8, 64, "bf16", 1e4),        # rotary 256-tiles, ragged, head_dim 64
