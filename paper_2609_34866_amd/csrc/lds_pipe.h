@@ -31,15 +31,15 @@ __device__ inline void lds_dma4(const void *src, unsigned char *dst) {
 // ring themselves: it cannot tell a ring's transposed reads from the stage a transfer fills, and
 // would wait for all of them (and for every store behind them) before the first such read.  The
 // compiler's own counted waits stay valid: transfers it does not count only make them longer.
-// They set m0 behind its back: a kernel uses either these or the builtins above, not both.
-// (The 16-byte form takes a wave-uniform base and a byte offset per lane.)
+// (They name m0 as overwritten, so that the builtins above and any other instruction of the compiler's that reads
+// it set it again.  The 16-byte form takes a wave-uniform base and a byte offset per lane.)
 __device__ inline void lds_dma16_raw(const void *base, uint32_t off, const unsigned char *dst) {
     const uint32_t o = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(const lds_u8 *)dst);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(o), "v"(off), "s"(base) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(o), "v"(off), "s"(base) : "memory", "m0");
 }
 __device__ inline void lds_dma4_raw(const void *src, const unsigned char *dst) {
     const uint32_t o = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(const lds_u8 *)dst);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(o), "v"(src) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(o), "v"(src) : "memory", "m0");
 }
 
 // The same transfer in the MUBUF form (buffer_load_dwordx4 ... lds): a wave-uniform buffer

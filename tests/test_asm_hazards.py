@@ -57,3 +57,20 @@ def test_last_build_is_clean():
         assert build.mfma_result_hazards(text) == []
     if not found:
         pytest.skip("no generated assembly (build() not run here)")
+
+
+def test_asm_that_writes_m0_says_so():
+    """The compiler keeps m0 between its own instructions that read it (the LDS transfers): inline asm that
+    sets it has to name it among the overwritten registers."""
+    import re
+
+    seen = 0
+    csrc = build.CSRC
+    for name in sorted(os.listdir(csrc)):
+        text = open(os.path.join(csrc, name)).read()
+        for m in re.finditer(r"\basm\s*(?:volatile\s*)?\((.*?)\);", text, re.S):
+            code, _, rest = m.group(1).partition(":")
+            if re.search(r"\bm0\b", code):
+                seen += 1
+                assert '"m0"' in rest.rsplit(":", 1)[-1], (name, m.group(0))
+    assert seen >= 2
