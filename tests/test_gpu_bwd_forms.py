@@ -22,6 +22,7 @@ FORMS = [
     (1, 67, 64, 12, 1, 128, 32, "f16"),       # two slices, a group of twelve
     (97, 65, 64, 2, 2, 128, 32, "bf16"),      # four slices
     (193, 40, 64, 2, 2, 128, 32, "bf16"),     # paired
+    (513, 40, 64, 2, 2, 64, 32, "f16"),       # paired at head_dim 64 (with the KL term from 257 pairs on)
 ]
 
 
