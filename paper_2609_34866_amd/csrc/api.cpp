@@ -998,8 +998,8 @@ jab_status jab_loss_sweep(const jab_problem *p, const void *x, const void *w, in
     }
     // 2. one score matrix per (b_Q, b_K), applied to the value tensors of up to attn_max_nv triples; the
     // sets of one size in launches of up to ATT_MAX_SETS, which fill the chip where one set does not and
-    // leave one tail instead of many (us, one launch per set / per 16: {2,3,4,8}^3 of 8 x 2048 Mistral tokens
-    // 14990 / 14740, 1 x 1024 993 / 825, GPT-2 4 x 512 361 / 249, tiny fp32 4 x 128 580 / 83)
+    // leave one tail instead of many (us, one launch per set / per 16: {2,3,4,8}^3 of 1 x 1024 Mistral tokens
+    // 935 / 747, 8 x 2048 14710 / 14450 with 180 between runs, GPT-2 4 x 512 344 / 234, tiny fp32 4 x 128 606 / 91)
     struct Group {
         int iq, ik, nv, iv[4], ip[4];
     };

@@ -31,8 +31,9 @@
 //      one before; for grids that do not fill the chip twice, and the KL term at head_dim 128.
 //    - attn_bwd_dkdv_dma_kernel: a workgroup takes the 128-key blocks p and nkb - 1 - p (the same
 //      number of tiles for all), tile after tile, two workgroups per CU.
-//    What bounds both once the chip is full: LDS reads (a wave reads 32 KiB of fragments for the 32
-//    matrix instructions of a tile at head_dim 128; 1.2 us for the four waves' tile in either form).
+//    What bounds the paired form once the chip is full is not one unit (16 x 2048 tokens, head_dim 128, counters
+//    of the launch): matrix cores 45 % busy, the LDS data path 29 % of its cycles, no bank conflicts, each
+//    wave at a wait for 47 % of its time, two waves per SIMD.  Either form takes 1.2 us for four waves' tile.
 //  * dQ from the stored dS: a wave owns 32 queries of one query head; the workgroup's waves
 //    share a kv head and walk its 32-key tiles, each wave's dS tiles riding the same LDS ring
 //    and read transposed into the B operand of dQ^T += K^T dS^T (5 products in all).

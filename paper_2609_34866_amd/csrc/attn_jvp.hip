@@ -394,9 +394,9 @@ __global__ __launch_bounds__(256, 1) void attn_jvp_kernel(JvpArgs a, float scale
 // so 1.64; attn_jvp_kernel 2.30.)
 // Queries that are not flagged keep their reference, so their arithmetic is the same in both passes.  fp16, whose
 // packed operands end at 2^16, keeps attn_jvp_kernel.
-// Measured, attn_jvp_kernel (two passes at head_dim 128, nothing overlapped) / this, us per probe: 4 x 2048
-// with 32 / 8 heads of 128 1457 / 519 (41 % matrix-core busy), 1 x 999 174 / 56, 8 x 1024 with 12 heads of
-// 64 185 / 98.  About 1.4 us per block (56 products, 0.9 us, and 215 + 16 vector operations that share
+// Measured, attn_jvp_kernel (two passes at head_dim 128, nothing overlapped) / this, us per probe in a kernel
+// trace of 40 calls: 4 x 2048 with 32 / 8 heads of 128 1622 / 542 (887 TFLOP/s on the seven products), 1 x 999
+// 176 / 59, 8 x 1024 with 12 heads of 64 189 / 109.  About 1.4 us per block (56 products, 0.9 us, and 215 + 16 vector operations that share
 // the wave's issue slots) and 19 us per tile (loads, start-up, epilogue).  A rescale inside the one
 // pass made the compiler move all 256 accumulators through the architectural registers every block.
 template <int DT, int DH>

@@ -110,7 +110,7 @@ hipError_t launch_lsq_scale_grad(const QuantShape &sh, int dtype, const void *w,
 // Causal GQA flash attention over one batch of sequences.
 //   q/k: element pointers with Q(b,t,h,c) = q[(b*T + t)*ld + h*dh + c] (k with the key/value
 //   head index); v[i]: transposed values, V(b,t,g,c) = v[(g*dh + c)*ldv + b*Tp + vt_perm(t)]
-//   with Tp = T rounded up to 32 (as written by launch_gemm_nt_vt); nv value tensors share
+//   with Tp = T rounded up to 32 (as written by launch_project); nv value tensors share
 //   one score matrix.
 //   mode: bit flags ATT_LOSS (read a_ref, write (sse, sum a_ref^2) per wave into
 //   partials), ATT_STORE_O (store the output, fp32, into a_out), ATT_STORE_LSE (store

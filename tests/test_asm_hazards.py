@@ -1,4 +1,4 @@
-"""The build's check of the inline-asm matrix products (attn_fwd_fast.h's mma_v): no instruction may
+"""The build's check of the inline-asm matrix products (mfma_asm.h's mma_v): no instruction may
 access a product's architectural-register result within the hazard window, except the next product
 of its chain.  The checker against hand-written cases, and the generated assembly of the last build."""
 import os
