@@ -362,7 +362,8 @@ AttnBwdArgs sequences(const AttnBwdArgs &a, int b0, int n) {
 // chip's waves (one per SIMD) anyway, since four leave waves without a tile at each block's end and in every block
 // of few tiles, and add their sums.  In times of a tile: the longest block, or all tiles over 4 x 256 waves
 // (0.8 of a tile per block for its start and end); four waves' steps over 256 workgroups (1.3 per block).  shared:
-// the kernel's registers let two such workgroups share a CU, which hides more of theirs.
+// the kernel's registers let two such workgroups share a CU (dQ below head_dim 128), which hides more of theirs.
+// The same with the KL term as without, so lambda = 0 gives the squared error's gradients bit for bit.
 // us, four waves / one (and 128-row workgroups before): dK/dV GPT-2 1000 x 33 tokens 1207 / 319 (707), 100 x 100
 // 244 / 100 (156), 8 x 512 132 / 99 (196), 3 x 333 39 / 62 (76); 32 / 8 heads of 128 64 x 33 117 / 89 (173),
 // 16 x 100 83 / 159 (181), 8 x 512 403 / 637 (695).  dQ GPT-2 1000 x 33 480 / 225 (536), 20 x 333 103 / 83
@@ -398,7 +399,7 @@ hipError_t run(const AttnBwdArgs &a, hipStream_t st) {
             ? launch(attn_bwd_dkdv_f32_kernel<DH, KL, 1>, 1, a.n_kv_heads, f32_lds_bytes<DH, KL, 1>(2))
             : launch(attn_bwd_dkdv_f32_kernel<DH, KL, 4>, 4, a.n_kv_heads, f32_lds_bytes<DH, KL, 4>(2));
     if (e != hipSuccess) return e;
-    return one_wave(nb, 1, (int64_t)a.n_heads * a.batch, DH == 16 || (DH == 64 && !KL))
+    return one_wave(nb, 1, (int64_t)a.n_heads * a.batch, DH < 128)
                ? launch(attn_bwd_dq_f32_kernel<DH, KL, 1>, 1, a.n_heads, f32_lds_bytes<DH, KL, 1>(1))
                : launch(attn_bwd_dq_f32_kernel<DH, KL, 4>, 4, a.n_heads, f32_lds_bytes<DH, KL, 4>(1));
 }

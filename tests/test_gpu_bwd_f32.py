@@ -46,3 +46,22 @@ def test_more_workgroups_than_one_launch_takes():
         # 2^-24 per addition, 262144 of them in up to sixteen parts
         assert float((dv - want).norm()) <= 1e-4 * float(want.norm())
         assert float(dw[:-hkv * dh].double().norm()) <= 1e-4 * float(want.norm())
+
+
+@pytest.mark.parametrize("dh", [16, 64, 128])
+@pytest.mark.parametrize("B,T,hq,hkv", [(1, 161, 4, 2), (8, 512, 12, 12), (20, 100, 12, 12), (150, 40, 4, 4), (16, 100, 8, 2)])
+def test_lambda_zero_is_the_plain_backward(B, T, hq, hkv, dh):
+    """The KL form takes the same number of waves and the same order of sums: equal bits, for blocks of one wave
+    and of four."""
+    p = jab.problem(B, T, 64, hq, hkv, dh, 32, torch.float32)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    x = torch.randn((B, T, 64), generator=gen, device="cuda")
+    w = torch.randn((p.rows, 64), generator=gen, device="cuda") * 0.1
+    bits = (3, 4, 2)
+    scale, zero = jab.quant_init(p, w, bits)
+    a, qk, lse = jab.attn_ref_kl(p, x, w)
+    gam = jab.lsq_gscale(bits, 32)
+    _, dw, ds = jab.loss_bwd(p, x, w, bits, scale, zero, a, gam)
+    _, dw0, ds0 = jab.loss_bwd_kl(p, x, w, bits, scale, zero, a, qk, lse, gam, 0.0)
+    assert torch.equal(dw, dw0) and torch.equal(ds, ds0)
