@@ -33,7 +33,7 @@
  *   output untouched.  jab_last_error() returns a per-thread description.
  *   A HIP launch error returns JAB_E_HIP; asynchronous device faults surface
  *   at the caller's next synchronisation.
- * - Results are deterministic: no atomics on any reduction, fixed reduction
+ * - Results are deterministic: no atomics on any sum, fixed reduction
  *   order, so two identical calls produce bitwise-identical outputs.
  *
  * Layouts (row-major)
